@@ -70,9 +70,8 @@ struct Mult {
 // this form because their stores, spaced by the longer instruction stream,
 // write faster on MI355X (same GPU, same shapes: plain u64 6.8-6.9 against
 // 5.8 TB/s, interleaved batch 6.1 against 5.8 TB/s).  The fused consumer,
-// bound by its arithmetic, uses nn_dev_mulmod (VarFP64Fused).  Translation
-// units are built with FP contraction off so no product is fused into a
-// neighbouring add.
+// bound by its arithmetic, uses mm_bal below.  Translation units are built
+// with FP contraction off so no product is fused into a neighbouring add.
 NN_HD double mm_fp64(double z, double v, double qh, double ql) {
     const double mod = (double)kMod;
     const double ph = v * z;
@@ -83,6 +82,40 @@ NN_HD double mm_fp64(double z, double v, double qh, double ql) {
     const double r = (ph - sh) + (pl - sl);
     return r < 0.0 ? r + mod : r;
 }
+
+// ------------------------------------------------------- balanced FP64 --
+// The step on balanced representatives, for a consumer that needs the sum of
+// the states and not each of them reduced to [1, m): a state is an integer r
+// congruent to z with |r| < 0.6 m, the multiplier v' one of v, v - m with
+// |v'| < m/2, and q' = RN(v'/m).  Six instructions against nn_dev_mulmod's
+// eleven: no conditional add, and one product of the quotient instead of two.
+// With 2^52 < m = 1.2344 * 2^52:
+//  * |r q'| < 0.3 m < 2^51, so fma(r, q', 1.5*2^52) lies in [2^52, 2^53),
+//    where doubles are the integers, and is r q' rounded once to an integer:
+//    q, after the exact subtraction, is within 1/2 of r q', and r q' within
+//    |r| 2^-55 < 0.0926 of r v'/m (|q'| < 1/2 carries at most 2^-55 of
+//    error).  So the new r = v' r - q m is an integer with |r| < 0.593 m,
+//    which closes the bound;
+//  * |v' r| < 0.3 m^2 < 2^103, so ph's unit is at most 2^50 and |pl| <= 2^49;
+//    ph - q m = r_new - pl is an integer below 0.593 m + 2^49 < 2^53, so the
+//    FMA is exact, and so is the last add.
+// A state in (0, m) enters as z or z - m, whichever is the smaller.
+struct BalMult {
+    double v;  // v or v - m, |v| < m/2
+    double q;  // RN(v/m)
+};
+
+constexpr double kBalRound = 6755399441055744.0;  // 1.5 * 2^52
+
+NN_HD double mm_bal(double r, BalMult f) {
+    const double ph = f.v * r;
+    const double pl = __builtin_fma(f.v, r, -ph);
+    const double q = __builtin_fma(r, f.q, kBalRound) - kBalRound;
+    return __builtin_fma(-q, kModD, ph) + pl;
+}
+
+// The balanced representative of a state z in (0, m).
+NN_HD double balanced(double z) { return z > 0.5 * kModD ? z - kModD : z; }
 
 // ------------------------------------------------------------- Barrett --
 // Algorithm Barrett (Section 3.1) with k = 53: q1 = x >> 52,
@@ -137,14 +170,6 @@ struct VarFP64 {
     typedef double S;
     static NN_HD S load(uint64_t x) { return (double)x; }
     static NN_HD S mul(S z, const Mult& f) { return mm_fp64(z, f.v, f.qh, f.ql); }
-    static NN_HD uint64_t to_u64(S z) { return (uint64_t)z; }
-    static NN_HD double to_f64(S z) { return z * kRecip; }
-};
-// The FP64 state with nn_dev_mulmod's shorter reduction (fused consumer).
-struct VarFP64Fused {
-    typedef double S;
-    static NN_HD S load(uint64_t x) { return (double)x; }
-    static NN_HD S mul(S z, const Mult& f) { return nn_dev_mulmod(z, nn_dev_mult{f.v, f.qh, f.ql}); }
     static NN_HD uint64_t to_u64(S z) { return (uint64_t)z; }
     static NN_HD double to_f64(S z) { return z * kRecip; }
 };

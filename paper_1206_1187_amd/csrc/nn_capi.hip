@@ -410,7 +410,7 @@ int nn_consume(uint64_t* state, uint64_t count, int kind, void* result_dev, void
     if (c.flags || c.occupancy || (c.width && c.width != 2) || (c.ilp && c.ilp != 2) || c.unroll)
         return fail(NN_EINVAL, "nn_consume takes block, grid and mulmod only");
     const KindDefaults& kd = kind_defaults(NN_OUT_F64);
-    const uint32_t block = c.block ? c.block : kDefaultBlock;
+    const uint32_t block = c.block ? c.block : kConsumeBlock;
     if (block < 64 || block > 1024 || block % 64)
         return fail(NN_EINVAL, "block %u: must be a multiple of 64 in [64, 1024]", block);
     const uint32_t mulmod = c.mulmod ? c.mulmod : kd.mulmod;
@@ -419,24 +419,23 @@ int nn_consume(uint64_t* state, uint64_t count, int kind, void* result_dev, void
                     mulmod);
     uint32_t grid = c.grid;
     if (!grid) {
-        // No stores to keep sequential: fill the device.
-        const uint64_t need = (count + 2ull * block - 1) / (2ull * block);
-        const uint64_t cap = (uint64_t)(d->cus > 0 ? d->cus : 1) * 8;
-        grid = (uint32_t)(need < cap ? (need ? need : 1) : cap);
+        const uint64_t need = (count - 1) / (kConsumeMinRows * block) + 1;
+        const uint64_t cap = (uint64_t)(d->cus > 0 ? d->cus : 1) * kConsumeBlock / block *
+                             (count >= kConsumeTwoPerCu ? 2 : 1);
+        grid = (uint32_t)(need < cap ? need : cap);
     }
     if ((uint64_t)grid * block > kMaxThreads)
         return fail(NN_EINVAL, "grid*block exceeds %llu threads", (unsigned long long)kMaxThreads);
-    GenArgs a;
-    a.out = nullptr;
+    ConsumeArgs a;
     a.T = (uint64_t)grid * block;
-    const uint64_t row = 2 * a.T;
-    a.e_full = count / row;
-    a.rem = (uint32_t)(count % row);
+    a.e_full = count / a.T;
+    a.rem = (uint32_t)(count % a.T);
     a.base = h_mulmod(s, kMult);
-    const uint64_t jump = MultPowers::get().pow(row);
-    a.J = make_mult(jump);
-    a.M1 = make_mult(kMult);
-    a.JI = make_mult(MultPowers::get().pow(2 * row));
+    uint64_t jump = MultPowers::get().pow(a.T);
+    for (int k = 0; k < 3; ++k, jump = h_mulmod(jump, jump)) {
+        a.J[k] = make_mult(jump);
+        a.B[k] = make_bal(jump);
+    }
     a.t_lo = d->t_lo;
     a.t_hi = d->t_hi;
     hipError_t e = launch_consume((int)mulmod, kind, grid, block, (hipStream_t)stream, a, result_dev);

@@ -92,4 +92,14 @@ inline Mult make_mult(uint64_t v) {
     return f;
 }
 
+// The balanced form of a multiplier (mm_bal): v or v - m, the one below m/2
+// in magnitude, and its rounded quotient by m (qh + ql carries 106 bits of
+// v/m, so their sum rounds to nearest).
+inline BalMult make_bal(uint64_t v) {
+    const bool low = v <= kMod / 2;
+    const Mult f = make_mult(low ? v : kMod - v);
+    const double q = f.qh + f.ql;
+    return low ? BalMult{f.v, q} : BalMult{-f.v, -q};
+}
+
 }  // namespace nn

@@ -142,83 +142,172 @@ __global__ __launch_bounds__(1024) void k_generate2_ilp(uint64_t* __restrict__ o
 }
 
 // Fused consumer (the paper's point that variates usually feed a simulation
-// directly, Section 3.2; its Table 2 removes the memory traffic): the same
-// generation as k_generate2_ilp with IL = 2, the outputs summed in
-// registers.  Kind 0 sums raw states modulo 2^64 (exact in any order).
+// directly, Section 3.2; its Table 2 removes the memory traffic): the outputs
+// are summed in registers and never stored.  Kind 0 sums raw states modulo
+// 2^64 (exact in any order).
+
+// The sum of v over a workgroup, valid in thread 0 (every thread calls it, once
+// per type: a second call would write the LDS that the first still reads).
+template <class X>
+__device__ __forceinline__ X block_sum(X v) {
+    __shared__ X part[16];
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    const uint32_t w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) part[w] = v;
+    __syncthreads();
+    v = threadIdx.x < (blockDim.x >> 6) ? part[threadIdx.x] : X(0);
+    if (w == 0)
+        for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+// The integer reductions, four rows in flight per thread.
 template <class V, int KIND>
-__global__ __launch_bounds__(1024) void k_consume(uint64_t T, uint64_t e_full, uint32_t rem,
-                                                  uint64_t base, Mult J, Mult M1, Mult JI,
-                                                  const Mult* __restrict__ t_lo,
-                                                  const Mult* __restrict__ t_hi, void* result) {
+__global__ __launch_bounds__(1024) void k_consume(ConsumeArgs a, void* result) {
     const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-    typename V::S za0 = thread_start<V>(base, 2ull * t, t_lo, t_hi);
-    typename V::S zb0 = V::mul(za0, M1);
-    typename V::S za1 = V::mul(za0, J);
-    typename V::S zb1 = V::mul(zb0, J);
-    uint64_t su = 0;
+    typename V::S z[4];
+    z[0] = thread_start<V>(a.base, t, a.t_lo, a.t_hi);
+    z[1] = V::mul(z[0], a.J[0]);
+    z[2] = V::mul(z[0], a.J[1]);
+    z[3] = V::mul(z[1], a.J[1]);
+    unsigned long long su = 0;
     double sf = 0.0;
-    auto take = [&](typename V::S z) {
+    auto take = [&](typename V::S x) {
         if constexpr (KIND == 0)
-            su += V::to_u64(z);
+            su += V::to_u64(x);
         else
-            sf += V::to_f64(z);
+            sf += V::to_f64(x);
     };
     uint64_t i = 0;
-    for (; i + 2 <= e_full; i += 2) {
-        take(za0);
-        take(zb0);
-        take(za1);
-        take(zb1);
-        za0 = V::mul(za0, JI);
-        zb0 = V::mul(zb0, JI);
-        za1 = V::mul(za1, JI);
-        zb1 = V::mul(zb1, JI);
+    for (; i + 4 <= a.e_full; i += 4) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            take(z[c]);
+            z[c] = V::mul(z[c], a.J[2]);
+        }
     }
-    typename V::S pa = za0, pb = zb0;
-    if (i < e_full) {  // one full row left
-        take(za0);
-        take(zb0);
-        pa = za1;
-        pb = zb1;
+    const uint32_t left = (uint32_t)(a.e_full - i);  // full rows left, then the partial row
+#pragma unroll
+    for (uint32_t c = 0; c < 4; ++c)
+        if (c < left || (c == left && t < a.rem)) take(z[c]);
+    if constexpr (KIND == 0) {
+        su = block_sum(su);
+        if (threadIdx.x == 0) atomicAdd(static_cast<unsigned long long*>(result), su);
+    } else {
+        sf = block_sum(sf);
+        if (threadIdx.x == 0) atomicAdd(static_cast<double*>(result), sf);
     }
-    const uint32_t rem_pairs = rem >> 1;
-    if (t < rem_pairs) {
-        take(pa);
-        take(pb);
-    } else if ((rem & 1u) && t == rem_pairs) {
-        take(pa);
+}
+
+// The FP64 reduction on balanced states (mm_bal): a state z is r or r + m, so
+// the sum of the states is the sum of the r plus m for every negative one.
+// Bound by the VALU: per output six instructions for the step, one compare
+// whose mask the scalar unit counts, and the sum's:
+//  * kind 1: one add.  The partial sums of balanced states stay near zero, so
+//    they round less than sums of variates do, and the conversion is one
+//    product per workgroup.
+//  * kind 0: the exact sum, one add per pair (|r + r'| < 1.2 m < 2^53) and
+//    three that split it into multiples of 2^26 (added to hi, which starts at
+//    1.5 * 2^78 where the unit is 2^26) and the rest (below 2^26, added to
+//    lo): exact for 2^24 pairs, so hi and lo are emptied every 2^20 trips.
+// Four rows in flight per thread: four independent chains.  2^30 variates: 258
+// us, 4.16e12 a second (85 % of the VALU's rate for eight instructions an
+// output at 2.4 GHz), against 421 us with nn_dev_mulmod's step and a
+// conversion per variate; 2^30 raw states 304 us against 600.
+template <int KIND>
+__global__ __launch_bounds__(1024) void k_consume_bal(ConsumeArgs a, void* result) {
+    constexpr double kSplit = 453347182355485940514816.0;  // 1.5 * 2^78
+    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
+    double z[4];
+    z[0] = balanced(thread_start<VarFP64>(a.base, t, a.t_lo, a.t_hi));
+    z[1] = mm_bal(z[0], a.B[0]);
+    z[2] = mm_bal(z[0], a.B[1]);
+    z[3] = mm_bal(z[1], a.B[1]);
+    double hi[2] = {kSplit, kSplit}, lo[2] = {0.0, 0.0};  // kind 0
+    double sf[4] = {0.0, 0.0, 0.0, 0.0};                  // kind 1
+    unsigned long long su = 0;
+    uint64_t negative = 0;  // of the whole wavefront; neg: since the last emptying
+    uint32_t neg = 0;
+    auto split = [&](int k, double x) {
+        const double h = hi[k] + x;
+        lo[k] += x - (h - hi[k]);
+        hi[k] = h;
+    };
+    auto empty = [&] {
+        negative += neg;
+        neg = 0;
+#pragma unroll
+        for (int k = 0; k < 2 && KIND == 0; ++k) {
+            su += ((unsigned long long)(long long)((hi[k] - kSplit) * 0x1p-26) << 26) +
+                  (unsigned long long)(long long)lo[k];
+            hi[k] = kSplit;
+            lo[k] = 0.0;
+        }
+    };
+    auto count = [&](double r) {
+        neg += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(r < 0.0));
+    };
+    uint64_t trips = a.e_full >> 2;
+    while (trips) {
+        const uint32_t n = trips < (1u << 20) ? (uint32_t)trips : 1u << 20;
+        trips -= n;
+        for (uint32_t i = 0; i < n; ++i) {
+            if constexpr (KIND == 0) {
+                split(0, z[0] + z[1]);
+                split(1, z[2] + z[3]);
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if constexpr (KIND == 1) sf[c] += z[c];
+                count(z[c]);
+                z[c] = mm_bal(z[c], a.B[2]);
+            }
+        }
+        empty();
     }
-    // Reduce across the wavefront, then one atomic per wavefront.
-    for (int off = 32; off > 0; off >>= 1) {
-        if constexpr (KIND == 0)
-            su += (uint64_t)__shfl_xor((unsigned long long)su, off, 64);
-        else
-            sf += __shfl_xor(sf, off, 64);
+    const uint32_t left = (uint32_t)a.e_full & 3u;  // full rows left, then the partial row
+#pragma unroll
+    for (uint32_t c = 0; c < 4; ++c) {
+        if (c < left || (c == left && t < a.rem)) {
+            count(z[c]);
+            if constexpr (KIND == 0)
+                su += (unsigned long long)(long long)z[c];
+            else
+                sf[c] += z[c];
+        }
     }
-    if ((threadIdx.x & 63) == 0) {
-        if constexpr (KIND == 0)
-            atomicAdd(reinterpret_cast<unsigned long long*>(result), (unsigned long long)su);
-        else
-            atomicAdd(reinterpret_cast<double*>(result), sf);
+    negative = (threadIdx.x & 63) == 0 ? negative + neg : 0;  // the wavefront's count, once
+    if constexpr (KIND == 0) {
+        su = block_sum(su + negative * kMod);
+        if (threadIdx.x == 0) atomicAdd(static_cast<unsigned long long*>(result), su);
+    } else {
+        negative = block_sum(negative);
+        const double s = block_sum((sf[0] + sf[1]) + (sf[2] + sf[3]));
+        if (threadIdx.x == 0)
+            atomicAdd(static_cast<double*>(result),
+                      __builtin_fma((double)negative, kModD, s) * kRecip);
     }
 }
 
 template <class V>
 static hipError_t consume_v(int kind, uint32_t grid, uint32_t block, hipStream_t s,
-                            const GenArgs& a, void* result) {
+                            const ConsumeArgs& a, void* result) {
     if (kind == 0)
-        hipLaunchKernelGGL((k_consume<V, 0>), dim3(grid), dim3(block), 0, s, a.T, a.e_full,
-                           a.rem, a.base, a.J, a.M1, a.JI, a.t_lo, a.t_hi, result);
+        k_consume<V, 0><<<grid, block, 0, s>>>(a, result);
     else
-        hipLaunchKernelGGL((k_consume<V, 1>), dim3(grid), dim3(block), 0, s, a.T, a.e_full,
-                           a.rem, a.base, a.J, a.M1, a.JI, a.t_lo, a.t_hi, result);
+        k_consume<V, 1><<<grid, block, 0, s>>>(a, result);
     return hipGetLastError();
 }
 
 hipError_t launch_consume(int mulmod, int kind, uint32_t grid, uint32_t block, hipStream_t s,
-                          const GenArgs& a, void* result) {
+                          const ConsumeArgs& a, void* result) {
     switch (mulmod) {
-        case 1: return consume_v<VarFP64Fused>(kind, grid, block, s, a, result);
+        case 1:
+            if (kind == 0)
+                k_consume_bal<0><<<grid, block, 0, s>>>(a, result);
+            else
+                k_consume_bal<1><<<grid, block, 0, s>>>(a, result);
+            return hipGetLastError();
         case 2: return consume_v<VarBarrett>(kind, grid, block, s, a, result);
         case 3: return consume_v<VarShoup>(kind, grid, block, s, a, result);
         case 4: return consume_v<VarMontgomery>(kind, grid, block, s, a, result);

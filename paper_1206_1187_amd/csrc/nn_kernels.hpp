@@ -41,12 +41,36 @@ hipError_t launch_generate(int mulmod, int kind, int width, int unroll, int ilp,
                            bool nontemporal, uint32_t grid, uint32_t block, hipStream_t stream,
                            const GenArgs& a);
 
-// Fused consumer: the row layout's states (W = 2, IL rows in flight) are
-// consumed in registers instead of stored: each thread adds its outputs
-// (raw states modulo 2^64 for kind 0, variates in binary64 for kind 1) and
-// one atomic per thread folds the partial sums into *result.
+// Fused consumer: T = grid*block threads, thread t taking the outputs t, t + T,
+// t + 2T, ... in registers and adding them up (raw states modulo 2^64 for
+// kind 0, variates in binary64 for kind 1); one atomic per workgroup folds
+// the sums into *result.  count = e_full*T + rem with rem < T; `base` is
+// state * 2^53 and J[k] = (2^53)^(T 2^k): the steps by one, two and four rows.
+struct ConsumeArgs {
+    uint64_t T;
+    uint64_t e_full;
+    uint32_t rem;
+    uint64_t base;
+    Mult J[3];
+    BalMult B[3];  // the same multipliers balanced (the FP64 reduction)
+    const Mult* t_lo;
+    const Mult* t_hi;
+};
+
+// Workgroups of the default launch.  Every workgroup ends in one atomic on
+// the same address, and those are served one after another at about 12 ns
+// each (8192 of them, one per wavefront, held a call of any size up at
+// 100 us), so the workgroups are as large as they come, at most one per
+// compute unit, and a thread has at least kConsumeMinRows outputs.  From
+// kConsumeTwoPerCu outputs on two per compute unit hide more latency than
+// their atomics cost (2^28 variates: 66.4 against 69.2 us; 10,000,019: 11.2
+// against 9.2).
+constexpr uint32_t kConsumeBlock = 1024;
+constexpr uint64_t kConsumeMinRows = 8;
+constexpr uint64_t kConsumeTwoPerCu = 1ull << 27;
+
 hipError_t launch_consume(int mulmod, int kind, uint32_t grid, uint32_t block, hipStream_t s,
-                          const GenArgs& a, void* result);
+                          const ConsumeArgs& a, void* result);
 
 // Flat layout: workgroup b of 256 threads writes R rows of 512 elements,
 // [512 R b, 512 R (b + 1)) of the launch, two consecutive ones per lane in

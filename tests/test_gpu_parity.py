@@ -463,6 +463,30 @@ def test_fused_consumer_state_sum_exact(mulmod):
         assert abs(float(resf.cpu()[0]) - exact) <= bound, (count, float(resf.cpu()[0]), exact)
 
 
+@pytest.mark.parametrize("block,grid", [(0, 0), (64, 1), (1024, 3), (192, 700)])
+def test_fused_consumer_balanced_edges(block, grid):
+    """The FP64 consumer's balanced states at the edges of its rows: one
+    output, a wavefront and one more, four rows (the trip of its loop) of T
+    threads less one, exactly and one more, and a partial fifth row; from a
+    state whose next output is 1 (the smallest) as well.  The raw sum is exact;
+    the variate sum is held to (n - 1) * 2^-53 of the correctly rounded sum of
+    the oracle's variates, the bound of adding n positive terms in any order,
+    plus two final roundings."""
+    T = (block or 1024) * (grid or 1)
+    for z0 in (orc.seed(wl.INDEX_MIN + 1), orc.skip(1, wl.PERIOD - 1)):
+        ref, _ = orc.gen(z0, 4 * T + T // 2, "u64", threads=0)
+        reff, _ = orc.gen(z0, 4 * T + T // 2, "f64", threads=0)
+        for count in sorted({1, 64, 65, T, 4 * T - 1, 4 * T, 4 * T + 1, 4 * T + T // 2}):
+            cfg = nn.make_cfg(block=block, grid=grid)
+            res, zn = nn.consume(z0, count, "u64", cfg=cfg)
+            resf, _ = nn.consume(z0, count, "f64", cfg=cfg)
+            got = int(res.view(torch.int64).cpu().numpy().view(np.uint64)[0])
+            assert got == int(ref[:count].sum(dtype=np.uint64)), count
+            assert zn == int(ref[count - 1])
+            exact = math.fsum(reff[:count].tolist())
+            assert abs(float(resf.cpu()[0]) - exact) <= (count + 1) * 2.0 ** -53 * exact, count
+
+
 def test_consecutive_layout_bit_exact():
     """The consecutive layout (the paper's per-thread loop with the Modified
     Barrett step, serial order restored through LDS): tile sizes from 2 to
