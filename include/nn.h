@@ -73,12 +73,13 @@ typedef enum nn_mulmod {
  *
  * Three layouts write the same values (serial order in memory):
  *  - flat (NN_CFG_FLAT; the default for a cfg that sets none of block,
- *    grid, ilp or width 1, on an output that is 16-byte aligned or, with
- *    width 0, holds at least 2^22 outputs): every 256-thread workgroup writes `unroll` rows of 512
- *    consecutive outputs (one contiguous chunk), two per lane in one
- *    16-byte store per row, and exits; an output that is only 8-byte
- *    aligned gets its first element from a one-workgroup launch and the
- *    rest 16-byte aligned.  With 4 rows the chunks are
+ *    grid, ilp or width 1, on an output that is 16-byte aligned, or that
+ *    holds at least 2^22 outputs with width 0, or with a cfg that sets only
+ *    mulmod and the store policy): every 256-thread workgroup writes `unroll`
+ *    rows of 512 consecutive outputs (one contiguous chunk), two per lane in
+ *    one 16-byte store per row, and exits; the same launch writes a partial
+ *    last chunk and, for an output that is only 8-byte aligned, its first
+ *    element, the rest being 16-byte aligned.  With 4 rows the chunks are
  *    taken in XCD runs: of every 2048 consecutive chunks, each of the 8
  *    XCDs (which take consecutive workgroups in turn) writes 256
  *    consecutive ones (4 MiB); chunks after the last full run, and every

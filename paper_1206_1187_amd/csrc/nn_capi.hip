@@ -28,6 +28,7 @@ namespace {
 struct Resolved {
     uint32_t block, grid, mulmod, unroll, width, occupancy, ilp;
     bool nontemporal, flat, consec, strided;
+    bool small_unaligned;  // flat by the rule for small outputs that are only 8-byte aligned
     bool xcd_runs;  // flat, 4 rows: whole chunks in XCD runs (NN_CFG_ADDRESS_ORDER clears it)
     uint32_t lds;  // dynamic LDS bytes per workgroup that cap residency
 };
@@ -59,7 +60,7 @@ int resolve_cfg(const nn_launch_cfg* cfg, int kind, uint64_t count, const Device
     r->strided = (c.flags & NN_CFG_PAPER_STRIDED) != 0;
     if ((c.flags & NN_CFG_ADDRESS_ORDER) && (r->consec || r->strided || (c.flags & NN_CFG_ROWS)))
         return fail(NN_EINVAL, "NN_CFG_ADDRESS_ORDER applies to the flat layout only");
-    r->flat = false;
+    r->flat = r->small_unaligned = false;
     if (r->strided) {
         // The paper's layout: E consecutive elements per thread, stored
         // transposed (out[t + i*T] = element t*E + i), 8-byte stores.
@@ -138,14 +139,20 @@ int resolve_cfg(const nn_launch_cfg* cfg, int kind, uint64_t count, const Device
     // 8-byte aligned any width, which asks for the row layout's stores); it
     // wrote faster than the row layout on every MI355X measured, for both
     // kinds (2^30 f64: 6.9 against 6.7 TB/s; 2^28 u64: 6.65 against 6.05).
-    // An output that is only 8-byte aligned gets its first element from a
-    // one-workgroup launch and the rest, 16-byte aligned, as usual; below
-    // kFlatUnalignedMin outputs that extra launch costs more than the flat
-    // layout gains, and such outputs keep the row layout (one launch).
-    r->flat = (c.flags & NN_CFG_FLAT) != 0 ||
-              (!(c.flags & NN_CFG_ROWS) && !c.block && !c.grid && !c.ilp &&
-               (aligned16 ? c.width == 0 || c.width == 2
-                          : c.width == 0 && count >= kFlatUnalignedMin));
+    // An output that is only 8-byte aligned takes it at every size: the flat
+    // kernel adds its first element to the 16-byte aligned rest, and is ahead
+    // of the row layout's 8-byte stores (kernel times, f64: 1000 outputs 1.6
+    // against 2.0 us, 131,072 2.8 against 3.0, 2^20 4.1 against 5.0, 2^24 22
+    // against 31; at 20,000 both take 2.6).  Below kFlatUnalignedMin outputs a
+    // cfg that sets more than mulmod and the store policy keeps the row
+    // layout there, with the values that layout takes.
+    const bool any = !(c.flags & NN_CFG_ROWS) && !c.block && !c.grid && !c.ilp;
+    r->small_unaligned = any && !aligned16 && count < kFlatUnalignedMin && !c.width &&
+                         !c.unroll && !c.occupancy &&
+                         !(c.flags & (NN_CFG_FLAT | NN_CFG_ADDRESS_ORDER));
+    r->flat = (c.flags & NN_CFG_FLAT) != 0 || r->small_unaligned ||
+              (any && (aligned16 ? c.width == 0 || c.width == 2
+                                 : c.width == 0 && count >= kFlatUnalignedMin));
     if ((c.flags & NN_CFG_ADDRESS_ORDER) && !r->flat)
         return fail(NN_EINVAL, "NN_CFG_ADDRESS_ORDER applies to the flat layout only");
     r->occupancy = c.occupancy ? c.occupancy : (r->flat ? kFlatDefaultOccupancy : 0u);
@@ -217,6 +224,23 @@ int check_out(uint64_t count, void* out) {
     if ((uintptr_t)out > UINTPTR_MAX - count * 8)
         return fail(NN_ERANGE, "output range wraps the address space");
     return NN_OK;
+}
+
+// The next launch of a flat output of `count` outputs, of which `off` are
+// done: its pointers and chunk counts.  The first launch takes the first
+// element of an output that is only 8-byte aligned as its head.  Returns the
+// outputs it covers.
+uint64_t flat_slice(const Resolved& r, uint64_t* out, uint64_t off, uint64_t count, FlatArgs* f) {
+    const uint64_t per = (uint64_t)kFlatPerBlock * r.unroll;
+    const uint64_t head = off == 0 && (uintptr_t)out % 16 ? 1 : 0;
+    const uint64_t left = count - off - head;
+    const uint64_t n = left < kFlatMaxCount ? left : kFlatMaxCount;
+    f->head = head ? out : nullptr;
+    f->out = out + off + head;
+    f->full = (uint32_t)(n / per);
+    f->runs = (uint32_t)flat_run_chunks((int)r.unroll, r.xcd_runs, f->full);
+    f->tail = (uint32_t)(n % per);
+    return head + n;
 }
 
 }  // namespace
@@ -336,32 +360,15 @@ int nn_generate_ex(uint64_t* state, uint64_t count, void* out_dev, int kind, voi
         FlatArgs f;
         f.M1 = make_mult(kMult);
         f.J = make_mult(MultPowers::get().pow(kFlatPerBlock));
-        f.xcd_runs = r.xcd_runs;
-        // an output that is only 8-byte aligned: its first element alone
-        // (the tail kernel with one output), then the 16-byte aligned rest
-        const uint64_t head = ((uintptr_t)out_dev % 16) ? 1 : 0;
-        if (head) {
-            f.out = (uint64_t*)out_dev;
-            f.count = 1;
-            f.base = f.mid_base = f.tail_base = h_skip(s, 1);
-            hipError_t e = launch_generate_flat((int)r.mulmod, kind, r.nontemporal, (int)r.unroll,
-                                                r.lds, (hipStream_t)stream, f);
-            if (e != hipSuccess)
-                return fail(NN_EHIP, "generate launch: %s", hipGetErrorString(e));
+        f.head_state = h_skip(s, 1);
+        hipError_t e = hipSuccess;
+        for (uint64_t off = 0; off < count && e == hipSuccess;) {
+            off += flat_slice(r, (uint64_t*)out_dev, off, count, &f);
+            f.base = h_skip(s, (uint64_t)(f.out - (uint64_t*)out_dev) + 1);
+            e = launch_generate_flat((int)r.mulmod, kind, r.nontemporal, (int)r.unroll, r.lds,
+                                     (hipStream_t)stream, f);
         }
-        for (uint64_t off = head; off < count; off += kFlatMaxCount) {
-            const uint64_t n = count - off < kFlatMaxCount ? count - off : kFlatMaxCount;
-            f.out = (uint64_t*)out_dev + off;
-            f.count = n;
-            f.base = h_skip(s, off + 1);  // the first output of this chunk
-            const uint64_t per = (uint64_t)kFlatPerBlock * r.unroll;
-            f.mid_base = h_skip(f.base, flat_run_chunks((int)r.unroll, r.xcd_runs, n / per) * per);
-            f.tail_base = h_skip(f.base, n / per * per);
-            hipError_t e = launch_generate_flat((int)r.mulmod, kind, r.nontemporal, (int)r.unroll,
-                                                r.lds, (hipStream_t)stream, f);
-            if (e != hipSuccess)
-                return fail(NN_EHIP, "generate launch: %s", hipGetErrorString(e));
-        }
+        if (e != hipSuccess) return fail(NN_EHIP, "generate launch: %s", hipGetErrorString(e));
         *state = h_skip(s, count);
         return ok();
     }
@@ -460,23 +467,18 @@ int nn_fill(uint64_t count, void* out_dev, uint64_t value, void* stream, const n
     st = resolve_cfg(&c, NN_OUT_F64, count, *d, out_dev, &r);
     if (st) return st;
     if (r.consec || r.strided) return fail(NN_EINVAL, "nn_fill has no consecutive layout");
-    if (with_start && !r.flat) return fail(NN_EINVAL, "NN_FILL_WITH_START needs the flat layout");
+    if (with_start && (!r.flat || r.small_unaligned))
+        return fail(NN_EINVAL, "NN_FILL_WITH_START needs the flat layout");
     if (r.flat) {
-        // as nn_generate: an 8-byte aligned output's first element alone
-        const uint64_t head = ((uintptr_t)out_dev % 16) ? 1 : 0;
-        if (head) {
-            hipError_t e = launch_fill_flat(r.nontemporal, (int)r.unroll, r.lds,
-                                            (hipStream_t)stream, with_start, r.xcd_runs,
-                                            (uint64_t*)out_dev, 1, value);
-            if (e != hipSuccess) return fail(NN_EHIP, "fill launch: %s", hipGetErrorString(e));
+        FlatArgs f;
+        memset(&f, 0, sizeof f);
+        hipError_t e = hipSuccess;
+        for (uint64_t off = 0; off < count && e == hipSuccess;) {
+            off += flat_slice(r, (uint64_t*)out_dev, off, count, &f);
+            e = launch_fill_flat(r.nontemporal, (int)r.unroll, r.lds, (hipStream_t)stream,
+                                 with_start, f, value);
         }
-        for (uint64_t off = head; off < count; off += kFlatMaxCount) {
-            const uint64_t n = count - off < kFlatMaxCount ? count - off : kFlatMaxCount;
-            hipError_t e = launch_fill_flat(r.nontemporal, (int)r.unroll, r.lds,
-                                            (hipStream_t)stream, with_start, r.xcd_runs,
-                                            (uint64_t*)out_dev + off, n, value);
-            if (e != hipSuccess) return fail(NN_EHIP, "fill launch: %s", hipGetErrorString(e));
-        }
+        if (e != hipSuccess) return fail(NN_EHIP, "fill launch: %s", hipGetErrorString(e));
         return ok();
     }
     if (r.lds) return fail(NN_EINVAL, "occupancy applies to the flat layout only");

@@ -394,8 +394,8 @@ __device__ __forceinline__ uint64_t flat_chunk(uint64_t w) {
 // round trips of scalar-load latency than needed: the tables sit at a fixed
 // address (flat_sym), so their loads go out with the load of the base, the
 // whole-chunk kernel takes no count and tests nothing, and the table
-// indices are in range for every lane.  A ragged last chunk goes to
-// k_generate_flat_tail.
+// indices are in range for every lane.  It takes whole chunks only, all of
+// them in XCD runs or none; every other output goes to k_generate_flat_any.
 template <class V, int KIND, bool NT, int R, int G>
 __global__ __launch_bounds__(kFlatBlock) void k_generate_flat(uint64_t base,
                                                               uint64_t* __restrict__ out,
@@ -421,48 +421,72 @@ __global__ __launch_bounds__(kFlatBlock) void k_generate_flat(uint64_t base,
     }
 }
 
-// The last, partial chunk: `count` < kFlatPerBlock*R outputs from `out`,
-// one workgroup (b = 0 relative to `base`).
+// Any other output in one launch: its whole chunks (the first `runs` in XCD
+// runs), the partial last chunk, which the last workgroup writes pair by
+// pair, and the element before `out` of an output that is only 8-byte
+// aligned, which workgroup 0 adds.  The partial chunk and that element cost
+// nothing of their own, where each launch of their own (one workgroup, after
+// or before the others) took 3-4 us: 2^28 - 3 variates 308 -> 303 us,
+// 20,000,003 into an 8-byte aligned output 31.5 -> 24.9 us, 3,000,017 12.8 ->
+// 9.8 us.  The tests on `runs` and `full` hold a workgroup's table loads back
+// until its arguments are there, which the whole-chunk kernel avoids: on whole
+// runs that one stays ahead (2^23 variates 11.7 against 12.1 us, 2^30 1187
+// against 1193).
 template <class V, int KIND, bool NT, int R>
-__global__ __launch_bounds__(kFlatBlock) void k_generate_flat_tail(uint64_t base,
-                                                                   uint64_t* __restrict__ out,
-                                                                   Mult M1, Mult J,
-                                                                   uint64_t count) {
+__global__ __launch_bounds__(kFlatBlock) void k_generate_flat_any(FlatArgs a) {
+    extern __shared__ char occupancy_cap[];
+    (void)occupancy_cap;
+    const uint32_t w = blockIdx.x;
+    const uint32_t b = R == 4 && w < a.runs ? (uint32_t)xcd_run_index(w) : w;
     const uint32_t l = threadIdx.x;
     typename V::S za, zb;
-    flat_start_sym<V>(0, l, R, base, M1, za, zb);
-    uint64_t k = 2u * l;
-    for (int r = 0; r < R && k < count; ++r, k += kFlatPerBlock) {
-        if (k + 1 < count) {
+    flat_start_sym<V>(b, l, R, a.base, a.M1, za, zb);
+    const global_ptr<uint64_t> p = as_global(a.out) + ((uint64_t)kFlatPerBlock * R * b + 2u * l);
+    if (b < a.full) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
             u64x2 v;
             v.x = out_bits<V, KIND>(za);
             v.y = out_bits<V, KIND>(zb);
-            put<NT>(reinterpret_cast<u64x2*>(out + k), v);
-        } else {
-            put<NT>(out + k, out_bits<V, KIND>(za));
+            put<NT>(reinterpret_cast<global_ptr<u64x2>>(p + r * kFlatPerBlock), v);
+            if (r + 1 < R) {
+                za = V::mul(za, a.J);
+                zb = V::mul(zb, a.J);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        za = V::mul(za, J);
-        zb = V::mul(zb, J);
+    } else {
+        uint32_t k = 2u * l;
+        for (int r = 0; r < R && k < a.tail; ++r, k += kFlatPerBlock) {
+            if (k + 1 < a.tail) {
+                u64x2 v;
+                v.x = out_bits<V, KIND>(za);
+                v.y = out_bits<V, KIND>(zb);
+                put<NT>(reinterpret_cast<global_ptr<u64x2>>(p + r * kFlatPerBlock), v);
+            } else {
+                put<NT>(p + r * kFlatPerBlock, out_bits<V, KIND>(za));
+            }
+            za = V::mul(za, a.J);
+            zb = V::mul(zb, a.J);
+        }
     }
+    if (w == 0 && a.head && l == 0)
+        put<NT>(as_global(a.head), out_bits<V, KIND>(V::load(a.head_state)));
 }
 
 // The paper's "Constant" kernel (Section 4.2) for the flat layout: exactly
 // k_generate_flat's stores with the arithmetic taken out -- whole chunks of
 // R rows of kFlatPerBlock outputs, no count test, each row's store followed
-// by the same scheduling barrier, and a ragged last chunk in a separate
-// one-workgroup kernel (k_fill_flat_tail).
+// by the same scheduling barrier (k_fill_flat), and k_generate_flat_any's for
+// every other output (k_fill_flat_any).
 //
 // START: also the generator's start -- its three table loads (the chunk's
 // two row multipliers and the lane's offset) -- with only a comparison in
 // place of its multiplications, so the stores wait for the same loads:
 // the generator minus its arithmetic.  (The entries are positive, so the
 // comparison always keeps `value`.)
-template <bool NT, int R, bool START, int G>
-__global__ __launch_bounds__(kFlatBlock) void k_fill_flat(uint64_t* __restrict__ out,
-                                                          uint64_t value) {
-    extern __shared__ char occupancy_cap[];
-    (void)occupancy_cap;
-    const uint64_t b = flat_chunk<G>(blockIdx.x);
+template <int R, bool START>
+__device__ __forceinline__ u64x2 fill_pair(uint64_t b, uint64_t value) {
     u64x2 v;
     v.x = value;
     if constexpr (START) {
@@ -473,6 +497,16 @@ __global__ __launch_bounds__(kFlatBlock) void k_fill_flat(uint64_t* __restrict__
         v.x = hi + lo + lane > 0.0 ? value : 0;
     }
     v.y = v.x;
+    return v;
+}
+
+template <bool NT, int R, bool START, int G>
+__global__ __launch_bounds__(kFlatBlock) void k_fill_flat(uint64_t* __restrict__ out,
+                                                          uint64_t value) {
+    extern __shared__ char occupancy_cap[];
+    (void)occupancy_cap;
+    const uint64_t b = flat_chunk<G>(blockIdx.x);
+    const u64x2 v = fill_pair<R, START>(b, value);
     u64x2* p = reinterpret_cast<u64x2*>(out + (uint64_t)kFlatPerBlock * R * b + 2u * threadIdx.x);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -481,52 +515,60 @@ __global__ __launch_bounds__(kFlatBlock) void k_fill_flat(uint64_t* __restrict__
     }
 }
 
-// The last, partial chunk of a fill: `count` < kFlatPerBlock*R outputs.
-template <bool NT, int R>
-__global__ __launch_bounds__(kFlatBlock) void k_fill_flat_tail(uint64_t* __restrict__ out,
-                                                               uint64_t count, uint64_t value) {
-    u64x2 v;
-    v.x = value;
-    v.y = value;
-    uint64_t k = 2u * threadIdx.x;
-    for (int r = 0; r < R && k < count; ++r, k += kFlatPerBlock) {
-        if (k + 1 < count)
-            put<NT>(reinterpret_cast<u64x2*>(out + k), v);
-        else
-            put<NT>(out + k, value);
+template <bool NT, int R, bool START>
+__global__ __launch_bounds__(kFlatBlock) void k_fill_flat_any(FlatArgs a, uint64_t value) {
+    extern __shared__ char occupancy_cap[];
+    (void)occupancy_cap;
+    const uint32_t w = blockIdx.x;
+    const uint32_t b = R == 4 && w < a.runs ? (uint32_t)xcd_run_index(w) : w;
+    const uint32_t l = threadIdx.x;
+    const u64x2 v = fill_pair<R, START>(b, value);
+    const global_ptr<uint64_t> p = as_global(a.out) + ((uint64_t)kFlatPerBlock * R * b + 2u * l);
+    if (b < a.full) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            put<NT>(reinterpret_cast<global_ptr<u64x2>>(p + r * kFlatPerBlock), v);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+        uint32_t k = 2u * l;
+        for (int r = 0; r < R && k < a.tail; ++r, k += kFlatPerBlock) {
+            if (k + 1 < a.tail)
+                put<NT>(reinterpret_cast<global_ptr<u64x2>>(p + r * kFlatPerBlock), v);
+            else
+                put<NT>(p + r * kFlatPerBlock, value);
+        }
     }
+    if (w == 0 && a.head && l == 0) put<NT>(as_global(a.head), value);
+}
+
+// Whole chunks only, all in XCD runs or none: the kernel without tests.
+static bool flat_whole(const FlatArgs& a) {
+    return a.full && !a.tail && !a.head && (a.runs == 0 || a.runs == a.full);
+}
+// Workgroups of the other: one for the partial chunk, or for the lone head.
+static uint32_t flat_grid(const FlatArgs& a) {
+    const uint32_t chunks = a.full + (a.tail ? 1u : 0u);
+    return chunks ? chunks : 1u;
 }
 
 template <class V, int KIND, bool NT, int R>
 static hipError_t flat_one(uint32_t lds, hipStream_t s, const FlatArgs& a) {
-    const uint64_t per = (uint64_t)kFlatPerBlock * R;
-    const uint64_t full = a.count / per;  // whole chunks
-    const uint64_t tail = a.count - full * per;
-    const uint64_t runs = flat_run_chunks(R, a.xcd_runs, full);  // whole chunks in XCD runs
-    if constexpr (R == 4) {
-        if (runs) {
-            hipLaunchKernelGGL((k_generate_flat<V, KIND, NT, R, kFlatXcdRun>),
-                               dim3((uint32_t)runs), dim3(kFlatBlock), lds, s, a.base, a.out,
-                               a.M1, a.J);
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
+    if (flat_whole(a)) {
+        if constexpr (R == 4) {
+            if (a.runs) {
+                hipLaunchKernelGGL((k_generate_flat<V, KIND, NT, R, kFlatXcdRun>), dim3(a.full),
+                                   dim3(kFlatBlock), lds, s, a.base, a.out, a.M1, a.J);
+                return hipGetLastError();
+            }
         }
-    }
-    if (full > runs) {
-        // the whole chunks after the last run, in workgroup order from their own base
-        hipLaunchKernelGGL((k_generate_flat<V, KIND, NT, R, 0>), dim3((uint32_t)(full - runs)),
-                           dim3(kFlatBlock), lds, s, runs ? a.mid_base : a.base,
-                           a.out + runs * per, a.M1, a.J);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (tail) {
-        // the tail chunk starts full*R rows in: its own base, one workgroup
-        hipLaunchKernelGGL((k_generate_flat_tail<V, KIND, NT, R>), dim3(1), dim3(kFlatBlock), 0,
-                           s, a.tail_base, a.out + full * per, a.M1, a.J, tail);
+        hipLaunchKernelGGL((k_generate_flat<V, KIND, NT, R, 0>), dim3(a.full), dim3(kFlatBlock),
+                           lds, s, a.base, a.out, a.M1, a.J);
         return hipGetLastError();
     }
-    return hipSuccess;
+    hipLaunchKernelGGL((k_generate_flat_any<V, KIND, NT, R>), dim3(flat_grid(a)), dim3(kFlatBlock),
+                       lds, s, a);
+    return hipGetLastError();
 }
 
 template <class V, int KIND, bool NT>
@@ -560,65 +602,45 @@ hipError_t launch_generate_flat(int mulmod, int kind, bool nt, int rows, uint32_
     }
 }
 
-template <bool NT, int R, int G>
-static hipError_t fill_flat_launch(uint32_t grid, uint32_t lds, hipStream_t s, bool start,
-                                   uint64_t* out, uint64_t value) {
-    if (start)
-        hipLaunchKernelGGL((k_fill_flat<NT, R, true, G>), dim3(grid), dim3(kFlatBlock), lds, s,
-                           out, value);
-    else
-        hipLaunchKernelGGL((k_fill_flat<NT, R, false, G>), dim3(grid), dim3(kFlatBlock), lds, s,
-                           out, value);
+template <bool NT, int R, bool START>
+static hipError_t fill_flat_one(uint32_t lds, hipStream_t s, const FlatArgs& a, uint64_t value) {
+    if (flat_whole(a)) {
+        if constexpr (R == 4) {
+            if (a.runs) {
+                hipLaunchKernelGGL((k_fill_flat<NT, R, START, kFlatXcdRun>), dim3(a.full),
+                                   dim3(kFlatBlock), lds, s, a.out, value);
+                return hipGetLastError();
+            }
+        }
+        hipLaunchKernelGGL((k_fill_flat<NT, R, START, 0>), dim3(a.full), dim3(kFlatBlock), lds, s,
+                           a.out, value);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL((k_fill_flat_any<NT, R, START>), dim3(flat_grid(a)), dim3(kFlatBlock), lds,
+                       s, a, value);
     return hipGetLastError();
 }
 
-// Whole chunks in the generator's order (XCD runs, then workgroup order),
-// then the tail.
-template <bool NT, int R>
-static hipError_t fill_flat_one(uint32_t lds, hipStream_t s, bool start, bool xcd_runs,
-                                uint64_t* out, uint64_t count, uint64_t value) {
-    const uint64_t per = (uint64_t)kFlatPerBlock * R;
-    const uint64_t full = count / per;
-    const uint64_t tail = count - full * per;
-    const uint64_t runs = flat_run_chunks(R, xcd_runs, full);
-    if constexpr (R == 4) {
-        if (runs) {
-            const hipError_t e =
-                fill_flat_launch<NT, R, kFlatXcdRun>((uint32_t)runs, lds, s, start, out, value);
-            if (e != hipSuccess) return e;
-        }
-    }
-    if (full > runs) {
-        // START: the table indices restart at the first chunk after the runs
-        const hipError_t e = fill_flat_launch<NT, R, 0>((uint32_t)(full - runs), lds, s, start,
-                                                        out + runs * per, value);
-        if (e != hipSuccess) return e;
-    }
-    if (tail) {
-        hipLaunchKernelGGL((k_fill_flat_tail<NT, R>), dim3(1), dim3(kFlatBlock), 0, s,
-                           out + full * per, tail, value);
-        return hipGetLastError();
-    }
-    return hipSuccess;
-}
-
-template <bool NT>
-static hipError_t fill_flat_r(int rows, uint32_t lds, hipStream_t s, bool start, bool xcd_runs,
-                              uint64_t* out, uint64_t count, uint64_t value) {
+template <bool NT, bool START>
+static hipError_t fill_flat_r(int rows, uint32_t lds, hipStream_t s, const FlatArgs& a,
+                              uint64_t value) {
     switch (rows) {
-        case 1: return fill_flat_one<NT, 1>(lds, s, start, xcd_runs, out, count, value);
-        case 2: return fill_flat_one<NT, 2>(lds, s, start, xcd_runs, out, count, value);
-        case 4: return fill_flat_one<NT, 4>(lds, s, start, xcd_runs, out, count, value);
-        case 8: return fill_flat_one<NT, 8>(lds, s, start, xcd_runs, out, count, value);
-        case 16: return fill_flat_one<NT, 16>(lds, s, start, xcd_runs, out, count, value);
+        case 1: return fill_flat_one<NT, 1, START>(lds, s, a, value);
+        case 2: return fill_flat_one<NT, 2, START>(lds, s, a, value);
+        case 4: return fill_flat_one<NT, 4, START>(lds, s, a, value);
+        case 8: return fill_flat_one<NT, 8, START>(lds, s, a, value);
+        case 16: return fill_flat_one<NT, 16, START>(lds, s, a, value);
         default: return hipErrorInvalidValue;
     }
 }
 
 hipError_t launch_fill_flat(bool nt, int rows, uint32_t lds, hipStream_t s, bool start,
-                            bool xcd_runs, uint64_t* out, uint64_t count, uint64_t value) {
-    return nt ? fill_flat_r<true>(rows, lds, s, start, xcd_runs, out, count, value)
-              : fill_flat_r<false>(rows, lds, s, start, xcd_runs, out, count, value);
+                            const FlatArgs& a, uint64_t value) {
+    if (start)
+        return nt ? fill_flat_r<true, true>(rows, lds, s, a, value)
+                  : fill_flat_r<false, true>(rows, lds, s, a, value);
+    return nt ? fill_flat_r<true, false>(rows, lds, s, a, value)
+              : fill_flat_r<false, false>(rows, lds, s, a, value);
 }
 
 // Kernel selector: W = 1, W = 2, or W = 2 with IL = 2 or 4 rows in flight.

@@ -99,8 +99,8 @@ constexpr uint64_t kFlatMaxCount = kFlatMaxRowsPerLaunch * kFlatPerBlock;  // 2^
 // workgroup: 6.2-6.35 TB/s at 31 744 bytes or less, 7.4-7.5 TB/s from
 // 32 256 to 40 960 bytes; non-temporal stores stay at 6.2-6.4 throughout.
 constexpr uint32_t kFlatMaxRows = 16;
-// Outputs from which an output that is only 8-byte aligned takes the flat
-// layout by default (its first element in a launch of its own).
+// Outputs from which an output that is only 8-byte aligned takes every flat
+// cfg field without NN_CFG_FLAT (below, a cfg that sets one means the rows).
 constexpr uint64_t kFlatUnalignedMin = 1ull << 22;
 constexpr uint32_t kFlatDefaultRows = 4;
 constexpr uint32_t kFlatDefaultOccupancy = 4;
@@ -119,8 +119,7 @@ hipError_t upload_flat_symbol(const Mult* entries);
 // per workgroup the whole chunks are taken in runs of 8*kFlatXcdRun
 // workgroups instead, in which XCD x writes the kFlatXcdRun consecutive
 // chunks [x kFlatXcdRun, (x + 1) kFlatXcdRun) of the run (4 MiB).  Whole
-// chunks beyond the last full run keep workgroup order (a launch of their
-// own from mid_base).
+// chunks beyond the last full run keep workgroup order.
 constexpr uint32_t kFlatXcds = 8;
 constexpr uint32_t kFlatXcdRun = 256;
 // Whole chunks of a flat launch that go to the XCD-run kernel (runs: the
@@ -130,25 +129,28 @@ inline uint64_t flat_run_chunks(int rows, bool runs, uint64_t whole_chunks) {
     return rows == 4 && runs ? whole_chunks / run * run : 0;
 }
 
+// One launch writes all of it: the whole chunks, the partial last one and,
+// where the caller's output is only 8-byte aligned, the element before `out`.
 struct FlatArgs {
-    uint64_t* out;   // 16-byte aligned
-    uint64_t count;  // <= kFlatMaxCount
     uint64_t base;   // state of out[0]
-    uint64_t mid_base;   // state of the first output after the XCD runs (flat_run_chunks)
-    uint64_t tail_base;  // state of the first output of the partial last chunk, if any
+    uint64_t* out;   // 16-byte aligned
+    uint32_t full;   // whole chunks of kFlatPerBlock*rows outputs
+    uint32_t runs;   // the first of them, in XCD runs (flat_run_chunks)
+    uint32_t tail;   // outputs of the partial last chunk
+    uint64_t* head;  // one output before out[0], or null
+    uint64_t head_state;
     Mult M1;         // 2^53
     Mult J;          // (2^53)^kFlatPerBlock: the next row of a lane
-    bool xcd_runs;   // 4 rows: whole chunks in XCD runs (else address order)
 };
 
 // rows: rows per workgroup (1, 2, 4, 8, 16); lds_bytes > 0 caps the
 // resident workgroups per compute unit.
 hipError_t launch_generate_flat(int mulmod, int kind, bool nontemporal, int rows,
                                 uint32_t lds_bytes, hipStream_t stream, const FlatArgs& a);
-// start: the fill that keeps the generator's table loads (NN_FILL_WITH_START).
+// start: the fill that keeps the generator's table loads (NN_FILL_WITH_START);
+// it reads neither the states nor the multipliers of `a`.
 hipError_t launch_fill_flat(bool nontemporal, int rows, uint32_t lds_bytes, hipStream_t stream,
-                            bool start, bool xcd_runs, uint64_t* out, uint64_t count,
-                            uint64_t value);
+                            bool start, const FlatArgs& a, uint64_t value);
 
 // Consecutive layout: the output is cut into tiles of block*E elements;
 // workgroup w makes tiles w, w + grid, ...  In a tile, thread t makes

@@ -155,6 +155,38 @@ def test_output_alignment():
     assert (_bits(buf) == SENTINEL).all()
 
 
+@pytest.mark.parametrize("rows", [1, 2, 4, 8, 16])
+@pytest.mark.parametrize("head", [0, 1])
+def test_flat_remainders_in_one_launch(rows, head):
+    """Partial chunks at their edges (one output, a row, one short of a
+    chunk), alone, after a few chunks and, with four rows, after a whole XCD
+    run, with and without the head element of an output that is only 8-byte
+    aligned; the fill, with and without the generator's start, likewise."""
+    z0 = orc.seed(wl.INDEX_MIN + 7)
+    per = 512 * rows
+    wholes = [0, 3] + ([2048, 2049] if rows == 4 else [])
+    top = wholes[-1] * per + max(per, 514) + 1  # the largest count below
+    ref, _ = orc.gen(z0, top, "u64", threads=0)
+    for whole in wholes:
+        for rest in (0, 1, 2, 511, 512, 513, per - 1):
+            count = whole * per + rest + head
+            if not count:
+                continue
+            got, zn = _gen_guarded(z0, count, "u64", guard=512 + head,
+                                   cfg=nn.make_cfg(layout="flat", unroll=rows))
+            assert np.array_equal(got, ref[:count]), (rows, whole, rest, head)
+            assert zn == orc.skip(z0, count)
+            for start in (False, True):
+                buf = _sentinel_buffer(count + 2 * (512 + head))
+                at = 512 + head
+                nn.fill(buf[at:at + count], 0x3FF0000000000001, with_start=start,
+                        cfg=nn.make_cfg(layout="flat", unroll=rows))
+                torch.cuda.synchronize()
+                h = _bits(buf)
+                assert (h[:at] == SENTINEL).all() and (h[at + count:] == SENTINEL).all()
+                assert (h[at:at + count] == 0x3FF0000000000001).all(), (rows, whole, rest, head)
+
+
 @pytest.mark.parametrize("variant", VARIANTS)
 def test_flat_layout_bit_exact(variant):
     """The flat layout (workgroups of 1-16 rows of 512 outputs) for every
