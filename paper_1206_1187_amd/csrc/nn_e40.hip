@@ -290,7 +290,34 @@ struct E40FlatArgs {
     Mult40L M1L, JL, JNL;
     const Mult40* tabs;  // t_lo, t_hi, t_flo, t_fhi, then the same as limbs
     double base_lo, base_hi;  // base as base-B limbs (limbs())
+    // k_e40_flat_any only:
+    uint32_t runs;       // the first chunks, in XCD runs (e40_run_chunks)
+    uint32_t tail;       // outputs of the partial chunk after the whole ones
+    uint64_t* head;      // one output before out[0], or null
+    uint64_t head_state;
 };
+
+// The states of lane l's pair of the row u = 512-output rows after a.out.
+template <int MM>
+__device__ __forceinline__ void e40_start(const E40FlatArgs& a, uint64_t u, uint32_t l,
+                                          typename Step<MM>::S& za, typename Step<MM>::S& zb) {
+    if constexpr (MM == 1) {
+        // in limbs throughout: the chunk's two row multipliers, then the
+        // lane's two offsets (all four loads independent, from e40_sym), no
+        // Montgomery
+        const Mult40L hi = e40_sym[kSymHi + u / kFLo], lo = e40_sym[kSymLo + u % kFLo];
+        const Mult40L la = e40_sym[2u * l], lb = e40_sym[2u * l + 1];
+        const L2 S0 = mul40l(mul40l(L2{a.base_lo, a.base_hi}, hi), lo);
+        za = mul40l(S0, la);
+        zb = mul40l(S0, lb);
+    } else {
+        const uint64_t z0 = mm40(mm40(mm40(a.base, a.tabs[kFHiOff + u / kFLo].mont),
+                                      a.tabs[kFLoOff + u % kFLo].mont),
+                                 a.tabs[2u * l].mont);
+        za = Step<0>::from(z0);
+        zb = Step<0>::from(mm40(z0, a.M1.mont));
+    }
+}
 
 // Workgroup w writes chunk w, then w + grid, ... (grid <= n_chunks, as the
 // host launches it), or with G > 0 (one workgroup per chunk over whole XCD
@@ -309,24 +336,8 @@ __global__ __launch_bounds__(256) void k_e40_flat(E40FlatArgs a) {
         c = c - r + (r % kFlatXcds) * G + r / kFlatXcds;
     }
     const uint32_t l = threadIdx.x;
-    const uint64_t u = c * R;
     S za, zb;
-    if constexpr (MM == 1) {
-        // in limbs throughout: the chunk's two row multipliers, then the
-        // lane's two offsets (all four loads independent, from e40_sym), no
-        // Montgomery
-        const Mult40L hi = e40_sym[kSymHi + u / kFLo], lo = e40_sym[kSymLo + u % kFLo];
-        const Mult40L la = e40_sym[2u * l], lb = e40_sym[2u * l + 1];
-        const L2 S0 = mul40l(mul40l(L2{a.base_lo, a.base_hi}, hi), lo);
-        za = mul40l(S0, la);
-        zb = mul40l(S0, lb);
-    } else {
-        const uint64_t z0 = mm40(mm40(mm40(a.base, a.tabs[kFHiOff + u / kFLo].mont),
-                                      a.tabs[kFLoOff + u % kFLo].mont),
-                                 a.tabs[2u * l].mont);
-        za = St::from(z0);
-        zb = St::from(mm40(z0, a.M1.mont));
-    }
+    e40_start<MM>(a, c * R, l, za, zb);
     const global_ptr<uint64_t> out = as_global(a.out);
     for (;;) {
         const global_ptr<u64x2> p =
@@ -350,32 +361,6 @@ __global__ __launch_bounds__(256) void k_e40_flat(E40FlatArgs a) {
     }
 }
 
-// The last, partial chunk (count < 512 R outputs, one workgroup), from its
-// own base.
-template <int KIND, int MM, int R, bool NT>
-__global__ __launch_bounds__(256) void k_e40_flat_tail(E40FlatArgs a, uint64_t count) {
-    typedef Step<MM> St;
-    typedef typename St::S S;
-    const uint32_t l = threadIdx.x;
-    const uint64_t z0 = mm40(a.base, a.tabs[2u * l].mont);
-    S za = St::from(z0);
-    S zb = St::from(mm40(z0, a.M1.mont));
-    const global_ptr<uint64_t> out = as_global(a.out);
-    uint64_t k = 2u * l;
-    for (int r = 0; r < R && k < count; ++r, k += 512) {
-        if (k + 1 < count) {
-            u64x2 v;
-            v.x = St::template bits<KIND>(za);
-            v.y = St::template bits<KIND>(zb);
-            put<NT>(reinterpret_cast<global_ptr<u64x2>>(out + k), v);
-        } else {
-            put<NT>(out + k, St::template bits<KIND>(za));
-        }
-        za = St::mul(za, a.J, a.JL);
-        zb = St::mul(zb, a.J, a.JL);
-    }
-}
-
 // XCD runs of 4 MiB: chunks of 512 R outputs per XCD run.
 template <int R>
 constexpr int kE40Run = 1024 / R;
@@ -387,59 +372,95 @@ inline uint64_t e40_run_chunks(int rows, uint64_t n_chunks) {
     return n_chunks / run * run;
 }
 
-// a: the whole chunks (grid workgroups; grid == a.n_chunks: one per chunk,
-// then mid takes the chunks after the XCD runs, mid.n_chunks of them, from
-// its own base); tail: the partial last chunk.
+// Any output with one workgroup per chunk, in one launch: the whole chunks
+// (the first `runs` in XCD runs), the partial chunk after them, which the last
+// workgroup writes pair by pair, and the element before `out` of an output
+// that is only 8-byte aligned, which workgroup 0 adds.  (A launch of its own
+// for each of these parts cost 3-4 us: 200,003 raw states 13.5 -> 10.7 us a
+// call.)
 template <int KIND, int MM, int R, bool NT>
-hipError_t flat_launch(uint32_t grid, uint32_t lds, hipStream_t s, const E40FlatArgs& a,
-                       const E40FlatArgs& mid, const E40FlatArgs& tail, uint64_t tail_count) {
-    if (a.n_chunks) {
-        if (grid == a.n_chunks && MM == 1) {
-            const uint64_t runs = e40_run_chunks(R, a.n_chunks);
-            if (runs) {
-                E40FlatArgs r = a;
-                r.n_chunks = runs;
-                k_e40_flat<KIND, MM, R, NT, kE40Run<R>><<<(uint32_t)runs, 256, lds, s>>>(r);
-                const hipError_t e = hipGetLastError();
-                if (e != hipSuccess) return e;
+__global__ __launch_bounds__(256) void k_e40_flat_any(E40FlatArgs a) {
+    extern __shared__ char occupancy_cap[];
+    (void)occupancy_cap;
+    typedef Step<MM> St;
+    constexpr uint32_t G = kE40Run<R>, run = kFlatXcds * G;
+    const uint32_t w = blockIdx.x;
+    const uint32_t r = w % run;
+    const uint32_t c = w < a.runs ? w - r + (r % kFlatXcds) * G + r / kFlatXcds : w;
+    const uint32_t l = threadIdx.x;
+    typename St::S za, zb;
+    e40_start<MM>(a, (uint64_t)c * R, l, za, zb);
+    const global_ptr<uint64_t> p = as_global(a.out) + ((uint64_t)512 * R * c + 2u * l);
+    if (c < a.n_chunks) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            u64x2 v;
+            v.x = St::template bits<KIND>(za);
+            v.y = St::template bits<KIND>(zb);
+            put<NT>(reinterpret_cast<global_ptr<u64x2>>(p + r * 512), v);
+            if (r + 1 < R) {
+                za = St::mul(za, a.J, a.JL);
+                zb = St::mul(zb, a.J, a.JL);
             }
-            if (mid.n_chunks) {
-                k_e40_flat<KIND, MM, R, NT, 0><<<(uint32_t)mid.n_chunks, 256, lds, s>>>(mid);
-                const hipError_t e = hipGetLastError();
-                if (e != hipSuccess) return e;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+        uint32_t k = 2u * l;
+        for (int r = 0; r < R && k < a.tail; ++r, k += 512) {
+            if (k + 1 < a.tail) {
+                u64x2 v;
+                v.x = St::template bits<KIND>(za);
+                v.y = St::template bits<KIND>(zb);
+                put<NT>(reinterpret_cast<global_ptr<u64x2>>(p + r * 512), v);
+            } else {
+                put<NT>(p + r * 512, St::template bits<KIND>(za));
             }
-        } else {
-            k_e40_flat<KIND, MM, R, NT, 0><<<grid, 256, lds, s>>>(a);
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
+            za = St::mul(za, a.J, a.JL);
+            zb = St::mul(zb, a.J, a.JL);
         }
     }
-    if (tail_count) {
-        k_e40_flat_tail<KIND, MM, R, NT><<<1, 256, 0, s>>>(tail, tail_count);
-        return hipGetLastError();
+    if (w == 0 && a.head && l == 0)
+        put<NT>(as_global(a.head), St::template bits<KIND>(St::from(a.head_state)));
+}
+
+// `grid` workgroups over the whole chunks of `a`; one per chunk takes the
+// partial chunk and the head along, fewer leave them to `rest` (n_chunks 0).
+template <int KIND, int MM, int R, bool NT>
+hipError_t flat_launch(uint32_t grid, uint32_t lds, hipStream_t s, const E40FlatArgs& a,
+                       const E40FlatArgs& rest) {
+    const bool more = a.tail || a.head;
+    if (grid < a.n_chunks) {
+        k_e40_flat<KIND, MM, R, NT, 0><<<grid, 256, lds, s>>>(a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess || !more) return e;
+        k_e40_flat_any<KIND, MM, R, NT><<<1, 256, 0, s>>>(rest);
+    } else if (!more && a.runs == a.n_chunks) {
+        k_e40_flat<KIND, MM, R, NT, kE40Run<R>><<<(uint32_t)a.n_chunks, 256, lds, s>>>(a);
+    } else {
+        const uint32_t chunks = (uint32_t)a.n_chunks + (a.tail ? 1u : 0u);
+        k_e40_flat_any<KIND, MM, R, NT><<<chunks ? chunks : 1u, 256, lds, s>>>(a);
     }
-    return hipSuccess;
+    return hipGetLastError();
 }
 
 template <int KIND, int MM, bool NT>
 hipError_t flat_r(int rows, uint32_t grid, uint32_t lds, hipStream_t s, const E40FlatArgs& a,
-                  const E40FlatArgs& mid, const E40FlatArgs& tail, uint64_t tail_count) {
+                  const E40FlatArgs& rest) {
     switch (rows) {
-        case 2: return flat_launch<KIND, MM, 2, NT>(grid, lds, s, a, mid, tail, tail_count);
-        case 4: return flat_launch<KIND, MM, 4, NT>(grid, lds, s, a, mid, tail, tail_count);
-        case 8: return flat_launch<KIND, MM, 8, NT>(grid, lds, s, a, mid, tail, tail_count);
-        case 16: return flat_launch<KIND, MM, 16, NT>(grid, lds, s, a, mid, tail, tail_count);
-        case 32: return flat_launch<KIND, MM, 32, NT>(grid, lds, s, a, mid, tail, tail_count);
+        case 2: return flat_launch<KIND, MM, 2, NT>(grid, lds, s, a, rest);
+        case 4: return flat_launch<KIND, MM, 4, NT>(grid, lds, s, a, rest);
+        case 8: return flat_launch<KIND, MM, 8, NT>(grid, lds, s, a, rest);
+        case 16: return flat_launch<KIND, MM, 16, NT>(grid, lds, s, a, rest);
+        case 32: return flat_launch<KIND, MM, 32, NT>(grid, lds, s, a, rest);
         default: return hipErrorInvalidValue;
     }
 }
 
 hipError_t launch_flat(int kind, int mm, int rows, bool nt, uint32_t grid, uint32_t lds,
-                       hipStream_t s, const E40FlatArgs& a, const E40FlatArgs& mid,
-                       const E40FlatArgs& tail, uint64_t tail_count) {
-#define NN_E40_FLAT(K, M)                                                          \
-    return nt ? flat_r<K, M, true>(rows, grid, lds, s, a, mid, tail, tail_count)    \
-              : flat_r<K, M, false>(rows, grid, lds, s, a, mid, tail, tail_count);
+                       hipStream_t s, const E40FlatArgs& a, const E40FlatArgs& rest) {
+#define NN_E40_FLAT(K, M)                                   \
+    return nt ? flat_r<K, M, true>(rows, grid, lds, s, a, rest) \
+              : flat_r<K, M, false>(rows, grid, lds, s, a, rest);
     if (kind == 0) {
         if (mm) { NN_E40_FLAT(0, 1) } else { NN_E40_FLAT(0, 0) }
     }
@@ -500,21 +521,26 @@ hipError_t launch(int kind, int mm, int ilp, int unroll, bool nt, uint32_t grid,
 // layout; u64 6.28-6.36 against 6.10-6.21 with 8 rows and 6.05 for the row
 // layout).  The step is VALU-bound, so the longer chunk pays: a lane's
 // start (four limb products) is spread over 32 outputs.
+// An output too short to give every CU two such chunks takes shorter ones (8,
+// 4, then 2 rows): its time is a workgroup's own chain of rows.  Kernel times
+// with 16 rows and by this rule, f64 (u64): 200,003 outputs 4.16 and 2.74 us
+// (4.34, 2.80), 2^20 5.12 and 4.46 (5.26, 4.38), 3,000,017 7.76 and 7.64
+// (7.88, 7.88); from 2^22 on 16 rows are the faster or tie.
 constexpr uint32_t kE40FlatDefaultRows = 16;
 
 // nn_e40_generate_ex's flat layout (arguments already validated: a valid
 // state, count > 0, an in-range pointer).  cfg: unroll = rows of 512
-// outputs per chunk (2, 4, 8, 16, 32; default 16), grid = workgroups per launch
+// outputs per chunk (2, 4, 8, 16, 32; default by size), grid = workgroups per launch
 // (0: one per chunk), occupancy = residency cap (0: 4), store policy
 // (default temporal).
 int generate_flat(uint64_t* state, uint64_t count, void* out_dev, int kind, void* stream,
                   const nn_launch_cfg& c, int mm) {
     if ((c.block && c.block != 256) || c.ilp > 1)
         return fail(NN_EINVAL, "the flat layout has 256 threads per workgroup and no ilp");
-    const uint32_t rows = c.unroll ? c.unroll : kE40FlatDefaultRows;
-    if (rows != 2 && rows != 4 && rows != 8 && rows != 16 && rows != 32)
+    if (c.unroll && c.unroll != 2 && c.unroll != 4 && c.unroll != 8 && c.unroll != 16 &&
+        c.unroll != 32)
         return fail(NN_EINVAL, "unroll %u: the flat layout writes 2, 4, 8, 16 or 32 rows per chunk",
-                    rows);
+                    c.unroll);
     const Mult40* tab = nullptr;
     int st = device_tables(&tab);
     if (st) return st;
@@ -528,59 +554,50 @@ int generate_flat(uint64_t* state, uint64_t count, void* out_dev, int kind, void
         return fail(NN_EINVAL, "occupancy %u not expressible on this device", occ);
     const bool nt = (c.flags & NN_CFG_NONTEMPORAL_STORES) != 0;
     const uint64_t s = *state;
+    uint32_t rows = c.unroll ? c.unroll : kE40FlatDefaultRows;
+    if (!c.unroll && !c.grid)
+        while (rows > 2 && count / (512ull * rows) < 2ull * (d->cus > 0 ? d->cus : 1)) rows /= 2;
     const uint64_t per = 512ull * rows;
     const uint64_t max_launch = kFlatMaxRows * 512;
-    E40FlatArgs a;
+    E40FlatArgs a = {};
     a.M1 = make_mult40(kMult);
     a.J = make_mult40(Powers::get().pow(512));
     a.M1L = make_mult40l(a.M1.v);
     a.JL = make_mult40l(a.J.v);
     a.tabs = tab;
-    // an output that is only 8-byte aligned: its first element alone (the
-    // tail kernel with one output), then the 16-byte aligned rest
+    // an output that is only 8-byte aligned: its first element beside the
+    // 16-byte aligned rest
     const uint64_t head = ((uintptr_t)out_dev % 16) ? 1 : 0;
-    if (head) {
-        E40FlatArgs h = a;
-        h.n_chunks = 0;
-        h.out = (uint64_t*)out_dev;
-        h.base = h_mul(s, Powers::get().pow(1));
-        const hipError_t e =
-            launch_flat(kind, mm, (int)rows, nt, 1, lds, (hipStream_t)stream, h, h, h, 1);
-        if (e != hipSuccess) return fail(NN_EHIP, "e40 launch: %s", hipGetErrorString(e));
-    }
-    for (uint64_t off = head; off < count; off += max_launch) {
+    a.head = head ? (uint64_t*)out_dev : nullptr;
+    a.head_state = h_mul(s, kMult);
+    uint64_t off = head;
+    do {
         const uint64_t n = count - off < max_launch ? count - off : max_launch;
         a.out = (uint64_t*)out_dev + off;
         a.base = h_mul(s, Powers::get().pow(off + 1));  // the state of this slice's first output
         a.base_lo = limbs(a.base).lo;
         a.base_hi = limbs(a.base).hi;
         a.n_chunks = n / per;
-        uint32_t grid = 1;
-        if (a.n_chunks) {
-            grid = c.grid && c.grid < a.n_chunks ? c.grid : (uint32_t)a.n_chunks;
+        a.tail = (uint32_t)(n % per);
+        a.runs = mm == 1 ? (uint32_t)e40_run_chunks((int)rows, a.n_chunks) : 0u;
+        uint32_t grid = (uint32_t)a.n_chunks;
+        E40FlatArgs rest = a;
+        if (c.grid && c.grid < a.n_chunks) {
+            grid = c.grid;
             a.JN = make_mult40(Powers::get().pow(per * grid - 512ull * (rows - 1)));
             a.JNL = make_mult40l(a.JN.v);
+            rest.n_chunks = rest.runs = 0;
+            rest.out = a.out + a.n_chunks * per;
+            rest.base = h_mul(a.base, Powers::get().pow(a.n_chunks * per));
+            rest.base_lo = limbs(rest.base).lo;
+            rest.base_hi = limbs(rest.base).hi;
         }
-        // one workgroup per chunk with the FP64 step: XCD runs, then the
-        // chunks after the last run from their own base
-        E40FlatArgs m = a;
-        m.n_chunks = 0;
-        if (a.n_chunks && grid == a.n_chunks && mm == 1) {
-            const uint64_t runs = e40_run_chunks((int)rows, a.n_chunks);
-            m.n_chunks = a.n_chunks - runs;
-            m.out = a.out + runs * per;
-            m.base = h_mul(a.base, Powers::get().pow(runs * per));
-            m.base_lo = limbs(m.base).lo;
-            m.base_hi = limbs(m.base).hi;
-        }
-        E40FlatArgs t = a;
-        const uint64_t tail = n - a.n_chunks * per;
-        t.out = a.out + a.n_chunks * per;
-        t.base = h_mul(a.base, Powers::get().pow(a.n_chunks * per));
-        const hipError_t e = launch_flat(kind, mm, (int)rows, nt, grid, lds, (hipStream_t)stream,
-                                         a, m, t, tail);
+        const hipError_t e =
+            launch_flat(kind, mm, (int)rows, nt, grid, lds, (hipStream_t)stream, a, rest);
         if (e != hipSuccess) return fail(NN_EHIP, "e40 launch: %s", hipGetErrorString(e));
-    }
+        a.head = nullptr;
+        off += n;
+    } while (off < count);
     *state = h_mul(s, Powers::get().pow(count));
     return ok();
 }
@@ -636,13 +653,17 @@ int nn_e40_generate_ex(uint64_t* state, uint64_t count, void* out_dev, int kind,
         return fail(NN_EINVAL, "NN_CFG_TEMPORAL_STORES and NN_CFG_NONTEMPORAL_STORES are exclusive");
     const int mm = c.mulmod == NN_MULMOD_MONTGOMERY ? 0 : 1;
     // No layout flag: the flat layout with the FP64 step unless the cfg sets
-    // a row-layout field (block, ilp); an output that is only 8-byte aligned
-    // gets its first element alone, by default from kFlatUnalignedMin
-    // outputs on (below, the row layout's one launch is the cheaper).
+    // a row-layout field (block, ilp).  Its one launch also takes the first
+    // element of an output that is only 8-byte aligned; below
+    // kFlatUnalignedMin outputs a cfg that sets grid, unroll or occupancy
+    // keeps the row layout there, with the values that layout takes (the row
+    // kernel is the slower at every size: 1000 f64 outputs 2.4 against 1.9 us,
+    // 200,003 3.3 against 2.7, 2^22 9.9 against 9.1).
     const bool aligned16 = ((uintptr_t)out_dev % 16) == 0;
     const bool flat = (c.flags & NN_CFG_FLAT) ||
                       (!(c.flags & NN_CFG_ROWS) && mm == 1 && !c.block && !c.ilp &&
-                       (aligned16 || count >= kFlatUnalignedMin));
+                       (aligned16 || count >= kFlatUnalignedMin ||
+                        (!c.grid && !c.unroll && !c.occupancy)));
     if (flat) return e40::generate_flat(state, count, out_dev, kind, stream, c, mm);
     if (c.occupancy) return fail(NN_EINVAL, "occupancy applies to the flat layout only");
     const uint32_t block = c.block ? c.block : 256u;

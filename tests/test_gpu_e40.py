@@ -128,6 +128,31 @@ def test_e40_flat_xcd_runs_bit_exact():
         assert zn == orc.e40_skip(z0, top - 1)
 
 
+@pytest.mark.parametrize("head", [0, 1])
+@pytest.mark.parametrize("kw", [dict(), dict(layout="flat", unroll=2), dict(layout="flat", unroll=32),
+                                dict(layout="flat", unroll=2, grid=3),
+                                dict(layout="flat", unroll=4, mulmod="montgomery")])
+def test_e40_flat_remainders_in_one_launch(kw, head):
+    """Partial chunks at their edges and the head element of an output that
+    is only 8-byte aligned, alone, after a few chunks, after a whole XCD run
+    (4096 chunks of two rows) and, for the default, on both sides of the sizes
+    where it takes more rows per chunk."""
+    z0 = orc.e40_seed(orc.E40_INDEX_MIN + 77)
+    per = 512 * kw.get("unroll", 2)
+    ends = [0, 5 * per] + ([4096 * 1024 + 1024] if kw == dict(layout="flat", unroll=2) else [])
+    if not kw:
+        ends += [512 * 512 * r for r in (4, 8, 16)]
+    ref, _ = orc.e40_gen(z0, max(ends) + 515, "u64")
+    for end in ends:
+        for rest in (0, 1, 2, 511, 513):
+            count = end + rest + head
+            if not count:
+                continue
+            got, zn = _gen_guarded(z0, count, "u64", cfg=nn.make_cfg(**kw), guard=512 + head)
+            assert np.array_equal(got, ref[:count]), (kw, end, rest, head)
+            assert zn == orc.e40_skip(z0, count)
+
+
 def test_e40_flat_beyond_one_launch_sampled():
     """More than 2^30 outputs (several flat launches): windows on both
     sides of every launch boundary and at the tail."""
