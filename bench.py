@@ -82,7 +82,7 @@ def traffic_from_profile():
 
 def batched_leg(nn, torch, per_stream=True):
     """Config 4: 10,000 streams (lengths log-uniform in [1, 2^22]) as one
-    batched launch replayed from the plan's hipGraph, in the shape
+    batch of the plan, in the shape
     tune.bench_batch_kw gives (the one the full-size parity test compares),
     against the same streams with one nn_generate launch each on the same
     stream; the other batch kernels for comparison."""

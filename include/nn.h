@@ -271,7 +271,9 @@ typedef struct nn_stream_desc {
  * grid; 0 = grid); mulmod: an
  * nn_mulmod; flags: NN_CFG_TEMPORAL_STORES, NN_BATCH_NO_GRAPH (enqueue a
  * copy and a kernel launch instead of replaying the plan's graph),
- * NN_BATCH_INTERLEAVED; occupancy: NN_BATCH_CHUNKS only, 0 (4) or a cap in
+ * NN_BATCH_INTERLEAVED, NN_BATCH_CHUNKS.  A cfg that names no kernel (neither
+ * of those two, block, grid and cluster 0, mulmod 0 or NN_MULMOD_FP64) gets
+ * the chunked one, with non-temporal stores at an occupancy of 3; occupancy: NN_BATCH_CHUNKS only, 0 (4) or a cap in
  * [2,16] on the chunk kernel's resident workgroups per compute unit (as
  * nn_launch_cfg's occupancy caps the plain flat layout's). */
 typedef struct nn_batch_cfg {
@@ -304,8 +306,7 @@ typedef struct nn_batch_cfg {
  * record and one workgroup, which writes every window's part of it; windows
  * that overlap each other get a record per chunk and window instead.
  * grid 0 (the default): one workgroup per record, the records taken in
- * the plain flat layout's XCD runs (the plan's graph gets the batch's
- * record count as its grid before each replay); a nonzero grid: that many
+ * the plain flat layout's XCD runs; a nonzero grid: that many
  * persistent workgroups taking the records round-robin in the same order.  Needs
  * the FP64 reduction, block 0 or 256, cluster 0 or 1 and output indices
  * below 2^51 (NN_ERANGE otherwise).  Exclusive with NN_BATCH_INTERLEAVED.
@@ -313,21 +314,19 @@ typedef struct nn_batch_cfg {
  * reduction's flat inline kernel). */
 #define NN_BATCH_CHUNKS 32u
 
-/* Opaque batch plan: device workspace, pinned staging and a hipGraph of
- * (staging -> workspace copy, persistent kernel) whose arguments never
- * change, owned by the library until nn_batch_plan_destroy.  A chunked
- * plan (NN_BATCH_CHUNKS) also owns a stream (non-blocking, default
- * priority) that carries each batch's descriptor upload and record
- * pre-pass, so they run during the previous batch's kernel; its graph holds
- * the chunk kernel alone. */
+/* Opaque batch plan, owned by the library until nn_batch_plan_destroy: pinned
+ * staging for the descriptors and, for the blocked and interleaved kernels, a
+ * device copy of it and a hipGraph of the kernels.  A chunked plan has
+ * device memory for its records; its pre-pass reads the staging, and its two
+ * kernels are launched directly. */
 typedef struct nn_batch_plan nn_batch_plan;
 
 /* nn_batch_plan_create -- a plan on the current device for batches of at
  * most `max_streams` streams and `max_outputs` outputs in total, writing
  * `kind` outputs.  Allocates two slots (batches alternate between them),
  * each a workspace of 40 bytes per descriptor (one per stream, plus one per
- * 2^24 outputs for the split of long streams) in device and pinned host
- * memory; the interleaved and chunked kernels add 16 bytes of device
+ * 2^24 outputs for the split of long streams) in pinned host memory and, but
+ * for the chunked kernel, in device memory; the interleaved and chunked kernels add 16 bytes of device
  * memory per record (one per row of 2*block outputs or chunk of 2048, plus
  * two per descriptor, and for chunks one more per descriptor).
  * Errors: NN_EINVAL (kind, cfg), NN_ERANGE (capacity), NN_ENOMEM, NN_EHIP. */
@@ -339,23 +338,21 @@ int nn_batch_plan_destroy(nn_batch_plan *plan);
 int nn_batch_plan_cfg(const nn_batch_plan *plan, nn_batch_cfg *cfg_out);
 
 /* nn_generate_batch -- the batched form of Algorithm BB step 3: every
- * stream of `descs` (host array of n) is generated by one persistent kernel
- * launch on `stream` (a hipStream_t), replayed from the plan's hipGraph.
- * It takes a plan rather than (descs, n, out, kind, stream) alone because a
- * hipGraph is replayed with fixed kernel arguments: the plan owns the
- * instantiated graphs and the device workspace their arguments point to
- * (descriptors, records), and fixes the output kind and kernel shape, so a
- * call uploads descriptors and replays without allocating or capturing.
+ * stream of `descs` (host array of n) is generated on `stream` (a
+ * hipStream_t) by the plan's kernel.  It takes a plan rather than (descs, n,
+ * out, kind, stream) alone because the plan owns the memory that the kernels
+ * read (descriptors, records) and, for the kernels that are replayed, the
+ * graphs, and fixes the output kind and kernel shape, so a call neither
+ * allocates nor captures.
  * nn_generate_batch_static below is the plan-free form of the same call.
  * out_dev: device memory of the plan's device, 16-byte aligned, holding
  * every window.  Streams longer than 2^24 outputs are split internally.
  * Outputs are identical to nn_generate on each stream alone.  final_states
  * (host array of n, or NULL) receives each stream's state after its window.
- * Asynchronous; the call blocks only while the plan's previous batch is
- * still copying its descriptors.  In a chunked plan the upload and the
- * pre-pass go to the plan's own stream and `stream` waits for them through
- * an event before the chunk kernel, so the call is not meant for a stream
- * under capture (the plan replays graphs of its own).  A plan serves one
+ * Asynchronous; the call blocks only while the batch before the plan's
+ * previous one is unfinished (its slot holds the descriptors).  The call is
+ * not meant for a stream under capture (the slots are reused, and the plan
+ * may replay graphs of its own).  A plan serves one
  * call at a time (calls on one plan are serialised).  Errors: NN_EINVAL (states, pointers, wrong
  * device), NN_ERANGE (more streams or outputs than the plan holds; nothing
  * is enqueued), NN_EHIP. */
@@ -394,7 +391,7 @@ int nn_generate_batch_static(const nn_stream_desc *descs, uint32_t n, void *out_
  * the same whether it runs alone or with any other traffic.  Requests are
  * admitted from the head of the arrival queue while the output pool has
  * room and slots are free, and launched as batches on `lanes` concurrent
- * HIP streams, each replaying a batch plan's graph. */
+ * HIP streams, each with a batch plan of its own. */
 typedef struct nn_server nn_server;
 
 typedef struct nn_server_cfg {

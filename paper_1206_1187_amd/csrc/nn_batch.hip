@@ -204,9 +204,11 @@ __global__ __launch_bounds__(1024) void k_batch_inline(BatchArgs a, BatchInline 
 // outputs [W (floor(o / W) + j), W (floor(o / W) + j + 1)), W = 2*kIlPairs*block,
 // which are its elements W j - s + k, k < W, with s = o mod W.  (Adjacent
 // rows go to different workgroups, and rows that shared a cache line would
-// leave partial lines in two L2s.)  Workgroups take windows d = blockIdx.x,
-// + gridDim.x, ...; thread t of 256 takes the window's rows t, t + 256, ...:
-// one skip-ahead to its first row, then a step of (2^53)^(W*256) per row.
+// leave partial lines in two L2s.)  Thread t of a window's TPW takes its rows
+// t, t + TPW, ...: one skip-ahead to its first row, then a step of
+// (2^53)^(W*TPW) per row.  A wavefront per window for the chunked kernel (9999
+// windows of 1 to 64 outputs: 43 -> 21 us, most lanes having no row), a
+// workgroup for the interleaved kernel's shorter rows and for long windows.
 //
 // The chunked kernel's owned mode (kChunkOwned) numbers records by chunk:
 // record k of the window's chunk j is k + j, k from the descriptor, and a
@@ -215,13 +217,13 @@ __global__ __launch_bounds__(1024) void k_batch_inline(BatchArgs a, BatchInline 
 // chunk of the window; every window's first-chunk record also goes to ext,
 // where the workgroup of a chunk that windows share finds them.  An empty
 // window gets an empty ext record.
-template <bool INDEXED>
+// TPW threads take a window, 256 / TPW windows a workgroup at a time.
+template <bool INDEXED, int TPW>
 __global__ __launch_bounds__(256) void k_batch_rec(BatchArgs a) {
-    const const_ptr<BatchHeader> hdr = as_const(a.ws);
-    const uint32_t n_desc = hdr->n_desc;
-    const uint64_t n_rows = hdr->n_rows;
-    const bool owned = hdr->mode == kChunkOwned;
-    const const_ptr<BatchDesc> desc = reinterpret_cast<const_ptr<BatchDesc>>(hdr + 1);
+    const uint32_t n_desc = a.n_desc;
+    const uint64_t n_rows = a.n_rec;
+    const bool owned = a.mode == kChunkOwned;
+    const const_ptr<BatchDesc> desc = as_const(a.desc);
     // row r -> cluster c = r / Rc, member (r - c Rc) mod K, its row (r - c Rc) / K
     const uint64_t K = a.cluster, C = a.grid / a.cluster;
     const uint64_t Rc = (n_rows + C - 1) / C;
@@ -229,10 +231,13 @@ __global__ __launch_bounds__(256) void k_batch_rec(BatchArgs a) {
     const uint64_t W = a.row_outs;  // outputs per row, a power of two
     const global_ptr<u64x2> rec = reinterpret_cast<global_ptr<u64x2>>(as_global(a.rec));
     const global_ptr<u64x2> ext = reinterpret_cast<global_ptr<u64x2>>(as_global(a.ext));
-    for (uint32_t d = blockIdx.x; d < n_desc; d += gridDim.x) {
+    constexpr uint32_t kPer = 256 / TPW;
+    const uint32_t mine = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / TPW);
+    const uint32_t t = threadIdx.x % TPW;
+    for (uint32_t d = blockIdx.x * kPer + mine; d < n_desc; d += gridDim.x * kPer) {
         const BatchDesc D = load_desc(desc + d);
         if (owned && D.len == 0) {
-            if (threadIdx.x == 0) {
+            if (t == 0) {
                 u64x2 E;
                 E.x = 0;
                 E.y = kRecEmpty;
@@ -242,14 +247,14 @@ __global__ __launch_bounds__(256) void k_batch_rec(BatchArgs a) {
         }
         const uint64_t s = D.out_off & (W - 1);
         const uint64_t nr = (D.len + s + W - 1) / W;
-        uint64_t j = threadIdx.x;
+        uint64_t j = t;
         if (j >= nr) continue;
         const uint64_t r0 = owned ? D.row_start & ~(kDescFirstShared | kDescLastShared) : D.row_start;
         const bool first_shared = owned && (D.row_start & kDescFirstShared);
         const bool last_shared = owned && (D.row_start & kDescLastShared);
         uint64_t src;
         if constexpr (INDEXED)
-            src = as_const(hdr->states)[D.src];
+            src = as_const(a.states)[D.src];
         else
             src = D.src;
         // element W j - s of the window: src * (2^53)^(pos + W j - s + 1),
@@ -257,7 +262,7 @@ __global__ __launch_bounds__(256) void k_batch_rec(BatchArgs a) {
         uint64_t e = D.pos + 1 + W * j;
         e = e >= s ? e - s : e + kPeriod - s;
         double z = skip_any<VarFP64>(src, e, a.t_sk);
-        for (; j < nr; j += 256) {
+        for (; j < nr; j += TPW) {
             const uint64_t r = r0 + j;
             const uint64_t first = W * j;  // s + (window index of element 0)
             const uint64_t hi = D.len + s - first < W ? D.len + s - first : W;
@@ -476,15 +481,120 @@ __global__ __launch_bounds__(256) void k_batch_rows(BatchArgs a) {
 // XCDs cost the 10,000-window batch 12 % of its rate.)
 __device__ Mult chunk_sym[kChunkSymEntries];
 
+// The windows of a shared chunk (shared_chunk), in the dynamic LDS.
+struct SharedWins {
+    double z[kFlatBlock + 1];        // the window's state at the chunk's element 0
+    uint64_t at[4];
+    uint32_t range[kFlatBlock + 1];  // its part of the chunk: lo | hi << 16
+    uint32_t count[4], first[4], past[4];
+};
+static_assert(sizeof(SharedWins) <= kChunkMinLds, "the launches leave room for it");
+
 hipError_t upload_chunk_symbol(const Mult* entries) {
     return hipMemcpyToSymbol(HIP_SYMBOL(chunk_sym), entries, sizeof(Mult) * kChunkSymEntries, 0,
                              hipMemcpyHostToDevice);
 }
 
+// A chunk of the owned mode that windows d, d + 1, ... share: `info` and z0 are
+// window d's record for it, the later windows' are their ext records (empty
+// windows' are skipped), of which the first also gives the chunk's output
+// index.  The windows come into LDS up to 256 at a time, in order, and every
+// lane finds the window of each of its outputs by binary search: output k of a
+// window whose element 0 of the chunk has the state z is z J^r (2^53)^(2l), its
+// row's and its lane's multipliers.  So the time does not grow with the
+// windows, where one pass over the chunk per window took about 1.2 us each:
+// 9999 windows of 1 to 64 outputs 163 -> 6.5 us, 2924 of 1 to 256 62 -> 6.5,
+// 446 of 1 to 8192 19.6 -> 6.5.
 template <int KIND, bool NT>
+__device__ __forceinline__ void shared_chunk(const BatchArgs& a, double z0, uint64_t info,
+                                             const Mult& ma, const Mult& mb, SharedWins* s) {
+    constexpr uint64_t C = kChunkOuts;
+    const u64x2* ext = reinterpret_cast<const u64x2*>(a.ext);
+    const global_ptr<uint64_t> out = as_global(a.out);
+    const uint32_t l = threadIdx.x, lane = l & 63u, wave = l >> 6;
+    uint64_t w = (info & kRecIndexMask) >> 11;  // d + 1
+    uint64_t g = ~0ull;                         // the chunk's output index
+    uint32_t n = 1;                             // windows in LDS
+    if (l == 0) {
+        s->z[0] = z0;
+        s->range[0] = ((uint32_t)info & (uint32_t)(C - 1)) | (uint32_t)(info >> kRecHiShift) << 16;
+    }
+    for (bool more = true; more;) {
+        // windows w .. w + 255: the ones of this chunk, closed up
+        u64x2 R;
+        R.x = 0;
+        R.y = kRecEmpty;
+        if (w + l < a.n_desc) R = ext[w + l];
+        const bool full = R.y != kRecEmpty;
+        const uint64_t at = R.y & kRecIndexMask & ~(C - 1);
+        const uint64_t fulls = __ballot(full);
+        if (lane == 0) s->first[wave] = fulls ? 1u : 0u;
+        if (fulls && lane == (uint32_t)__builtin_ctzll(fulls)) s->at[wave] = at;
+        __syncthreads();
+        if (g == ~0ull)
+            for (int v = 3; v >= 0; --v)
+                if (s->first[v]) g = s->at[v];
+        const bool here = full && at == g;
+        const uint64_t mask = __ballot(here);
+        const bool past = __ballot(full && at != g) != 0;
+        if (lane == 0) {
+            s->count[wave] = (uint32_t)__popcll(mask);
+            s->past[wave] = past;
+        }
+        __syncthreads();
+        uint32_t pos = n + (uint32_t)__popcll(mask & ((1ull << lane) - 1));
+        for (uint32_t v = 0; v < wave; ++v) pos += s->count[v];
+        if (here) {
+            s->z[pos] = __builtin_bit_cast(double, R.x);
+            s->range[pos] = ((uint32_t)R.y & (uint32_t)(C - 1)) |
+                            (uint32_t)(R.y >> kRecHiShift) << 16;
+        }
+        n += s->count[0] + s->count[1] + s->count[2] + s->count[3];
+        w += kFlatBlock;
+        more = !(s->past[0] | s->past[1] | s->past[2] | s->past[3]) && w < a.n_desc;
+        __syncthreads();
+        if (g == ~0ull || n == 0) continue;  // none of the chunk's among them
+        uint32_t top = 1;
+        while (top < n) top <<= 1;
+#pragma unroll
+        for (uint32_t r = 0; r < kChunkRows; ++r) {
+            const uint32_t k = r * kFlatPerBlock + 2u * l;
+            uint32_t i = 0;  // the last window that starts at or before k, or 0
+            for (uint32_t step = top >> 1; step; step >>= 1)
+                if (i + step < n && (s->range[i + step] & 0xffffu) <= k) i += step;
+            const uint32_t ra = s->range[i];
+            // windows have at least one output: k + 1 is in this one or the next
+            const uint32_t ib = i + 1 < n && (s->range[i + 1] & 0xffffu) <= k + 1 ? i + 1 : i;
+            const uint32_t rb = s->range[ib];
+            const bool va = k >= (ra & 0xffffu) && k < ra >> 16;
+            const bool vb = k + 1 >= (rb & 0xffffu) && k + 1 < rb >> 16;
+            double za = s->z[i], zb = s->z[ib];
+            if (r) {
+                const Mult J = chunk_sym[2 * kFlatBlock + r - 1];
+                za = VarFP64::mul(za, J);
+                zb = VarFP64::mul(zb, J);
+            }
+            za = VarFP64::mul(za, ma);
+            zb = VarFP64::mul(zb, mb);
+            const global_ptr<uint64_t> p = out + (g + k);
+            if (va && vb)
+                put<NT>(reinterpret_cast<global_ptr<u64x2>>(p), pair_bits<VarFP64, KIND>(za, zb));
+            else if (va)
+                put<NT>(p, out_bits<VarFP64, KIND>(za));
+            else if (vb)
+                put<NT>(p + 1, out_bits<VarFP64, KIND>(zb));
+        }
+        n = 0;
+        __syncthreads();  // the next windows reuse the LDS
+    }
+}
+
+// DENSE: shared chunks go to shared_chunk, else window by window below.
+template <int KIND, bool NT, bool DENSE>
 __global__ __launch_bounds__(kFlatBlock) void k_batch_chunks(BatchArgs a) {
+    extern __shared__ char s_dyn[];  // caps residency; a shared chunk's windows (DENSE)
     constexpr uint32_t C = kChunkOuts;
-    const uint64_t n = a.n_rec;  // records (== hdr->n_rows)
+    const uint64_t n = a.n_rec;  // records
     const const_ptr<u64x2> rec = reinterpret_cast<const_ptr<u64x2>>(as_const(a.rec));
     constexpr uint64_t kRun = (uint64_t)kFlatXcds * kFlatXcdRun;
     const uint64_t runs = n / kRun * kRun;  // records in whole XCD runs
@@ -555,12 +665,14 @@ __global__ __launch_bounds__(kFlatBlock) void k_batch_chunks(BatchArgs a) {
             }
         } else if (!((info >> kRecMulti) & 1)) {
             part(info & kRecIndexMask & ~(uint64_t)(C - 1), z0, lo, hi);
+        } else if constexpr (DENSE) {
+            shared_chunk<KIND, NT>(a, z0, info, ma, mb, reinterpret_cast<SharedWins*>(s_dyn));
         } else {
             // Owned mode, a chunk that windows d, d + 1, ... share: the later
             // windows' records are their ext records (empty windows skipped);
             // the first of them also gives the chunk's output index.
             const const_ptr<u64x2> ext = reinterpret_cast<const_ptr<u64x2>>(as_const(a.ext));
-            const uint32_t n_desc = as_const(a.ws)->n_desc;
+            const uint32_t n_desc = a.n_desc;
             uint64_t w = (info & kRecIndexMask) >> 11;  // d + 1
             u64x2 R;
             R.y = kRecEmpty;
@@ -826,7 +938,7 @@ __global__ __launch_bounds__(1024) void k_static_descs(char* scratch, uint32_t n
         BatchHeader h;
         h.out = out;
         h.n_desc = n;
-        h.mode = kChunkPerRecord;
+        h.pad0 = 0;
         h.n_rows = s_sum[T - 1];
         h.states = nullptr;
         for (int i = 0; i < 4; ++i) h.pad[i] = 0;
@@ -849,17 +961,25 @@ hipError_t launch_queue(int kind, uint32_t grid, uint32_t block, hipStream_t s,
     return hipGetLastError();
 }
 
-const void* batch_rec_kernel(bool indexed) {
-    return indexed ? reinterpret_cast<const void*>(&k_batch_rec<true>)
-                   : reinterpret_cast<const void*>(&k_batch_rec<false>);
+const void* batch_rec_kernel(bool indexed, bool wave) {
+    if (wave)
+        return indexed ? reinterpret_cast<const void*>(&k_batch_rec<true, 64>)
+                       : reinterpret_cast<const void*>(&k_batch_rec<false, 64>);
+    return indexed ? reinterpret_cast<const void*>(&k_batch_rec<true, 256>)
+                   : reinterpret_cast<const void*>(&k_batch_rec<false, 256>);
 }
 
-const void* batch_chunks_kernel(int kind, bool nt) {
-    if (kind == 0)
-        return nt ? reinterpret_cast<const void*>(&k_batch_chunks<0, true>)
-                  : reinterpret_cast<const void*>(&k_batch_chunks<0, false>);
-    return nt ? reinterpret_cast<const void*>(&k_batch_chunks<1, true>)
-              : reinterpret_cast<const void*>(&k_batch_chunks<1, false>);
+template <int KIND>
+static const void* chunks_kernel_k(bool nt, bool dense) {
+    if (dense)
+        return nt ? reinterpret_cast<const void*>(&k_batch_chunks<KIND, true, true>)
+                  : reinterpret_cast<const void*>(&k_batch_chunks<KIND, false, true>);
+    return nt ? reinterpret_cast<const void*>(&k_batch_chunks<KIND, true, false>)
+              : reinterpret_cast<const void*>(&k_batch_chunks<KIND, false, false>);
+}
+
+const void* batch_chunks_kernel(int kind, bool nt, bool dense) {
+    return kind == 0 ? chunks_kernel_k<0>(nt, dense) : chunks_kernel_k<1>(nt, dense);
 }
 
 const void* batch_rows_kernel(int kind, bool nt) {

@@ -36,7 +36,7 @@ constexpr uint64_t kBatchMaxLen = 1ull << 24;
 struct BatchHeader {
     uint64_t* out;
     uint32_t n_desc;
-    uint32_t mode;  // chunked kernel: kChunkPerRecord or kChunkOwned
+    uint32_t pad0;
     uint64_t n_rows;
     const uint64_t* states;  // indexed batches: the stream-state table
     uint64_t pad[4];
@@ -88,7 +88,8 @@ constexpr uint64_t kRecEmpty = ~0ull;
 // through LDS.
 constexpr uint32_t kRecChunk = 4096;
 
-// Kernel arguments (fixed for the life of a plan but for n_rec and out).
+// Kernel arguments (fixed for the life of a plan but for the batch's own:
+// n_rec, out, n_desc and mode).
 struct BatchArgs {
     // Chunked kernel: its record array and, set for each batch (the plan
     // updates its graph node's arguments with the grid), the record count and
@@ -97,7 +98,12 @@ struct BatchArgs {
     uint64_t n_rec;
     uint64_t* out;
     RowRec* ext;            // chunked, owned mode: each window's first-chunk record
-    const BatchHeader* ws;  // device workspace
+    // Chunked kernel and every record pre-pass: the batch without its header.
+    const BatchDesc* desc;
+    const uint64_t* states;  // indexed batches: the stream-state table
+    uint32_t n_desc;
+    uint32_t mode;           // kChunkPerRecord or kChunkOwned
+    const BatchHeader* ws;  // device workspace (blocked and interleaved kernels)
     uint32_t cluster;       // workgroups sharing a row range (both batch kernels)
     Mult JB;                // (2^53)^(2*block*cluster): the next row of a lane
     Mult JB2;               // (2^53)^(4*block*cluster): two such rows
@@ -105,7 +111,7 @@ struct BatchArgs {
     const Mult* t_lo;
     const Mult* t_hi;
     const Mult* t_sk;       // kSkipLevels * kSkipSize entries
-    Mult JR;                // (2^53)^(row_outs*256): a pre-pass thread's next row
+    Mult JR;                // (2^53)^(row_outs*TPW): a pre-pass thread's next row
     uint32_t grid;          // workgroups of the row kernel
     uint32_t block;         // threads per workgroup of the row kernel
     uint32_t row_outs;      // outputs per row (2*kIlPairs*block, a power of two)
@@ -116,7 +122,9 @@ struct BatchArgs {
 // workgroups each take a contiguous range of rows and interleave them
 // (cluster = grid: workgroup w takes rows w, w + grid, ..., one write front
 // as in the plain row layout).
-const void* batch_rec_kernel(bool indexed);
+// wave: a wavefront per window (TPW = 64, 4 windows a workgroup), else a
+// workgroup (TPW = 256).
+const void* batch_rec_kernel(bool indexed, bool wave);
 const void* batch_rows_kernel(int kind, bool nontemporal);
 
 // Chunked kernel (FP64 reduction, 256 threads): the pre-pass writes one
@@ -130,8 +138,9 @@ constexpr uint32_t kChunkOuts = kChunkRows * 512;
 // The chunked kernel's multipliers in a static device array of its module:
 // (2^53)^(2l) for l < kFlatBlock, then (2^53)^(2l+1) (a lane's pair, each
 // half contiguous so a wave's loads of either are), then (2^53)^kFlatPerBlock
-// (one row).  Filled per device at set-up.
-constexpr uint32_t kChunkSymEntries = 2 * kFlatBlock + 1;
+// (one row) and its powers for the further rows of a chunk.  Filled per device at set-up.
+constexpr uint32_t kChunkSymEntries = 2 * kFlatBlock + kChunkRows - 1;
+constexpr uint32_t kChunkMinLds = 3328;  // dynamic LDS the chunk kernel needs at least
 hipError_t upload_chunk_symbol(const Mult* entries);
 // Records of the chunked kernel lie in record order (record j at j; the
 // pre-pass writes them as one cluster of one workgroup).  The kernel takes
@@ -140,7 +149,7 @@ hipError_t upload_chunk_symbol(const Mult* entries);
 // records [x kFlatXcdRun, (x + 1) kFlatXcdRun) of the run, so one XCD's
 // records share its L2's lines and it writes 4 MiB of consecutive chunks;
 // records after the last full run go in workgroup order.
-// Record modes of the chunked kernel (BatchHeader::mode):
+// Record modes of the chunked kernel (BatchArgs::mode):
 //  * per record: a record per chunk and window that meet, one workgroup each
 //    (windows in any order; a chunk that windows share is written by
 //    several workgroups);
@@ -156,7 +165,25 @@ constexpr uint32_t kChunkPerRecord = 0;
 constexpr uint32_t kChunkOwned = 1;
 constexpr uint64_t kDescFirstShared = 1ull << 62;
 constexpr uint64_t kDescLastShared = 1ull << 63;
-const void* batch_chunks_kernel(int kind, bool nontemporal);
+const void* batch_chunks_kernel(int kind, bool nontemporal, bool dense);
+// The kernel that writes a shared chunk's windows side by side (dense) writes
+// whole chunks 2 % slower (10,000 windows, 1,320,000 chunks: 3265 against 3198
+// us a batch), so it takes the batches where shared chunks are many or no long
+// batch hides them: fewer than kDenseChunks chunks (2000 windows, 20,000
+// chunks: 66 against 80 us), or a window for every eight.
+constexpr uint64_t kDenseChunks = 1ull << 16;
+inline bool chunks_dense(uint64_t chunks, uint64_t windows) {
+    return chunks < kDenseChunks || windows >= chunks / 8;
+}
+// Residency of a plan that names no kernel (non-temporal stores): 3 workgroups
+// per CU write the 10,000-window batch at 6.72 TB/s, 4 at 6.62.
+constexpr uint32_t kChunkImpliedOccupancy = 3;
+// The pre-pass gives a window a workgroup where the windows are long and too
+// few to fill the device with wavefronts (300 windows of 150 chunks on average
+// 98 against 107 us a batch; 9999 of 37 883 against 871).
+inline bool rec_wide(uint64_t chunks, uint64_t windows) {
+    return windows < 2048 && chunks >= 64 * windows;
+}
 
 // The kernel entry for (mulmod, kind, nontemporal, indexed); its single
 // parameter is a BatchArgs passed by value.

@@ -618,6 +618,8 @@ int nn_generate_batch_static(const nn_stream_desc* descs, uint32_t n, void* out_
     if (records > kStaticMaxRecords)  // cannot happen within the limits above
         return fail(NN_ERANGE, "batch of %llu chunk records", (unsigned long long)records);
     const hipStream_t s = (hipStream_t)stream;
+    uint32_t lds = (d->lds_per_cu / (kFlatDefaultOccupancy + 1) / 512 + 1) * 512;
+    if (lds > d->lds_per_block) lds = kChunkMinLds;
     char* ws = static_cast<char*>(d->scratch);
     // the caller's descriptors, then the descriptors and header the kernels read
     hipError_t e = hipMemcpyAsync(ws + kStaticRawOff, descs, (size_t)n * sizeof(nn_stream_desc),
@@ -626,7 +628,9 @@ int nn_generate_batch_static(const nn_stream_desc* descs, uint32_t n, void* out_
     // the chunked plan's arguments (nn_runtime.hip, slot_create) over the static workspace
     BatchArgs a;
     memset(&a, 0, sizeof a);
-    a.ws = reinterpret_cast<const BatchHeader*>(ws);
+    a.desc = reinterpret_cast<const BatchDesc*>(ws + kStaticDescOff);
+    a.n_desc = n;
+    a.mode = kChunkPerRecord;
     a.JB = make_mult(MultPowers::get().pow(kFlatPerBlock));
     a.Minv = make_mult(MultPowers::get().pow(kPeriod - 1));
     a.t_lo = d->t_lo;
@@ -637,18 +641,16 @@ int nn_generate_batch_static(const nn_stream_desc* descs, uint32_t n, void* out_
     a.grid = 1;
     a.cluster = 1;
     a.block = kFlatBlock;
-    a.JR = make_mult(MultPowers::get().pow((uint64_t)kChunkOuts * 256));
+    a.JR = make_mult(MultPowers::get().pow((uint64_t)kChunkOuts * 64));
     a.n_rec = records;
     a.out = static_cast<uint64_t*>(out_dev);
-    uint32_t lds = (d->lds_per_cu / (kFlatDefaultOccupancy + 1) / 512 + 1) * 512;
-    if (lds > d->lds_per_block) lds = 0;
     void* params[] = {&a};
-    // the record pre-pass: a workgroup per window
+    // the record pre-pass: a wavefront per window
     if (e == hipSuccess)
-        e = hipLaunchKernel(batch_rec_kernel(false), dim3(n > 65535 ? 65535u : n), dim3(256),
+        e = hipLaunchKernel(batch_rec_kernel(false, true), dim3((n + 3) / 4), dim3(256),
                             params, 0, s);
     if (e == hipSuccess)
-        e = hipLaunchKernel(batch_chunks_kernel(kind, true), dim3((uint32_t)records),
+        e = hipLaunchKernel(batch_chunks_kernel(kind, true, false), dim3((uint32_t)records),
                             dim3(kFlatBlock), params, lds, s);
     if (e != hipSuccess) return fail(NN_EHIP, "static batch launch: %s", hipGetErrorString(e));
     if (final_states)

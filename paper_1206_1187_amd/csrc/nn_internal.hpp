@@ -43,14 +43,16 @@ constexpr uint32_t kDefaultBlock = 256;
 
 }  // namespace nn
 
-// A batch plan: two slots, each a device workspace, a pinned staging copy
-// of it and a graph of the batch kernel (with the interleaved kernel's
-// row-record pre-pass before it).  Batches alternate between the slots, so the
-// host prepares batch i+1 while batch i runs; a slot is reused only after
-// the batch that last used it has finished.
+// A batch plan: two slots, each a pinned staging area for the batch's
+// descriptors and, for the blocked and interleaved kernels, its device copy and
+// a graph of the batch kernel (with the interleaved kernel's row-record
+// pre-pass before it); the chunked kernel's pre-pass reads the staging area.
+// Batches alternate between the slots, so the host prepares batch i+1 while
+// batch i runs; a slot is reused only after the batch that last used it has
+// finished.
 struct nn_batch_slot {
     size_t ws_bytes = 0;
-    void* ws_dev = nullptr;
+    void* ws_dev = nullptr;       // blocked and interleaved
     void* ws_host = nullptr;      // pinned staging, same layout as ws_dev
     nn::RowRec* rec = nullptr;    // device, cap_rows + 2 grid records (interleaved, chunked)
     nn::RowRec* ext = nullptr;    // device, cap_desc first-chunk records (chunked)
@@ -58,11 +60,7 @@ struct nn_batch_slot {
     bool pending = false;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    hipGraphNode_t main_node = nullptr;  // the batch kernel's node
-    uint32_t main_grid = 0;              // its grid as last set (chunked kernel, set per batch)
-    hipGraphNode_t rec_node = nullptr;   // the record pre-pass's node (interleaved, indexed chunked)
-    hipEvent_t ready = nullptr;          // overlapped plans: this slot's upload and pre-pass done
-    uint32_t rec_grid = 0;               // its grid as last set (one workgroup per window)
+    hipGraphNode_t rec_node = nullptr;   // the record pre-pass's node (interleaved)
     nn::BatchArgs args;
 };
 
@@ -73,13 +71,7 @@ struct nn_batch_plan {
     bool indexed = false;
     uint32_t mulmod = 0, block = 0, grid = 0, cluster = 1;
     bool nontemporal = true, use_graph = true, interleaved = false, chunks = false;
-    // Chunked plans of nn_generate_batch: each batch's descriptor upload and
-    // record pre-pass run on `side`, so they overlap the previous batch's
-    // chunk kernel; the caller's stream waits for them (event `ready` of the
-    // slot) and runs the chunk kernel.  They touch only the slot's own
-    // workspace, which the host has seen free (plan_wait) before reuse.
-    bool overlap = false;
-    hipStream_t side = nullptr;
+    nn::Mult JR64, JR256;  // chunked: a pre-pass thread's step (BatchArgs::JR)
     uint64_t cap_rows = 0;
     uint32_t map_grid = 0;
     uint32_t max_streams = 0;

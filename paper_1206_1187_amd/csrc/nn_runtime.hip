@@ -181,11 +181,12 @@ int ensure_device_current(int dev, DeviceTables** out) {
             std::copy(hb.begin(), hb.end(), sym.begin() + kFlatSymLo);
             e = upload_flat_symbol(sym.data());
             // the chunked batch kernel's: t_lo's even entries below 2*kFlatBlock,
-            // then its odd ones, then one row's step
+            // then its odd ones, then the steps by one, two and three rows
             std::vector<Mult> cs;
             for (uint32_t l = 0; l < kFlatBlock; ++l) cs.push_back(h[2u * l]);
             for (uint32_t l = 0; l < kFlatBlock; ++l) cs.push_back(h[2u * l + 1]);
-            cs.push_back(make_mult(MultPowers::get().pow(kFlatPerBlock)));
+            for (uint32_t r = 1; r < kChunkRows; ++r)
+                cs.push_back(make_mult(MultPowers::get().pow(kFlatPerBlock * r)));
             if (e == hipSuccess) e = upload_chunk_symbol(cs.data());
             if (e != hipSuccess) {
                 (void)hipFree(mem);
@@ -220,13 +221,11 @@ int current_device(DeviceTables** out) {
 // ---------------------------------------------------------------- plans --
 
 void plan_release(nn_batch_plan* p) {
-    if (p->side) (void)hipStreamSynchronize(p->side);
     for (nn_batch_slot& q : p->slot) {
         if (q.done) {
             (void)hipEventSynchronize(q.done);
             (void)hipEventDestroy(q.done);
         }
-        if (q.ready) (void)hipEventDestroy(q.ready);
         if (q.exec) (void)hipGraphExecDestroy(q.exec);
         if (q.graph) (void)hipGraphDestroy(q.graph);
         if (q.ws_dev) (void)hipFree(q.ws_dev);
@@ -234,7 +233,6 @@ void plan_release(nn_batch_plan* p) {
         if (q.ext) (void)hipFree(q.ext);
         if (q.ws_host) (void)hipHostFree(q.ws_host);
     }
-    if (p->side) (void)hipStreamDestroy(p->side);
     delete p;
 }
 
@@ -244,7 +242,8 @@ namespace {
 int slot_create(nn_batch_plan* p, nn_batch_slot& q, const DeviceTables& d,
                 const uint64_t* states) {
     q.ws_bytes = sizeof(BatchHeader) + (size_t)p->cap_desc * sizeof(BatchDesc);
-    hipError_t e = hipMalloc(&q.ws_dev, q.ws_bytes);
+    // the chunked kernel's pre-pass reads the pinned staging itself
+    hipError_t e = p->chunks ? hipSuccess : hipMalloc(&q.ws_dev, q.ws_bytes);
     if (e == hipSuccess && (p->interleaved || p->chunks))  // grid * per <= rows + clusters + grid
         e = hipMalloc((void**)&q.rec, (p->cap_rows + 2ull * p->grid) * sizeof(RowRec));
     if (e == hipSuccess && p->chunks)
@@ -258,10 +257,16 @@ int slot_create(nn_batch_plan* p, nn_batch_slot& q, const DeviceTables& d,
     memset(hdr, 0, sizeof *hdr);
     hdr->states = states;
     e = hipEventCreateWithFlags(&q.done, hipEventDisableTiming);
-    if (e == hipSuccess && p->overlap) e = hipEventCreateWithFlags(&q.ready, hipEventDisableTiming);
     if (e != hipSuccess) return fail(NN_EHIP, "event: %s", hipGetErrorString(e));
     const uint32_t block = p->block, cluster = p->cluster;
-    q.args.ws = (const BatchHeader*)q.ws_dev;
+    void* ws = q.ws_dev;
+    if (p->chunks) {
+        e = hipHostGetDevicePointer(&ws, q.ws_host, 0);
+        if (e != hipSuccess) return fail(NN_EHIP, "pinned staging: %s", hipGetErrorString(e));
+    }
+    q.args.ws = (const BatchHeader*)ws;
+    q.args.desc = reinterpret_cast<const BatchDesc*>(q.args.ws + 1);
+    q.args.states = states;
     q.args.cluster = cluster;
     q.args.JB = make_mult(MultPowers::get().pow(2ull * block * cluster));
     q.args.JB2 = make_mult(MultPowers::get().pow(4ull * block * cluster));
@@ -282,40 +287,30 @@ int slot_create(nn_batch_plan* p, nn_batch_slot& q, const DeviceTables& d,
         q.args.cluster = 1;
     }
     q.args.JR = make_mult(MultPowers::get().pow((uint64_t)q.args.row_outs * 256));
-    if (!p->use_graph) return NN_OK;
+    if (!p->use_graph || p->chunks) return NN_OK;
     // The graph holds the kernels; the descriptor upload before each replay
     // is an ordinary async copy on the same stream (a copy node from pinned
     // host memory measured slower on MI355X).
     e = hipGraphCreate(&q.graph, 0);
-    hipGraphNode_t last = nullptr;
+    hipGraphNode_t last = nullptr, main_node = nullptr;
     void* params[] = {&q.args};
-    if (e == hipSuccess && (p->interleaved || p->chunks) && !p->overlap) {
-        hipKernelNodeParams kp;
-        memset(&kp, 0, sizeof kp);
-        kp.func = const_cast<void*>(batch_rec_kernel(p->indexed));
+    hipKernelNodeParams kp;
+    memset(&kp, 0, sizeof kp);
+    kp.kernelParams = params;
+    if (e == hipSuccess && p->interleaved) {
+        kp.func = const_cast<void*>(batch_rec_kernel(p->indexed, false));
         kp.gridDim = dim3(p->map_grid);
         kp.blockDim = dim3(256);
-        kp.kernelParams = params;
         e = hipGraphAddKernelNode(&last, q.graph, nullptr, 0, &kp);
         q.rec_node = last;
-        q.rec_grid = p->map_grid;
     }
     if (e == hipSuccess) {
-        hipKernelNodeParams kp;
-        memset(&kp, 0, sizeof kp);
-        kp.func = p->chunks ? const_cast<void*>(batch_chunks_kernel(p->kind, p->nontemporal))
-                  : p->interleaved
-                      ? const_cast<void*>(batch_rows_kernel(p->kind, p->nontemporal))
-                      : const_cast<void*>(
-                            batch_kernel((int)p->mulmod, p->kind, p->nontemporal, p->indexed));
-        kp.gridDim = dim3(p->grid ? p->grid : 1);  // chunked, grid 0: set per batch
+        kp.func = p->interleaved ? const_cast<void*>(batch_rows_kernel(p->kind, p->nontemporal))
+                                 : const_cast<void*>(batch_kernel((int)p->mulmod, p->kind,
+                                                                  p->nontemporal, p->indexed));
+        kp.gridDim = dim3(p->grid);
         kp.blockDim = dim3(block);
-        kp.sharedMemBytes = p->chunks ? p->flat_lds : 0;
-        kp.kernelParams = params;
-        kp.extra = nullptr;
-        e = hipGraphAddKernelNode(&q.main_node, q.graph, last ? &last : nullptr, last ? 1 : 0,
-                                  &kp);
-        q.main_grid = p->grid ? p->grid : 1;
+        e = hipGraphAddKernelNode(&main_node, q.graph, last ? &last : nullptr, last ? 1 : 0, &kp);
     }
     if (e == hipSuccess) e = hipGraphInstantiate(&q.exec, q.graph, nullptr, nullptr, 0);
     if (e != hipSuccess) return fail(NN_EHIP, "batch graph: %s", hipGetErrorString(e));
@@ -335,14 +330,17 @@ int plan_create(int kind, uint32_t max_streams, uint64_t max_outputs, const nn_b
     if (c.flags &
         ~(NN_CFG_TEMPORAL_STORES | NN_BATCH_NO_GRAPH | NN_BATCH_INTERLEAVED | NN_BATCH_CHUNKS))
         return fail(NN_EINVAL, "unknown batch flags 0x%x", c.flags);
-    const bool chunks = (c.flags & NN_BATCH_CHUNKS) != 0;
+    // A cfg that asks for no kernel gets the chunked one (see below).
+    const bool implied = !(c.flags & (NN_BATCH_CHUNKS | NN_BATCH_INTERLEAVED)) && !c.block &&
+                         !c.grid && !c.cluster && (!c.mulmod || c.mulmod == NN_MULMOD_FP64);
+    const bool chunks = (c.flags & NN_BATCH_CHUNKS) != 0 || implied;
     if (chunks && (c.flags & NN_BATCH_INTERLEAVED))
         return fail(NN_EINVAL, "NN_BATCH_CHUNKS and NN_BATCH_INTERLEAVED are exclusive");
     if (chunks && ((c.block && c.block != 256) || c.cluster > 1 ||
                    (c.mulmod && c.mulmod != NN_MULMOD_FP64)))
         return fail(NN_EINVAL, "the chunked batch kernel has 256 threads, no clusters and the "
                                "FP64 reduction");
-    if (c.occupancy && !chunks)
+    if (c.occupancy && !(c.flags & NN_BATCH_CHUNKS))
         return fail(NN_EINVAL, "occupancy applies to the chunked batch kernel only");
     if (c.occupancy && (c.occupancy < 2 || c.occupancy > 16))
         return fail(NN_EINVAL, "occupancy %u: must be 0 or in [2, 16]", c.occupancy);
@@ -387,7 +385,6 @@ int plan_create(int kind, uint32_t max_streams, uint64_t max_outputs, const nn_b
     p->use_graph = !(c.flags & NN_BATCH_NO_GRAPH);
     p->interleaved = (c.flags & NN_BATCH_INTERLEAVED) != 0;
     p->chunks = chunks;
-    p->overlap = chunks && !indexed;
     if (p->interleaved &&
         (mulmod != NN_MULMOD_FP64 || (block & (block - 1)) || block > 256)) {
         plan_release(p);
@@ -406,17 +403,12 @@ int plan_create(int kind, uint32_t max_streams, uint64_t max_outputs, const nn_b
     p->J512 = make_mult(MultPowers::get().pow(kFlatPerBlock));
     // the chunk kernel's residency cap: dynamic LDS that leaves room for
     // `occupancy` workgroups per compute unit, not one more
-    p->occupancy = c.occupancy ? c.occupancy : kFlatDefaultOccupancy;
+    p->occupancy = c.occupancy ? c.occupancy
+                   : implied && p->nontemporal ? kChunkImpliedOccupancy : kFlatDefaultOccupancy;
     p->flat_lds = (d->lds_per_cu / (p->occupancy + 1) / 512 + 1) * 512;
-    if (p->flat_lds > d->lds_per_block) p->flat_lds = 0;
-    if (p->overlap) {
-        // default priority; non-blocking, so it does not wait for the null stream
-        hipError_t e = hipStreamCreateWithFlags(&p->side, hipStreamNonBlocking);
-        if (e != hipSuccess) {
-            plan_release(p);
-            return fail(NN_EHIP, "batch side stream: %s", hipGetErrorString(e));
-        }
-    }
+    if (p->flat_lds > d->lds_per_block) p->flat_lds = kChunkMinLds;
+    p->JR64 = make_mult(MultPowers::get().pow((uint64_t)kChunkOuts * 64));
+    p->JR256 = make_mult(MultPowers::get().pow((uint64_t)kChunkOuts * 256));
     for (nn_batch_slot& q : p->slot) {
         st = slot_create(p, q, *d, states);
         if (st) {
@@ -450,17 +442,58 @@ bool plan_idle(nn_batch_plan* p) {
     return idle;
 }
 
+namespace {
+
+// Records the slot's completion and turns to the other slot.
+int batch_launched(nn_batch_plan* p, hipError_t e, hipStream_t stream) {
+    if (e != hipSuccess) return fail(NN_EHIP, "batch launch: %s", hipGetErrorString(e));
+    nn_batch_slot& q = p->slot[p->next];
+    e = hipEventRecord(q.done, stream);
+    if (e != hipSuccess) return fail(NN_EHIP, "batch event: %s", hipGetErrorString(e));
+    q.pending = true;
+    p->next ^= 1;
+    return NN_OK;
+}
+
+}  // namespace
+
 int plan_launch_staged(nn_batch_plan* p, uint32_t nd, void* out, hipStream_t stream) {
     nn_batch_slot& q = p->slot[p->next];
-    // A small batch travels in the kernel arguments (no upload to wait for)
-    // and runs the blocked kernel whichever kernel the plan has; larger ones
-    // of an interleaved plan run its pre-pass and row kernel.
-    const bool in_args = nd <= kInlineDescs;
-    const bool il = (p->interleaved || p->chunks) && !in_args;
-    const uint64_t row = p->chunks && !in_args ? (uint64_t)kChunkOuts
-                                               : (il ? 2ull * kIlPairs : 2ull) * p->block;
     BatchHeader* hdr = (BatchHeader*)q.ws_host;
     BatchDesc* dd = plan_staged_descs(p);
+    // A small batch travels in the kernel arguments (no upload to wait for).
+    if (nd <= kInlineDescs && p->mulmod == NN_MULMOD_FP64 && (!p->indexed || p->host_states)) {
+        // each window as the plain flat layout writes it, from a start state
+        // computed here (so no skip-ahead on the device)
+        BatchFlatInline in;
+        memset(&in, 0, sizeof in);
+        in.out = (uint64_t*)out;
+        in.n = nd;
+        uint64_t chunks = 0;
+        for (uint32_t k = 0; k < nd; ++k) {
+            const BatchDesc& D = dd[k];
+            FlatWin& w = in.w[k];
+            w.s = (uint32_t)(D.out_off & 1u);
+            const uint64_t src = p->indexed ? p->host_states[D.src] : D.src;
+            w.base = h_skip(src, (D.pos % kPeriod) + 1 - w.s);  // element -s
+            w.len = D.len;
+            w.out_off = D.out_off;
+            w.chunk0 = (uint32_t)chunks;
+            chunks += (D.len + w.s + kChunkOuts - 1) / kChunkOuts;
+        }
+        return batch_launched(p,
+                              launch_batch_flat_inline(p->kind, p->nontemporal, (uint32_t)chunks,
+                                                       p->flat_lds, stream, p->tabs, p->M1,
+                                                       p->J512, in),
+                              stream);
+    }
+    // Another small batch runs the blocked kernel from its arguments, unless
+    // the plan is chunked; larger ones of an interleaved plan run its pre-pass
+    // and row kernel.
+    const bool in_args = nd <= kInlineDescs && !p->chunks;
+    const bool il = (p->interleaved || p->chunks) && !in_args;
+    const uint64_t row = p->chunks ? (uint64_t)kChunkOuts
+                                   : (il ? 2ull * kIlPairs : 2ull) * p->block;
     uint64_t rows = 0;
     for (uint32_t k = 0; k < nd; ++k) {
         dd[k].row_start = rows;
@@ -481,7 +514,7 @@ int plan_launch_staged(nn_batch_plan* p, uint32_t nd, void* out, hipStream_t str
     // disjoint.  Windows are independent, so they are sorted here if they
     // are not (a server's batches come in admission order); overlapping
     // windows take a record per chunk and window.
-    bool owned = p->chunks && !in_args;
+    bool owned = p->chunks;
     if (owned) {
         bool sorted = true;
         for (uint32_t k = 1; k < nd && sorted; ++k) sorted = dd[k - 1].out_off <= dd[k].out_off;
@@ -519,120 +552,61 @@ int plan_launch_staged(nn_batch_plan* p, uint32_t nd, void* out, hipStream_t str
     }
     hdr->out = (uint64_t*)out;
     hdr->n_desc = nd;
-    hdr->mode = owned ? kChunkOwned : kChunkPerRecord;
     hdr->n_rows = rows;
     const size_t bytes = sizeof(BatchHeader) + nd * sizeof(BatchDesc);
     hipError_t e;
-    if (in_args && p->mulmod == NN_MULMOD_FP64 && (!p->indexed || p->host_states)) {
-        // each window as the plain flat layout writes it, from a start state
-        // computed here (so no skip-ahead on the device)
-        BatchFlatInline in;
-        memset(&in, 0, sizeof in);
-        in.out = (uint64_t*)out;
-        in.n = nd;
-        uint64_t chunks = 0;
-        for (uint32_t k = 0; k < nd; ++k) {
-            const BatchDesc& D = dd[k];
-            FlatWin& w = in.w[k];
-            w.s = (uint32_t)(D.out_off & 1u);
-            const uint64_t src = p->indexed ? p->host_states[D.src] : D.src;
-            w.base = h_skip(src, (D.pos % kPeriod) + 1 - w.s);  // element -s
-            w.len = D.len;
-            w.out_off = D.out_off;
-            w.chunk0 = (uint32_t)chunks;
-            chunks += (D.len + w.s + kChunkOuts - 1) / kChunkOuts;
-        }
-        e = launch_batch_flat_inline(p->kind, p->nontemporal, (uint32_t)chunks, p->flat_lds,
-                                     stream, p->tabs, p->M1, p->J512, in);
-        if (e != hipSuccess) return fail(NN_EHIP, "batch launch: %s", hipGetErrorString(e));
-        e = hipEventRecord(q.done, stream);
-        if (e != hipSuccess) return fail(NN_EHIP, "batch event: %s", hipGetErrorString(e));
-        q.pending = true;
-        p->next ^= 1;
-        return NN_OK;
-    }
     if (in_args) {
         BatchInline in;
         memset(&in, 0, sizeof in);
         memcpy(&in, q.ws_host, bytes);
         e = launch_batch_inline((int)p->mulmod, p->kind, p->nontemporal, p->indexed, p->grid,
                                 p->block, stream, q.args, in);
-        if (e != hipSuccess) return fail(NN_EHIP, "batch launch: %s", hipGetErrorString(e));
-        e = hipEventRecord(q.done, stream);
-        if (e != hipSuccess) return fail(NN_EHIP, "batch event: %s", hipGetErrorString(e));
-        q.pending = true;
-        p->next ^= 1;
-        return NN_OK;
+        return batch_launched(p, e, stream);
     }
-    // overlapped plans upload and run the pre-pass on the side stream
-    const hipStream_t up = p->overlap ? p->side : stream;
-    e = hipMemcpyAsync(q.ws_dev, q.ws_host, bytes, hipMemcpyHostToDevice, up);
-    // the chunked kernel's workgroups: one per record unless the plan fixed a grid;
-    // its arguments carry the record count and the output
-    const uint32_t chunk_grid = p->grid ? p->grid : (uint32_t)rows;
     q.args.n_rec = rows;
     q.args.out = (uint64_t*)out;
+    q.args.n_desc = nd;
+    q.args.mode = owned ? kChunkOwned : kChunkPerRecord;
     // the record pre-pass: a workgroup per window (the window's skip-ahead is
     // its one long dependent chain), at least one
     const uint32_t rec_grid = nd < 1 ? 1u : nd > 65535 ? 65535u : nd;
-    if (e == hipSuccess && p->overlap) {
-        BatchArgs copy = q.args;
-        void* params[] = {&copy};
-        e = hipLaunchKernel(batch_rec_kernel(p->indexed), dim3(rec_grid), dim3(256), params, 0,
-                            p->side);
-        if (e == hipSuccess) e = hipEventRecord(q.ready, p->side);
-        if (e == hipSuccess) e = hipStreamWaitEvent(stream, q.ready, 0);
+    void* params[] = {&q.args};
+    if (p->chunks) {
+        const bool wide = rec_wide(rows, nd);
+        q.args.JR = wide ? p->JR256 : p->JR64;
+        e = hipLaunchKernel(batch_rec_kernel(p->indexed, !wide),
+                            dim3(wide ? rec_grid : (nd + 3) / 4), dim3(256), params, 0, stream);
+        // one workgroup per record unless the plan fixed a grid
+        if (e == hipSuccess)
+            e = hipLaunchKernel(batch_chunks_kernel(p->kind, p->nontemporal,
+                                                    owned && chunks_dense(rows, nd)),
+                                dim3(p->grid ? p->grid : (uint32_t)rows), dim3(kFlatBlock), params,
+                                p->flat_lds, stream);
+        return batch_launched(p, e, stream);
     }
-    if (e == hipSuccess && p->use_graph && q.rec_node && rec_grid != q.rec_grid) {
-        hipKernelNodeParams kp;
-        memset(&kp, 0, sizeof kp);
-        void* params[] = {&q.args};
-        kp.func = const_cast<void*>(batch_rec_kernel(p->indexed));
-        kp.gridDim = dim3(rec_grid);
-        kp.blockDim = dim3(256);
-        kp.kernelParams = params;
-        e = hipGraphExecKernelNodeSetParams(q.exec, q.rec_node, &kp);
-        if (e == hipSuccess) q.rec_grid = rec_grid;
-    }
-    if (e == hipSuccess && p->use_graph && p->chunks) {
-        hipKernelNodeParams kp;
-        memset(&kp, 0, sizeof kp);
-        void* params[] = {&q.args};
-        kp.func = const_cast<void*>(batch_chunks_kernel(p->kind, p->nontemporal));
-        kp.gridDim = dim3(chunk_grid);
-        kp.blockDim = dim3(p->block);
-        kp.sharedMemBytes = p->flat_lds;
-        kp.kernelParams = params;
-        e = hipGraphExecKernelNodeSetParams(q.exec, q.main_node, &kp);
-        if (e == hipSuccess) q.main_grid = chunk_grid;
-    }
+    e = hipMemcpyAsync(q.ws_dev, q.ws_host, bytes, hipMemcpyHostToDevice, stream);
     if (e == hipSuccess && p->use_graph) {
-        e = hipGraphLaunch(q.exec, stream);
-    } else if (e == hipSuccess) {
-        BatchArgs copy = q.args;
-        void* params[] = {&copy};
-        if (p->interleaved || p->chunks) {
-            if (!p->overlap)
-                e = hipLaunchKernel(batch_rec_kernel(p->indexed), dim3(rec_grid), dim3(256),
-                                    params, 0, stream);
-            if (e == hipSuccess && p->chunks)
-                e = hipLaunchKernel(batch_chunks_kernel(p->kind, p->nontemporal),
-                                    dim3(chunk_grid), dim3(kFlatBlock), params, p->flat_lds,
-                                    stream);
-            else if (e == hipSuccess)
-                e = hipLaunchKernel(batch_rows_kernel(p->kind, p->nontemporal), dim3(p->grid),
-                                    dim3(p->block), params, 0, stream);
-        } else {
-            e = launch_batch((int)p->mulmod, p->kind, p->nontemporal, p->indexed, p->grid,
-                             p->block, stream, q.args);
+        if (q.rec_node) {
+            hipKernelNodeParams kp;
+            memset(&kp, 0, sizeof kp);
+            kp.func = const_cast<void*>(batch_rec_kernel(p->indexed, false));
+            kp.gridDim = dim3(rec_grid);
+            kp.blockDim = dim3(256);
+            kp.kernelParams = params;
+            e = hipGraphExecKernelNodeSetParams(q.exec, q.rec_node, &kp);
         }
+        if (e == hipSuccess) e = hipGraphLaunch(q.exec, stream);
+    } else if (e == hipSuccess && p->interleaved) {
+        e = hipLaunchKernel(batch_rec_kernel(p->indexed, false), dim3(rec_grid), dim3(256), params, 0,
+                            stream);
+        if (e == hipSuccess)
+            e = hipLaunchKernel(batch_rows_kernel(p->kind, p->nontemporal), dim3(p->grid),
+                                dim3(p->block), params, 0, stream);
+    } else if (e == hipSuccess) {
+        e = launch_batch((int)p->mulmod, p->kind, p->nontemporal, p->indexed, p->grid, p->block,
+                         stream, q.args);
     }
-    if (e != hipSuccess) return fail(NN_EHIP, "batch launch: %s", hipGetErrorString(e));
-    e = hipEventRecord(q.done, stream);
-    if (e != hipSuccess) return fail(NN_EHIP, "batch event: %s", hipGetErrorString(e));
-    q.pending = true;
-    p->next ^= 1;
-    return NN_OK;
+    return batch_launched(p, e, stream);
 }
 
 }  // namespace nn

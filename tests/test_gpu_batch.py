@@ -201,6 +201,47 @@ def test_chunked_batch_unsorted_windows(temporal):
         assert f == orc.skip(s, n)
 
 
+@pytest.mark.parametrize("longest", [2, 8, 700, 3000])
+@pytest.mark.parametrize("occupancy", [0, 16])
+def test_chunks_shared_by_few_and_many_windows(longest, occupancy):
+    """Chunks that two to about a thousand windows share (one to four loads of
+    256 windows each), gaps between them, a window that fills whole chunks in
+    between; at the residency cap with the least LDS too."""
+    rng = np.random.default_rng(longest)
+    lengths = [int(x) for x in rng.integers(1, longest + 1, 2500 if longest < 9 else 300)]
+    lengths[100] = 9000
+    states, lengths, offsets, total = _mixed_batch(62 + longest, lengths)
+    for kind, dt in (("u64", torch.uint64), ("f64", torch.float64)):
+        buf = _sentinel(total)
+        with nn.BatchPlan(kind, len(lengths), total, chunks=True, occupancy=occupancy) as plan:
+            plan.generate(states, lengths, offsets, buf.view(dt))
+            torch.cuda.synchronize()
+        _check_batch(_bits(buf), states, lengths, offsets, kind)
+
+
+def test_chunked_batch_long_windows_back_to_back():
+    """130 windows of 600 chunks each: a workgroup per window in the pre-pass,
+    and over 2^16 chunks in all, so the chunk kernel for long batches; two
+    batches back to back, then a short one; sampled against the oracle."""
+    n, size = 130, 600 * 2048 + 3
+    states = np.array([orc.seed(wl.INDEX_MIN + 97 * i) for i in range(n)], dtype=np.uint64)
+    lengths = np.full(n, size, dtype=np.uint64)
+    offsets = np.arange(n, dtype=np.uint64) * size
+    short = np.full(n, 3000, dtype=np.uint64)
+    outs = [torch.empty(n * size, dtype=torch.uint64, device="cuda") for _ in range(3)]
+    with nn.BatchPlan("u64", n, n * size) as plan:
+        for out, ln, st in zip(outs, (lengths, lengths, short), (states, states[::-1], states)):
+            plan.generate(st, ln, offsets, out)
+        torch.cuda.synchronize()
+    for out, ln, st in zip(outs, (lengths, lengths, short), (states, states[::-1], states)):
+        flat = out.view(torch.int64)
+        for i in (0, 1, 64, n - 1):
+            for at in (0, int(ln[i]) // 2, int(ln[i]) - 700):
+                ref, _ = orc.gen(orc.skip(int(st[i]), at), 700, "u64")
+                o = int(offsets[i]) + at
+                assert np.array_equal(flat[o:o + 700].cpu().numpy().view(np.uint64), ref), (i, at)
+
+
 def test_chunked_batch_validation():
     for bad in (dict(block=128), dict(cluster=4), dict(mulmod="shoup"), dict(interleaved=True)):
         with pytest.raises(nn.NNError):
