@@ -310,8 +310,8 @@ typedef struct nn_batch_cfg {
  * persistent workgroups taking the records round-robin in the same order.  Needs
  * the FP64 reduction, block 0 or 256, cluster 0 or 1 and output indices
  * below 2^51 (NN_ERANGE otherwise).  Exclusive with NN_BATCH_INTERLEAVED.
- * Batches of at most 16 windows travel in the kernel arguments (the FP64
- * reduction's flat inline kernel). */
+ * Batches of at most 16 windows, with grid 0 of at most 128, travel in the
+ * kernel arguments (the flat inline kernel). */
 #define NN_BATCH_CHUNKS 32u
 
 /* Opaque batch plan, owned by the library until nn_batch_plan_destroy: pinned
@@ -366,7 +366,8 @@ int nn_generate_batch(nn_batch_plan *plan, const nn_stream_desc *descs, uint32_t
  * about 23 MB that every device loading the library holds until the
  * process ends.  Every stream of `descs` (host array of n) is written to
  * out_dev (device memory of the current device, 16-byte aligned) with the
- * chunked batch kernel (NN_BATCH_CHUNKS, non-temporal stores); outputs are
+ * chunked batch kernel (NN_BATCH_CHUNKS, non-temporal stores) or, for at most
+ * 128 streams outside a capture, the flat inline kernel; outputs are
  * identical to nn_generate on each stream alone.  kind: nn_out_kind.
  * final_states (host array of n, or NULL) receives each stream's state
  * after its window.  Limits: at most 65 536 streams and 2^31 outputs per

@@ -699,31 +699,38 @@ __global__ __launch_bounds__(kFlatBlock) void k_batch_chunks(BatchArgs a) {
     }
 }
 
-// Small batches in the kernel arguments (see BatchFlatInline): workgroup b
-// finds its window among at most kInlineDescs (a uniform scan), then writes
-// chunk c = b - chunk0 of it exactly as k_generate_flat writes a chunk,
-// storing only the window's outputs.
-template <int KIND, bool NT>
+// Small batches in the kernel arguments (see BatchFlatInline): a workgroup
+// finds its window by the count of windows that start at or before its chunk
+// (each lane of a wavefront compares one of 64 at a time), then writes chunk
+// b - chunk0 of it exactly as k_generate_flat writes a chunk, storing only
+// the window's outputs.
+template <int KIND, bool NT, uint32_t N>
 __global__ __launch_bounds__(kFlatBlock) void k_batch_flat_inline(const Mult* __restrict__ tabs,
                                                                   Mult M1, Mult J,
-                                                                  BatchFlatInline in) {
+                                                                  BatchFlatInline<N> in) {
     extern __shared__ char occupancy_cap[];
     (void)occupancy_cap;
     constexpr uint32_t C = kChunkOuts;
-    const uint32_t b = blockIdx.x;
-    uint32_t d = 0;
-    for (uint32_t k = 1; k < in.n; ++k)
-        if (in.w[k].chunk0 <= b) d = k;
-    const FlatWin W = in.w[d];
-    const uint64_t c = b - W.chunk0;
+    const uint32_t b =
+        blockIdx.x < in.runs ? (uint32_t)xcd_run_index(blockIdx.x) : (uint32_t)blockIdx.x;
     const uint32_t l = threadIdx.x;
+    uint32_t d = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < N; k += 64) {
+        const uint32_t i = k + (l & 63u);
+        d += (uint32_t)__popcll(__ballot(i < in.n && in.chunk0[i < N ? i : 0] <= b));
+    }
+    d -= 1;  // window 0 starts at chunk 0
+    const FlatWin W = in.w[d];
+    const uint64_t c = b - in.chunk0[d];
+    const uint32_t s = (uint32_t)W.out_off & (kInlineAlign - 1);
     double za, zb;
     flat_start<VarFP64>(c, l, (int)kChunkRows, W.base, tabs, M1, za, zb);
     // chunk-relative positions k of the window's elements k - s: [s, len + s)
     const uint64_t first = C * c;
-    const global_ptr<uint64_t> p = as_global(in.out) + (W.out_off - W.s + first + 2u * l);
-    const uint64_t hi = W.len + W.s;
-    if (first >= W.s && first + C <= hi) {
+    const global_ptr<uint64_t> p = as_global(in.out) + (W.out_off - s + first + 2u * l);
+    const uint64_t hi = W.len + s;
+    if (first >= s && first + C <= hi) {
 #pragma unroll
         for (int r = 0; r < (int)kChunkRows; ++r) {
             put<NT>(reinterpret_cast<global_ptr<u64x2>>(p + r * kFlatPerBlock),
@@ -735,36 +742,33 @@ __global__ __launch_bounds__(kFlatBlock) void k_batch_flat_inline(const Mult* __
         return;
     }
     // the window's first or last chunk: keep k in [s, len + s)
-    const uint32_t lo = first == 0 ? W.s : 0;
+    const uint32_t lo = first == 0 ? s : 0;
     const uint32_t top = hi - first < C ? (uint32_t)(hi - first) : C;
-#pragma unroll
-    for (int r = 0; r < (int)kChunkRows; ++r) {
+    for (int r = 0; r < (int)kChunkRows && r * kFlatPerBlock < top; ++r) {
         put_pair_in<KIND, NT>(p + r * kFlatPerBlock, za, zb, r * kFlatPerBlock + 2u * l, lo, top);
         za = VarFP64::mul(za, J);
         zb = VarFP64::mul(zb, J);
     }
 }
 
+template <uint32_t N>
 hipError_t launch_batch_flat_inline(int kind, bool nt, uint32_t grid, uint32_t lds,
                                     hipStream_t s, const Mult* tabs, const Mult& M1,
-                                    const Mult& J, const BatchFlatInline& in) {
-    if (kind == 0) {
-        if (nt)
-            hipLaunchKernelGGL((k_batch_flat_inline<0, true>), dim3(grid), dim3(kFlatBlock), lds,
-                               s, tabs, M1, J, in);
-        else
-            hipLaunchKernelGGL((k_batch_flat_inline<0, false>), dim3(grid), dim3(kFlatBlock), lds,
-                               s, tabs, M1, J, in);
-    } else {
-        if (nt)
-            hipLaunchKernelGGL((k_batch_flat_inline<1, true>), dim3(grid), dim3(kFlatBlock), lds,
-                               s, tabs, M1, J, in);
-        else
-            hipLaunchKernelGGL((k_batch_flat_inline<1, false>), dim3(grid), dim3(kFlatBlock), lds,
-                               s, tabs, M1, J, in);
-    }
-    return hipGetLastError();
+                                    const Mult& J, const BatchFlatInline<N>& in) {
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kFlatBlock), lds, s, tabs, M1, J, in);
+        return hipGetLastError();
+    };
+    if (kind == 0)
+        return nt ? go(k_batch_flat_inline<0, true, N>) : go(k_batch_flat_inline<0, false, N>);
+    return nt ? go(k_batch_flat_inline<1, true, N>) : go(k_batch_flat_inline<1, false, N>);
 }
+template hipError_t launch_batch_flat_inline<kInlineDescs>(
+    int, bool, uint32_t, uint32_t, hipStream_t, const Mult*, const Mult&, const Mult&,
+    const BatchFlatInline<kInlineDescs>&);
+template hipError_t launch_batch_flat_inline<kFlatInlineDescs>(
+    int, bool, uint32_t, uint32_t, hipStream_t, const Mult*, const Mult&, const Mult&,
+    const BatchFlatInline<kFlatInlineDescs>&);
 
 // The device request queue (see nn_batch.hpp).  Thread 0 of a workgroup
 // waits for the next entry with acquire loads of the host's `head`, copies

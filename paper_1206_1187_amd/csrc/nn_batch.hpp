@@ -207,32 +207,37 @@ hipError_t launch_batch_inline(int mulmod, int kind, bool nontemporal, bool inde
                                uint32_t grid, uint32_t block, hipStream_t stream,
                                const BatchArgs& a, const BatchInline& in);
 
-// A small batch of the FP64 reduction in the kernel arguments, each window
-// written as the plain generator's flat layout writes an output: chunks of
-// kChunkRows rows of 512 outputs, one workgroup each, dispatched in order
-// (a window's chunks after the previous window's).  The host gives each
-// window's start state, so a workgroup's start is the plain flat kernel's.
-// Window element x has the state base * (2^53)^(x + s), s = out_off mod 2
-// (chunks are aligned to output pairs, so the 16-byte stores stay aligned).
+// A batch of few windows and the FP64 reduction in the kernel arguments, each
+// window written as the plain generator's flat layout writes an output:
+// chunks of kChunkRows rows of 512 outputs, one workgroup each, dispatched in
+// order (a window's chunks after the previous window's; whole XCD runs of
+// them as in the plain layout).  The host gives each window's start state, so
+// a workgroup's start is the plain flat kernel's.  A window's chunks are
+// aligned to the output's 128-byte lines: with s = out_off mod kInlineAlign
+// its element x has the state base * (2^53)^(x + s).
+constexpr uint32_t kInlineAlign = 16;
 struct FlatWin {
     uint64_t base;     // state of window element -s
     uint64_t len;      // outputs, > 0
     uint64_t out_off;  // output index of window element 0
-    uint32_t s;        // out_off & 1
-    uint32_t chunk0;   // the window's first chunk (workgroup index)
 };
+// N windows take 28 N bytes of the 4096 that kernel arguments may have.
+template <uint32_t N>
 struct BatchFlatInline {
     uint64_t* out;
     uint32_t n;
-    uint32_t pad;
-    FlatWin w[kInlineDescs];
+    uint32_t runs;       // the first chunks, in XCD runs (flat_run_chunks)
+    uint32_t chunk0[N];  // each window's first chunk (workgroup index)
+    FlatWin w[N];
 };
+constexpr uint32_t kFlatInlineDescs = 128;
 
 // grid = the windows' chunks in total; lds caps residency as for the
-// plain flat layout.
+// plain flat layout.  N is kInlineDescs or kFlatInlineDescs.
+template <uint32_t N>
 hipError_t launch_batch_flat_inline(int kind, bool nontemporal, uint32_t grid, uint32_t lds,
                                     hipStream_t stream, const Mult* tabs, const Mult& M1,
-                                    const Mult& J, const BatchFlatInline& in);
+                                    const Mult& J, const BatchFlatInline<N>& in);
 
 // ------------------------------------------- batches without allocation --
 // nn_generate_batch_static runs the chunked kernel with its workspace in one

@@ -620,6 +620,33 @@ int nn_generate_batch_static(const nn_stream_desc* descs, uint32_t n, void* out_
     const hipStream_t s = (hipStream_t)stream;
     uint32_t lds = (d->lds_per_cu / (kFlatDefaultOccupancy + 1) / 512 + 1) * 512;
     if (lds > d->lds_per_block) lds = kChunkMinLds;
+    // Few windows travel in the kernel arguments, without the workspace --
+    // unless the stream is being captured: a replay reads the descriptors anew.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
+    if (n <= kFlatInlineDescs && hipStreamIsCapturing(s, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        capture = hipStreamCaptureStatusActive;
+    }
+    if (capture == hipStreamCaptureStatusNone) {
+        BatchDesc dd[kFlatInlineDescs];
+        uint32_t nd = 0;
+        bool fits = true;
+        for (uint32_t i = 0; i < n; ++i) {
+            if (!descs[i].length) continue;
+            fits = fits && descs[i].length <= kFlatMaxCount - kInlineAlign;
+            dd[nd++] = BatchDesc{descs[i].state, 0, descs[i].length, descs[i].out_offset, 0};
+        }
+        if (fits) {
+            const hipError_t e =
+                launch_flat_inline(kind, true, lds, d->t_lo, nullptr, dd, nd, out_dev, s);
+            if (e != hipSuccess)
+                return fail(NN_EHIP, "static batch launch: %s", hipGetErrorString(e));
+            if (final_states)
+                for (uint32_t i = 0; i < n; ++i)
+                    final_states[i] = h_skip(descs[i].state, descs[i].length);
+            return ok();
+        }
+    }
     char* ws = static_cast<char*>(d->scratch);
     // the caller's descriptors, then the descriptors and header the kernels read
     hipError_t e = hipMemcpyAsync(ws + kStaticRawOff, descs, (size_t)n * sizeof(nn_stream_desc),

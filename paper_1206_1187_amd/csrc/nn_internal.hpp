@@ -80,7 +80,6 @@ struct nn_batch_plan {
     // small batches of the FP64 reduction (the flat inline kernel)
     const uint64_t* host_states = nullptr;  // indexed plans: host copy of the state table
     const nn::Mult* tabs = nullptr;         // the device tables
-    nn::Mult M1, J512;                      // 2^53 and (2^53)^512
     uint32_t occupancy = 0;                 // chunk kernel: resident workgroups per CU
     uint32_t flat_lds = 0;                  // its residency cap as dynamic LDS
     nn_batch_slot slot[2];
@@ -114,6 +113,12 @@ inline BatchDesc* plan_staged_descs(nn_batch_plan* p) {
 // `stream`, and records the plan's completion event.  The caller checked
 // nd <= p->cap_desc and holds p->mu.
 int plan_launch_staged(nn_batch_plan* p, uint32_t nd, void* out, hipStream_t stream);
+
+// Launches nd <= kFlatInlineDescs windows, none empty, in the kernel arguments
+// (BatchFlatInline): of the state src, or states[src] where `states` is given.
+hipError_t launch_flat_inline(int kind, bool nt, uint32_t lds, const Mult* tabs,
+                              const uint64_t* states, const BatchDesc* dd, uint32_t nd, void* out,
+                              hipStream_t stream);
 
 // Device request queue (host side in nn_queue.hip, kernel in nn_batch.hip).
 struct DeviceQueue;

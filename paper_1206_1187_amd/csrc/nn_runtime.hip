@@ -399,8 +399,6 @@ int plan_create(int kind, uint32_t max_streams, uint64_t max_outputs, const nn_b
     p->cap_desc = (uint32_t)cap_desc;
     p->host_states = host_states;
     p->tabs = d->t_lo;
-    p->M1 = make_mult(kMult);
-    p->J512 = make_mult(MultPowers::get().pow(kFlatPerBlock));
     // the chunk kernel's residency cap: dynamic LDS that leaves room for
     // `occupancy` workgroups per compute unit, not one more
     p->occupancy = c.occupancy ? c.occupancy
@@ -455,38 +453,83 @@ int batch_launched(nn_batch_plan* p, hipError_t e, hipStream_t stream) {
     return NN_OK;
 }
 
+// Whether the flat inline kernel takes the batch: the FP64 reduction, start
+// states at hand, and few enough windows.  Up to kInlineDescs windows every
+// plan does; above, up to kFlatInlineDescs, chunked plans without a fixed
+// grid: without the pre-pass, its record per chunk and a second launch 64
+// windows of up to 2^14 outputs take 20.2 us a call against 23.6, 100 of up to
+// 2^22 (27,000,000 outputs) 32 against 40.
+bool flat_inline(const nn_batch_plan* p, const BatchDesc* dd, uint32_t nd) {
+    if (p->mulmod != NN_MULMOD_FP64 || (p->indexed && !p->host_states)) return false;
+    const bool few = nd <= kInlineDescs;
+    if (!few && (nd > kFlatInlineDescs || !p->chunks || p->grid)) return false;
+    for (uint32_t k = 0; k < nd; ++k) {
+        // a window's chunks are counted in the flat layout's row tables
+        if (dd[k].len > kFlatMaxCount - kInlineAlign) return false;
+        if (!few && dd[k].out_off + dd[k].len > (1ull << 51)) return false;  // refused below
+    }
+    return true;
+}
+
 }  // namespace
+
+namespace {
+
+// The multipliers of every inline batch: 2^53, (2^53)^512 and (2^53)^-k.
+struct InlineMults {
+    Mult M1, J512;
+    uint64_t back[kInlineAlign];
+    InlineMults() : M1(make_mult(kMult)), J512(make_mult(MultPowers::get().pow(kFlatPerBlock))) {
+        for (uint32_t k = 0; k < kInlineAlign; ++k) back[k] = MultPowers::get().pow(kPeriod - k);
+    }
+};
+
+template <uint32_t N>
+hipError_t flat_inline_n(int kind, bool nt, uint32_t lds, const Mult* tabs,
+                         const uint64_t* states, const BatchDesc* dd, uint32_t nd, void* out,
+                         hipStream_t stream) {
+    static const InlineMults m;
+    BatchFlatInline<N> in;
+    in.out = (uint64_t*)out;
+    in.n = nd;
+    uint64_t chunks = 0;
+    for (uint32_t k = 0; k < nd; ++k) {
+        const BatchDesc& D = dd[k];
+        FlatWin& w = in.w[k];
+        const uint32_t s = (uint32_t)D.out_off & (kInlineAlign - 1);
+        const uint64_t src = states ? states[D.src] : D.src;
+        w.base = h_mulmod(h_skip(src, (D.pos % kPeriod) + 1), m.back[s]);  // element -s
+        w.len = D.len;
+        w.out_off = D.out_off;
+        in.chunk0[k] = (uint32_t)chunks;
+        chunks += (D.len + s + kChunkOuts - 1) / kChunkOuts;
+    }
+    in.runs = (uint32_t)flat_run_chunks(4, true, chunks);
+    return launch_batch_flat_inline(kind, nt, (uint32_t)chunks, lds, stream, tabs, m.M1, m.J512,
+                                    in);
+}
+
+}  // namespace
+
+hipError_t launch_flat_inline(int kind, bool nt, uint32_t lds, const Mult* tabs,
+                              const uint64_t* states, const BatchDesc* dd, uint32_t nd, void* out,
+                              hipStream_t stream) {
+    return nd <= kInlineDescs
+               ? flat_inline_n<kInlineDescs>(kind, nt, lds, tabs, states, dd, nd, out, stream)
+               : flat_inline_n<kFlatInlineDescs>(kind, nt, lds, tabs, states, dd, nd, out, stream);
+}
 
 int plan_launch_staged(nn_batch_plan* p, uint32_t nd, void* out, hipStream_t stream) {
     nn_batch_slot& q = p->slot[p->next];
     BatchHeader* hdr = (BatchHeader*)q.ws_host;
     BatchDesc* dd = plan_staged_descs(p);
     // A small batch travels in the kernel arguments (no upload to wait for).
-    if (nd <= kInlineDescs && p->mulmod == NN_MULMOD_FP64 && (!p->indexed || p->host_states)) {
-        // each window as the plain flat layout writes it, from a start state
-        // computed here (so no skip-ahead on the device)
-        BatchFlatInline in;
-        memset(&in, 0, sizeof in);
-        in.out = (uint64_t*)out;
-        in.n = nd;
-        uint64_t chunks = 0;
-        for (uint32_t k = 0; k < nd; ++k) {
-            const BatchDesc& D = dd[k];
-            FlatWin& w = in.w[k];
-            w.s = (uint32_t)(D.out_off & 1u);
-            const uint64_t src = p->indexed ? p->host_states[D.src] : D.src;
-            w.base = h_skip(src, (D.pos % kPeriod) + 1 - w.s);  // element -s
-            w.len = D.len;
-            w.out_off = D.out_off;
-            w.chunk0 = (uint32_t)chunks;
-            chunks += (D.len + w.s + kChunkOuts - 1) / kChunkOuts;
-        }
+    if (flat_inline(p, dd, nd))
         return batch_launched(p,
-                              launch_batch_flat_inline(p->kind, p->nontemporal, (uint32_t)chunks,
-                                                       p->flat_lds, stream, p->tabs, p->M1,
-                                                       p->J512, in),
+                              launch_flat_inline(p->kind, p->nontemporal, p->flat_lds, p->tabs,
+                                                 p->indexed ? p->host_states : nullptr, dd, nd,
+                                                 out, stream),
                               stream);
-    }
     // Another small batch runs the blocked kernel from its arguments, unless
     // the plan is chunked; larger ones of an interleaved plan run its pre-pass
     // and row kernel.

@@ -201,6 +201,45 @@ def test_chunked_batch_unsorted_windows(temporal):
         assert f == orc.skip(s, n)
 
 
+@pytest.mark.parametrize("kind", ["u64", "f64"])
+@pytest.mark.parametrize("n", [1, 16, 17, 63, 64, 65, 127, 128, 129])
+def test_few_windows_default_chunked_and_static(kind, n):
+    """Batches on both sides of the sizes that travel in the kernel arguments
+    (16 and 128 windows) and of a wavefront's share of the window search:
+    every residue of the output offset modulo the 16-output lines, empty
+    windows, windows over several chunks; given in order and shuffled; on a
+    plan without a kernel, on a chunked one and without a plan."""
+    rng = np.random.default_rng(n)
+    lengths = [int(x) for x in np.exp(rng.uniform(0.0, np.log(9000.0), n))]
+    lengths[n // 2] = 0 if n > 1 else 4099
+    states, lengths, offsets, total = _mixed_batch(n + 50, lengths)
+    perm = rng.permutation(n)
+    dt = torch.float64 if kind == "f64" else torch.uint64
+    for order in (np.arange(n), perm):
+        st, ln, of = states[order], lengths[order], offsets[order]
+        for kw in (dict(), dict(chunks=True), None):
+            buf = _sentinel(total)
+            if kw is None:
+                fin = nn.generate_batch_static(st, ln, of, buf.view(dt), final_states=True)
+            else:
+                with nn.BatchPlan(kind, 130, total, **kw) as plan:
+                    fin = plan.generate(st, ln, of, buf.view(dt), final_states=True)
+            torch.cuda.synchronize()
+            _check_batch(_bits(buf), st, ln, of, kind)
+            assert fin.tolist() == [orc.skip(int(s), int(k)) for s, k in zip(st, ln)]
+
+
+def test_inline_batch_xcd_runs():
+    """Twenty windows of more chunks than one XCD run (2048), with a rest."""
+    lengths = [2048 * 2000 + 7, 1, 2048 * 300, 5] + [2049] * 16
+    states, lengths, offsets, total = _mixed_batch(61, lengths)
+    buf = _sentinel(total)
+    with nn.BatchPlan("u64", 20, total) as plan:
+        plan.generate(states, lengths, offsets, buf.view(torch.uint64))
+        torch.cuda.synchronize()
+    _check_batch(_bits(buf), states, lengths, offsets, "u64")
+
+
 @pytest.mark.parametrize("longest", [2, 8, 700, 3000])
 @pytest.mark.parametrize("occupancy", [0, 16])
 def test_chunks_shared_by_few_and_many_windows(longest, occupancy):
