@@ -101,27 +101,38 @@ def _kind(kind):
     raise NNError(_native.NN_EINVAL, "unknown output kind %r" % (kind,))
 
 
-def _stream_handle(stream):
+def _on_device(device, stream, call):
+    """``call(handle)`` with ``device`` current, handle being ``stream``'s or
+    the device's current stream's.  The device is entered only where it is
+    not current, and the stream's handle taken without a Stream object: a
+    small call is host time, of which those were 4 of 8 us."""
     import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(int(stream.cuda_stream))
+    index = device.index
+    if index != torch.cuda.current_device():
+        with torch.cuda.device(device):
+            return call(_stream_handle(stream, index))
+    return call(_stream_handle(stream, index))
+
+
+def _stream_handle(stream, index):
+    import torch
+    if stream is not None:
+        return int(stream.cuda_stream)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw(index) if raw is not None else torch.cuda.current_stream(index).cuda_stream
 
 
 def generate_into(state, out, stream=None, cfg=None):
     """Fill the contiguous cuda tensor ``out`` (uint64 or float64) with the
     next ``out.numel()`` outputs after ``state``; returns the new state.
     Asynchronous on ``stream`` (default: torch's current stream)."""
-    import torch
     if not out.is_cuda or not out.is_contiguous():
         raise NNError(_native.NN_EINVAL, "out must be a contiguous cuda tensor")
     kind = _kind(out.dtype)
     st = ctypes.c_uint64(int(state))
-    with torch.cuda.device(out.device):
-        rc = _native.lib().nn_generate_ex(
-            ctypes.byref(st), out.numel(), ctypes.c_void_p(out.data_ptr()), kind,
-            _stream_handle(stream), ctypes.byref(cfg) if cfg is not None else None)
-    _native.check(rc)
+    _native.check(_on_device(out.device, stream, lambda handle: _native.lib().nn_generate_ex(
+        ctypes.byref(st), out.numel(), out.data_ptr(), kind, handle,
+        ctypes.byref(cfg) if cfg is not None else None)))
     return int(st.value)
 
 
@@ -137,7 +148,6 @@ def fill(out, value, stream=None, cfg=None, with_start=False):
     """The paper's "Constant" kernel: write ``value`` (a 64-bit pattern) with
     the generator's store pattern; ``with_start`` (flat layout) also makes
     the generator's start-up table loads (NN_FILL_WITH_START)."""
-    import torch
     if not out.is_cuda or not out.is_contiguous() or out.element_size() != 8:
         raise NNError(_native.NN_EINVAL, "out must be a contiguous 8-byte cuda tensor")
     if with_start:
@@ -146,11 +156,9 @@ def fill(out, value, stream=None, cfg=None, with_start=False):
             ctypes.pointer(c)[0] = cfg
         c.flags |= _native.NN_FILL_WITH_START
         cfg = c
-    with torch.cuda.device(out.device):
-        rc = _native.lib().nn_fill(out.numel(), ctypes.c_void_p(out.data_ptr()),
-                                   int(value) % 2 ** 64, _stream_handle(stream),
-                                   ctypes.byref(cfg) if cfg is not None else None)
-    _native.check(rc)
+    _native.check(_on_device(out.device, stream, lambda handle: _native.lib().nn_fill(
+        out.numel(), out.data_ptr(), int(value) % 2 ** 64, handle,
+        ctypes.byref(cfg) if cfg is not None else None)))
 
 
 def consume(state, count, kind="u64", result=None, stream=None, cfg=None):
@@ -164,11 +172,9 @@ def consume(state, count, kind="u64", result=None, stream=None, cfg=None):
         result = torch.zeros(1, dtype=torch.int64 if k == NN_OUT_U64 else torch.float64,
                              device="cuda")
     st = ctypes.c_uint64(int(state))
-    with torch.cuda.device(result.device):
-        rc = _native.lib().nn_consume(ctypes.byref(st), int(count), k,
-                                      ctypes.c_void_p(result.data_ptr()), _stream_handle(stream),
-                                      ctypes.byref(cfg) if cfg is not None else None)
-    _native.check(rc)
+    _native.check(_on_device(result.device, stream, lambda handle: _native.lib().nn_consume(
+        ctypes.byref(st), int(count), k, result.data_ptr(), handle,
+        ctypes.byref(cfg) if cfg is not None else None)))
     return result, int(st.value)
 
 
@@ -197,12 +203,9 @@ def e40_generate_into(state, out, stream=None, cfg=None):
     if not out.is_cuda or not out.is_contiguous():
         raise NNError(_native.NN_EINVAL, "out must be a contiguous cuda tensor")
     st = ctypes.c_uint64(int(state))
-    import torch
-    with torch.cuda.device(out.device):
-        rc = _native.lib().nn_e40_generate_ex(
-            ctypes.byref(st), out.numel(), ctypes.c_void_p(out.data_ptr()), kind,
-            _stream_handle(stream), ctypes.byref(cfg) if cfg is not None else None)
-    _native.check(rc)
+    _native.check(_on_device(out.device, stream, lambda handle: _native.lib().nn_e40_generate_ex(
+        ctypes.byref(st), out.numel(), out.data_ptr(), kind, handle,
+        ctypes.byref(cfg) if cfg is not None else None)))
     return st.value
 
 
@@ -282,17 +285,14 @@ def generate_batch_static(states, lengths, out_offsets, out, stream=None, final_
     descs = _batch_descs(states, lengths, out_offsets, out)
     n = len(descs)
     fin = np.empty(n, dtype=np.uint64) if final_states else None
-    p64 = ctypes.POINTER(ctypes.c_uint64)
-    with torch.cuda.device(out.device):
-        handle = _stream_handle(stream)
-        rc = _native.lib().nn_generate_batch_static(
-            ctypes.c_void_p(descs.ctypes.data), n, ctypes.c_void_p(out.data_ptr()), kind,
-            handle, fin.ctypes.data_as(p64) if fin is not None else None)
-        _native.check(rc)
-        if n:
-            # the host array must outlive the asynchronous copy that reads it
-            s = torch.cuda.current_stream() if stream is None else stream
-            s.synchronize()
+    _native.check(_on_device(
+        out.device, stream, lambda handle: _native.lib().nn_generate_batch_static(
+            descs.ctypes.data, n, out.data_ptr(), kind, handle,
+            fin.ctypes.data if fin is not None else None)))
+    if n:
+        # the host array must outlive the asynchronous copy that reads it
+        s = torch.cuda.current_stream(out.device) if stream is None else stream
+        s.synchronize()
     return fin
 
 
@@ -342,21 +342,12 @@ class BatchPlan:
         want = torch.uint64 if self.kind == NN_OUT_U64 else torch.float64
         if not out.is_cuda or not out.is_contiguous() or out.dtype != want:
             raise NNError(_native.NN_EINVAL, "out must be a contiguous cuda %s tensor" % want)
-        n = len(states)
-        descs = np.empty(n, dtype=_DESC_DTYPE)
-        descs["state"] = np.asarray(states, dtype=np.uint64)
-        descs["length"] = np.asarray(lengths, dtype=np.uint64)
-        descs["out_offset"] = np.asarray(out_offsets, dtype=np.uint64)
-        ends = descs["out_offset"] + descs["length"]
-        if n and int(ends.max()) > out.numel():
-            raise NNError(_native.NN_ERANGE, "a window ends past the output tensor")
+        descs = _batch_descs(states, lengths, out_offsets, out)
+        n = len(descs)
         fin = np.empty(n, dtype=np.uint64) if final_states else None
-        p64 = ctypes.POINTER(ctypes.c_uint64)
-        with torch.cuda.device(out.device):
-            rc = _native.lib().nn_generate_batch(
-                self._h, ctypes.c_void_p(descs.ctypes.data), n, ctypes.c_void_p(out.data_ptr()),
-                _stream_handle(stream), fin.ctypes.data_as(p64) if fin is not None else None)
-        _native.check(rc)
+        _native.check(_on_device(out.device, stream, lambda handle: _native.lib().nn_generate_batch(
+            self._h, descs.ctypes.data, n, out.data_ptr(), handle,
+            fin.ctypes.data if fin is not None else None)))
         return fin
 
     def close(self):

@@ -357,9 +357,11 @@ int nn_generate_ex(uint64_t* state, uint64_t count, void* out_dev, int kind, voi
         return ok();
     }
     if (r.flat) {
+        static const Mult M1 = make_mult(kMult);
+        static const Mult J = make_mult(MultPowers::get().pow(kFlatPerBlock));
         FlatArgs f;
-        f.M1 = make_mult(kMult);
-        f.J = make_mult(MultPowers::get().pow(kFlatPerBlock));
+        f.M1 = M1;
+        f.J = J;
         f.head_state = h_skip(s, 1);
         hipError_t e = hipSuccess;
         for (uint64_t off = 0; off < count && e == hipSuccess;) {
@@ -555,10 +557,32 @@ int nn_generate_batch(nn_batch_plan* plan, const nn_stream_desc* descs, uint32_t
             for (uint32_t i = 0; i < n; ++i) final_states[i] = descs[i].state;
         return ok();
     }
-    int st = plan_wait(plan);
+    int st = NN_OK;
+    uint32_t nd = 0;
+    // Few windows go to the flat inline kernel, which needs no slot: neither
+    // the wait for one nor the event that gives it back (4 of 7 us of a small
+    // call).
+    BatchDesc few[kFlatInlineDescs];
+    if (pieces <= kFlatInlineDescs) {
+        for (uint32_t i = 0; i < n; ++i)
+            if (descs[i].length && nd < kFlatInlineDescs)
+                few[nd++] = BatchDesc{descs[i].state, 0, descs[i].length, descs[i].out_offset, 0};
+        if (flat_inline(plan, few, nd)) {
+            const hipError_t e =
+                launch_flat_inline(plan->kind, plan->nontemporal, plan->flat_lds, plan->tabs,
+                                   nullptr, few, nd, out_dev, (hipStream_t)stream);
+            if (e != hipSuccess) return fail(NN_EHIP, "batch launch: %s", hipGetErrorString(e));
+            plan->unslotted = true;
+            if (final_states)
+                for (uint32_t i = 0; i < n; ++i)
+                    final_states[i] = h_skip(descs[i].state, descs[i].length);
+            return ok();
+        }
+        nd = 0;
+    }
+    st = plan_wait(plan);
     if (st) return st;
     BatchDesc* dd = plan_staged_descs(plan);
-    uint32_t nd = 0;
     for (uint32_t i = 0; i < n; ++i) {
         const nn_stream_desc& q = descs[i];
         for (uint64_t off = 0; off < q.length; off += kBatchMaxLen) {

@@ -82,8 +82,11 @@ struct nn_batch_plan {
     const nn::Mult* tabs = nullptr;         // the device tables
     uint32_t occupancy = 0;                 // chunk kernel: resident workgroups per CU
     uint32_t flat_lds = 0;                  // its residency cap as dynamic LDS
+    nn::RowRec* chunk_mem = nullptr;  // device, chunked: both slots' rec and ext
+    char* pinned = nullptr;           // both slots' staging
     nn_batch_slot slot[2];
     int next = 0;  // the slot of the next batch
+    bool unslotted = false;  // a batch ran without a slot (and its event)
 };
 
 namespace nn {
@@ -114,6 +117,8 @@ inline BatchDesc* plan_staged_descs(nn_batch_plan* p) {
 // nd <= p->cap_desc and holds p->mu.
 int plan_launch_staged(nn_batch_plan* p, uint32_t nd, void* out, hipStream_t stream);
 
+// Whether the flat inline kernel takes the windows dd[0..nd).
+bool flat_inline(const nn_batch_plan* p, const BatchDesc* dd, uint32_t nd);
 // Launches nd <= kFlatInlineDescs windows, none empty, in the kernel arguments
 // (BatchFlatInline): of the state src, or states[src] where `states` is given.
 hipError_t launch_flat_inline(int kind, bool nt, uint32_t lds, const Mult* tabs,

@@ -221,6 +221,7 @@ int current_device(DeviceTables** out) {
 // ---------------------------------------------------------------- plans --
 
 void plan_release(nn_batch_plan* p) {
+    if (p->unslotted) (void)hipDeviceSynchronize();
     for (nn_batch_slot& q : p->slot) {
         if (q.done) {
             (void)hipEventSynchronize(q.done);
@@ -229,10 +230,10 @@ void plan_release(nn_batch_plan* p) {
         if (q.exec) (void)hipGraphExecDestroy(q.exec);
         if (q.graph) (void)hipGraphDestroy(q.graph);
         if (q.ws_dev) (void)hipFree(q.ws_dev);
-        if (q.rec) (void)hipFree(q.rec);
-        if (q.ext) (void)hipFree(q.ext);
-        if (q.ws_host) (void)hipHostFree(q.ws_host);
+        if (q.rec && !p->chunks) (void)hipFree(q.rec);
     }
+    if (p->chunk_mem) (void)hipFree(p->chunk_mem);
+    if (p->pinned) (void)hipHostFree(p->pinned);
     delete p;
 }
 
@@ -242,17 +243,27 @@ namespace {
 int slot_create(nn_batch_plan* p, nn_batch_slot& q, const DeviceTables& d,
                 const uint64_t* states) {
     q.ws_bytes = sizeof(BatchHeader) + (size_t)p->cap_desc * sizeof(BatchDesc);
-    // the chunked kernel's pre-pass reads the pinned staging itself
-    hipError_t e = p->chunks ? hipSuccess : hipMalloc(&q.ws_dev, q.ws_bytes);
-    if (e == hipSuccess && (p->interleaved || p->chunks))  // grid * per <= rows + clusters + grid
-        e = hipMalloc((void**)&q.rec, (p->cap_rows + 2ull * p->grid) * sizeof(RowRec));
-    if (e == hipSuccess && p->chunks)
-        e = hipMalloc((void**)&q.ext, (size_t)p->cap_desc * sizeof(RowRec));
+    const size_t i = &q - p->slot;
+    hipError_t e = hipSuccess;
+    if (p->chunks) {
+        // the pre-pass reads the pinned staging itself; both slots' records
+        // are one allocation
+        const size_t recs = p->cap_rows + 2ull * p->grid, both = recs + p->cap_desc;
+        if (!p->chunk_mem) e = hipMalloc((void**)&p->chunk_mem, 2 * both * sizeof(RowRec));
+        q.rec = p->chunk_mem + i * both;
+        q.ext = q.rec + recs;
+    } else {
+        e = hipMalloc(&q.ws_dev, q.ws_bytes);
+        if (e == hipSuccess && p->interleaved)  // grid * per <= rows + clusters + grid
+            e = hipMalloc((void**)&q.rec, (p->cap_rows + 2ull * p->grid) * sizeof(RowRec));
+    }
     if (e != hipSuccess)
         return fail(NN_ENOMEM, "batch workspace (%zu bytes): %s", q.ws_bytes, hipGetErrorString(e));
-    e = hipHostMalloc(&q.ws_host, q.ws_bytes, hipHostMallocDefault);
+    const size_t pitch = (q.ws_bytes + 255) & ~(size_t)255;
+    if (!p->pinned) e = hipHostMalloc((void**)&p->pinned, 2 * pitch, hipHostMallocDefault);
     if (e != hipSuccess)
         return fail(NN_ENOMEM, "pinned staging (%zu bytes): %s", q.ws_bytes, hipGetErrorString(e));
+    q.ws_host = p->pinned + i * pitch;
     BatchHeader* hdr = (BatchHeader*)q.ws_host;
     memset(hdr, 0, sizeof *hdr);
     hdr->states = states;
@@ -453,6 +464,8 @@ int batch_launched(nn_batch_plan* p, hipError_t e, hipStream_t stream) {
     return NN_OK;
 }
 
+}  // namespace
+
 // Whether the flat inline kernel takes the batch: the FP64 reduction, start
 // states at hand, and few enough windows.  Up to kInlineDescs windows every
 // plan does; above, up to kFlatInlineDescs, chunked plans without a fixed
@@ -470,8 +483,6 @@ bool flat_inline(const nn_batch_plan* p, const BatchDesc* dd, uint32_t nd) {
     }
     return true;
 }
-
-}  // namespace
 
 namespace {
 
@@ -537,13 +548,18 @@ int plan_launch_staged(nn_batch_plan* p, uint32_t nd, void* out, hipStream_t str
     const bool il = (p->interleaved || p->chunks) && !in_args;
     const uint64_t row = p->chunks ? (uint64_t)kChunkOuts
                                    : (il ? 2ull * kIlPairs : 2ull) * p->block;
+    // (rows are counted with shifts: a 64-bit division each is most of a
+    // window's host time)
+    const uint32_t shift = (uint32_t)__builtin_ctzll(row);
+    const bool pow2 = (row & (row - 1)) == 0;
     uint64_t rows = 0;
     for (uint32_t k = 0; k < nd; ++k) {
         dd[k].row_start = rows;
         // rows aligned to output pairs (blocked kernel) or to whole rows
         // of the output (interleaved kernel; chunks for the chunked one)
         const uint64_t s = dd[k].out_off & (il ? row - 1 : 1u);
-        rows += (dd[k].len + s + row - 1) / row;
+        const uint64_t up = dd[k].len + s + row - 1;
+        rows += pow2 ? up >> shift : up / row;
         // row records hold output indices in 52 bits
         if (il && dd[k].out_off + dd[k].len > (1ull << 51))
             return fail(NN_ERANGE, "interleaved and chunked batches take output indices below "
@@ -582,7 +598,7 @@ int plan_launch_staged(nn_batch_plan* p, uint32_t nd, void* out, hipStream_t str
                 D.row_start = 0;
                 continue;
             }
-            const uint64_t first = D.out_off / row, last = (D.out_off + D.len - 1) / row;
+            const uint64_t first = D.out_off >> shift, last = (D.out_off + D.len - 1) >> shift;
             const bool shared = prev >= 0 && prev_last == first;
             const uint64_t k0 = shared ? K - 1 : K;
             K = k0 + (last - first + 1);

@@ -52,7 +52,7 @@ class Server:
         if not self.fake:
             import torch
             self.pool = torch.empty(self.pool_bytes // 8, dtype=torch.int64, device="cuda")
-            pool_ptr = self.pool.data_ptr()
+            pool_ptr = self._pool_ptr = self.pool.data_ptr()
         flags = (NN_SERVER_FAKE_DEVICE if self.fake else 0) | \
             (_native.NN_SERVER_DEVICE_QUEUE if device_queue else 0)
         cfg = ServerCfg(pool_ptr, self.pool_bytes, int(max_batch_outputs),
@@ -65,26 +65,32 @@ class Server:
                                                ctypes.byref(h)))
         self._h = h
         self._buf = (Completion * 4096)()
+        lib = _lib()  # the per-request calls, looked up once
+        self._submit, self._poll = lib.nn_server_submit, lib.nn_server_poll
+        self._release = lib.nn_server_release
 
     def submit(self, stream_id, count):
         t = ctypes.c_uint64()
-        _native.check(_lib().nn_server_submit(self._h, int(stream_id), int(count),
-                                              ctypes.byref(t)))
-        return int(t.value)
+        rc = self._submit(self._h, int(stream_id), int(count), ctypes.byref(t))
+        if rc:
+            _native.check(rc)
+        return t.value
 
     def poll(self):
         """Progress, then the finished requests (list of Completion copies)."""
         out = []
         n = ctypes.c_uint32()
         while True:
-            _native.check(_lib().nn_server_poll(self._h, self._buf, len(self._buf),
-                                                ctypes.byref(n)))
-            out.extend(Completion.from_buffer_copy(self._buf[i]) for i in range(n.value))
+            _native.check(self._poll(self._h, self._buf, len(self._buf), ctypes.byref(n)))
+            if n.value:  # one copy of the lot, its elements the completions
+                out.extend((Completion * n.value).from_buffer_copy(self._buf))
             if n.value < len(self._buf):
                 return out
 
     def release(self, ticket):
-        _native.check(_lib().nn_server_release(self._h, int(ticket)))
+        rc = self._release(self._h, int(ticket))
+        if rc:
+            _native.check(rc)
 
     def cancel(self, ticket):
         _native.check(_lib().nn_server_cancel(self._h, int(ticket)))
@@ -103,12 +109,13 @@ class Server:
     def data(self, c):
         """The outputs of a completion: a torch view into the pool (GPU) or a
         numpy copy (fake device), as uint64 bit patterns."""
-        if c.count == 0 or not c.data:
+        data, count = c.data, c.count
+        if count == 0 or not data:
             return np.empty(0, dtype=np.uint64)
         if self.fake:
-            return np.frombuffer(ctypes.string_at(c.data, 8 * c.count), dtype=np.uint64).copy()
-        off = (c.data - self.pool.data_ptr()) // 8
-        return self.pool[off:off + c.count]
+            return np.frombuffer(ctypes.string_at(data, 8 * count), dtype=np.uint64).copy()
+        off = (data - self._pool_ptr) // 8
+        return self.pool[off:off + count]
 
     def close(self):
         if getattr(self, "_h", None) is not None:
