@@ -317,8 +317,10 @@ typedef struct nn_batch_cfg {
 /* Opaque batch plan, owned by the library until nn_batch_plan_destroy: pinned
  * staging for the descriptors and, for the blocked and interleaved kernels, a
  * device copy of it and a hipGraph of the kernels.  A chunked plan has
- * device memory for its records; its pre-pass reads the staging, and its two
- * kernels are launched directly. */
+ * device memory for its records and, if it holds batches of 2^28 outputs, a
+ * stream (non-blocking, default priority) on which their record pre-pass runs
+ * beside the previous batch's kernel; its pre-pass reads the staging, and its
+ * two kernels are launched directly. */
 typedef struct nn_batch_plan nn_batch_plan;
 
 /* nn_batch_plan_create -- a plan on the current device for batches of at

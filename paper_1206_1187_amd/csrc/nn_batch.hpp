@@ -178,6 +178,12 @@ inline bool chunks_dense(uint64_t chunks, uint64_t windows) {
 // Residency of a plan that names no kernel (non-temporal stores): 3 workgroups
 // per CU write the 10,000-window batch at 6.72 TB/s, 4 at 6.62.
 constexpr uint32_t kChunkImpliedOccupancy = 3;
+// Chunks from which a batch's pre-pass goes to the plan's side stream, beside
+// the previous batch's chunk kernel: back to back 10,000 windows of 1,320,000
+// chunks take 3035 against 3043 us, 9999 of 364,000 870 against 878-903.  A batch
+// on its own pays about 10 us for the two events (5000 windows of 97,000 chunks
+// 307 against 296 us, back to back 252 and 256).
+constexpr uint64_t kOverlapChunks = 1ull << 17;
 // The pre-pass gives a window a workgroup where the windows are long and too
 // few to fill the device with wavefronts (300 windows of 150 chunks on average
 // 98 against 107 us a batch; 9999 of 37 883 against 871).

@@ -57,6 +57,7 @@ struct nn_batch_slot {
     nn::RowRec* rec = nullptr;    // device, cap_rows + 2 grid records (interleaved, chunked)
     nn::RowRec* ext = nullptr;    // device, cap_desc first-chunk records (chunked)
     hipEvent_t done = nullptr;
+    hipEvent_t ready = nullptr;   // plans with a side stream: this slot's pre-pass done
     bool pending = false;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -71,6 +72,12 @@ struct nn_batch_plan {
     bool indexed = false;
     uint32_t mulmod = 0, block = 0, grid = 0, cluster = 1;
     bool nontemporal = true, use_graph = true, interleaved = false, chunks = false;
+    // Chunked plans of nn_generate_batch for long batches: their record
+    // pre-pass runs on `side`, so it overlaps the previous batch's chunk
+    // kernel; the caller's stream waits for it (event `ready` of the slot) and
+    // runs the chunk kernel.  It touches only the slot's own memory, which the
+    // host has seen free (plan_wait) before reuse.
+    hipStream_t side = nullptr;
     nn::Mult JR64, JR256;  // chunked: a pre-pass thread's step (BatchArgs::JR)
     uint64_t cap_rows = 0;
     uint32_t map_grid = 0;

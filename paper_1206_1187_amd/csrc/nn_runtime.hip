@@ -222,16 +222,19 @@ int current_device(DeviceTables** out) {
 
 void plan_release(nn_batch_plan* p) {
     if (p->unslotted) (void)hipDeviceSynchronize();
+    if (p->side) (void)hipStreamSynchronize(p->side);
     for (nn_batch_slot& q : p->slot) {
         if (q.done) {
             (void)hipEventSynchronize(q.done);
             (void)hipEventDestroy(q.done);
         }
+        if (q.ready) (void)hipEventDestroy(q.ready);
         if (q.exec) (void)hipGraphExecDestroy(q.exec);
         if (q.graph) (void)hipGraphDestroy(q.graph);
         if (q.ws_dev) (void)hipFree(q.ws_dev);
         if (q.rec && !p->chunks) (void)hipFree(q.rec);
     }
+    if (p->side) (void)hipStreamDestroy(p->side);
     if (p->chunk_mem) (void)hipFree(p->chunk_mem);
     if (p->pinned) (void)hipHostFree(p->pinned);
     delete p;
@@ -268,6 +271,7 @@ int slot_create(nn_batch_plan* p, nn_batch_slot& q, const DeviceTables& d,
     memset(hdr, 0, sizeof *hdr);
     hdr->states = states;
     e = hipEventCreateWithFlags(&q.done, hipEventDisableTiming);
+    if (e == hipSuccess && p->side) e = hipEventCreateWithFlags(&q.ready, hipEventDisableTiming);
     if (e != hipSuccess) return fail(NN_EHIP, "event: %s", hipGetErrorString(e));
     const uint32_t block = p->block, cluster = p->cluster;
     void* ws = q.ws_dev;
@@ -416,6 +420,14 @@ int plan_create(int kind, uint32_t max_streams, uint64_t max_outputs, const nn_b
                    : implied && p->nontemporal ? kChunkImpliedOccupancy : kFlatDefaultOccupancy;
     p->flat_lds = (d->lds_per_cu / (p->occupancy + 1) / 512 + 1) * 512;
     if (p->flat_lds > d->lds_per_block) p->flat_lds = kChunkMinLds;
+    if (chunks && !indexed && max_outputs / kChunkOuts >= kOverlapChunks) {
+        // default priority; non-blocking, so it does not wait for the null stream
+        hipError_t e = hipStreamCreateWithFlags(&p->side, hipStreamNonBlocking);
+        if (e != hipSuccess) {
+            plan_release(p);
+            return fail(NN_EHIP, "batch side stream: %s", hipGetErrorString(e));
+        }
+    }
     p->JR64 = make_mult(MultPowers::get().pow((uint64_t)kChunkOuts * 64));
     p->JR256 = make_mult(MultPowers::get().pow((uint64_t)kChunkOuts * 256));
     for (nn_batch_slot& q : p->slot) {
@@ -632,9 +644,13 @@ int plan_launch_staged(nn_batch_plan* p, uint32_t nd, void* out, hipStream_t str
     void* params[] = {&q.args};
     if (p->chunks) {
         const bool wide = rec_wide(rows, nd);
+        const bool side = p->side && rows >= kOverlapChunks;
         q.args.JR = wide ? p->JR256 : p->JR64;
         e = hipLaunchKernel(batch_rec_kernel(p->indexed, !wide),
-                            dim3(wide ? rec_grid : (nd + 3) / 4), dim3(256), params, 0, stream);
+                            dim3(wide ? rec_grid : (nd + 3) / 4), dim3(256), params, 0,
+                            side ? p->side : stream);
+        if (e == hipSuccess && side) e = hipEventRecord(q.ready, p->side);
+        if (e == hipSuccess && side) e = hipStreamWaitEvent(stream, q.ready, 0);
         // one workgroup per record unless the plan fixed a grid
         if (e == hipSuccess)
             e = hipLaunchKernel(batch_chunks_kernel(p->kind, p->nontemporal,
