@@ -201,6 +201,12 @@ int nn_default_cfg(int kind, uint64_t count, nn_launch_cfg *cfg_out);
  * only (NULL for the defaults).  Asynchronous on `stream`. */
 int nn_consume(uint64_t *state, uint64_t count, int kind, void *result_dev, void *stream,
                const nn_launch_cfg *cfg);
+/* nn_consume_set -- nn_consume into a value the caller need not initialise:
+ * *result_dev is set to the sum (0 for a count of 0).  Up to 2^15 outputs are
+ * one launch of one workgroup; longer calls clear the value in a launch of
+ * their own first. */
+int nn_consume_set(uint64_t *state, uint64_t count, int kind, void *result_dev, void *stream,
+                   const nn_launch_cfg *cfg);
 
 /* ------------------------------------------------ device-side generation --
  * For consumer kernels that make variates where they use them (nn_device.h,

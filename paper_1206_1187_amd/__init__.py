@@ -164,15 +164,17 @@ def fill(out, value, stream=None, cfg=None, with_start=False):
 def consume(state, count, kind="u64", result=None, stream=None, cfg=None):
     """The fused consumer: add the sum of the next ``count`` outputs (raw
     states modulo 2^64 for "u64", variates for "f64") to the one-element
-    cuda tensor ``result`` (allocated and zeroed when None).  Returns
+    cuda tensor ``result`` (a new one is set to the sum when None).  Returns
     (result, new_state)."""
     import torch
     k = _kind(kind)
+    fn = _native.lib().nn_consume
     if result is None:
-        result = torch.zeros(1, dtype=torch.int64 if k == NN_OUT_U64 else torch.float64,
+        result = torch.empty(1, dtype=torch.int64 if k == NN_OUT_U64 else torch.float64,
                              device="cuda")
+        fn = _native.lib().nn_consume_set
     st = ctypes.c_uint64(int(state))
-    _native.check(_on_device(result.device, stream, lambda handle: _native.lib().nn_consume(
+    _native.check(_on_device(result.device, stream, lambda handle: fn(
         ctypes.byref(st), int(count), k, result.data_ptr(), handle,
         ctypes.byref(cfg) if cfg is not None else None)))
     return result, int(st.value)

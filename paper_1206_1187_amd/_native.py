@@ -157,6 +157,7 @@ SIGNATURES = {
     "nn_default_cfg": (_int, [_int, _u64, ctypes.POINTER(LaunchCfg)]),
     "nn_fill": (_int, [_u64, _vp, _u64, _vp, ctypes.POINTER(LaunchCfg)]),
     "nn_consume": (_int, [_pu64, _u64, _int, _vp, _vp, ctypes.POINTER(LaunchCfg)]),
+    "nn_consume_set": (_int, [_pu64, _u64, _int, _vp, _vp, ctypes.POINTER(LaunchCfg)]),
     "nn_dev_mult_pow": (_int, [_u64, ctypes.POINTER(DevMult)]),
     "nn_e40_seed": (_int, [_u64, _pu64]),
     "nn_e40_skip": (_int, [_u64, _u64, _pu64]),

@@ -401,16 +401,25 @@ int nn_generate(uint64_t* state, uint64_t count, void* out_dev, int kind, void* 
     return nn_generate_ex(state, count, out_dev, kind, stream, nullptr);
 }
 
-int nn_consume(uint64_t* state, uint64_t count, int kind, void* result_dev, void* stream,
-               const nn_launch_cfg* cfg) {
+}  // extern "C"
+
+namespace {
+
+// nn_consume, or with `set` nn_consume_set.
+int consume(uint64_t* state, uint64_t count, int kind, void* result_dev, void* stream,
+            const nn_launch_cfg* cfg, bool set) {
     if (!state) return fail(NN_EINVAL, "state is NULL");
     if (kind != NN_OUT_U64 && kind != NN_OUT_F64) return fail(NN_EINVAL, "kind %d unknown", kind);
     const uint64_t s = *state;
     if (!valid_state(s))
         return fail(NN_EINVAL, "state %llu is not a unit modulo 3^33", (unsigned long long)s);
-    if (count == 0) return ok();
+    if (count == 0 && !set) return ok();
     if (!result_dev || (uintptr_t)result_dev % 8)
         return fail(NN_EINVAL, "result pointer %p must be non-NULL and 8-byte aligned", result_dev);
+    if (count == 0) {
+        const hipError_t e = launch_clear(result_dev, (hipStream_t)stream);
+        return e == hipSuccess ? ok() : fail(NN_EHIP, "consume launch: %s", hipGetErrorString(e));
+    }
     DeviceTables* d = nullptr;
     int st = current_device(&d);
     if (st) return st;
@@ -427,7 +436,9 @@ int nn_consume(uint64_t* state, uint64_t count, int kind, void* result_dev, void
         return fail(NN_EINVAL, "mulmod %u: nn_consume takes FP64, Barrett, Shoup or Montgomery",
                     mulmod);
     uint32_t grid = c.grid;
-    if (!grid) {
+    if (!grid && set && count <= kConsumeSetOne) {
+        grid = 1;
+    } else if (!grid) {
         const uint64_t need = (count - 1) / (kConsumeMinRows * block) + 1;
         const uint64_t cap = (uint64_t)(d->cus > 0 ? d->cus : 1) * kConsumeBlock / block *
                              (count >= kConsumeTwoPerCu ? 2 : 1);
@@ -435,22 +446,43 @@ int nn_consume(uint64_t* state, uint64_t count, int kind, void* result_dev, void
     }
     if ((uint64_t)grid * block > kMaxThreads)
         return fail(NN_EINVAL, "grid*block exceeds %llu threads", (unsigned long long)kMaxThreads);
+    hipError_t e = hipSuccess;
+    if (set && grid > 1) e = launch_clear(result_dev, (hipStream_t)stream);
     ConsumeArgs a;
+    a.set = set && grid == 1;
     a.T = (uint64_t)grid * block;
     a.e_full = count / a.T;
     a.rem = (uint32_t)(count % a.T);
     a.base = h_mulmod(s, kMult);
     uint64_t jump = MultPowers::get().pow(a.T);
     for (int k = 0; k < 3; ++k, jump = h_mulmod(jump, jump)) {
-        a.J[k] = make_mult(jump);
-        a.B[k] = make_bal(jump);
+        // the FP64 reduction's form or the others'
+        if (mulmod == NN_MULMOD_FP64)
+            a.B[k] = make_bal(jump);
+        else
+            a.J[k] = make_mult(jump);
     }
     a.t_lo = d->t_lo;
     a.t_hi = d->t_hi;
-    hipError_t e = launch_consume((int)mulmod, kind, grid, block, (hipStream_t)stream, a, result_dev);
+    if (e == hipSuccess)
+        e = launch_consume((int)mulmod, kind, grid, block, (hipStream_t)stream, a, result_dev);
     if (e != hipSuccess) return fail(NN_EHIP, "consume launch: %s", hipGetErrorString(e));
     *state = h_skip(s, count);
     return ok();
+}
+
+}  // namespace
+
+extern "C" {
+
+int nn_consume(uint64_t* state, uint64_t count, int kind, void* result_dev, void* stream,
+               const nn_launch_cfg* cfg) {
+    return consume(state, count, kind, result_dev, stream, cfg, false);
+}
+
+int nn_consume_set(uint64_t* state, uint64_t count, int kind, void* result_dev, void* stream,
+                   const nn_launch_cfg* cfg) {
+    return consume(state, count, kind, result_dev, stream, cfg, true);
 }
 
 int nn_fill(uint64_t count, void* out_dev, uint64_t value, void* stream, const nn_launch_cfg* cfg) {

@@ -161,6 +161,26 @@ __device__ __forceinline__ X block_sum(X v) {
     return v;
 }
 
+// A workgroup's sum to *result: set where it is the only one of a call that
+// sets the result, else added.
+template <class X>
+__device__ __forceinline__ void give(X* result, X sum, bool set) {
+    if (threadIdx.x) return;
+    if (set)
+        *result = sum;
+    else
+        atomicAdd(result, sum);
+}
+
+// Clears the result of a call that sets it with several workgroups (both kinds'
+// zero is the same 64 bits).
+__global__ void k_clear(uint64_t* result) { *result = 0; }
+
+hipError_t launch_clear(void* result, hipStream_t s) {
+    k_clear<<<1, 1, 0, s>>>(static_cast<uint64_t*>(result));
+    return hipGetLastError();
+}
+
 // The integer reductions, four rows in flight per thread.
 template <class V, int KIND>
 __global__ __launch_bounds__(1024) void k_consume(ConsumeArgs a, void* result) {
@@ -191,11 +211,9 @@ __global__ __launch_bounds__(1024) void k_consume(ConsumeArgs a, void* result) {
     for (uint32_t c = 0; c < 4; ++c)
         if (c < left || (c == left && t < a.rem)) take(z[c]);
     if constexpr (KIND == 0) {
-        su = block_sum(su);
-        if (threadIdx.x == 0) atomicAdd(static_cast<unsigned long long*>(result), su);
+        give(static_cast<unsigned long long*>(result), block_sum(su), a.set);
     } else {
-        sf = block_sum(sf);
-        if (threadIdx.x == 0) atomicAdd(static_cast<double*>(result), sf);
+        give(static_cast<double*>(result), block_sum(sf), a.set);
     }
 }
 
@@ -278,14 +296,12 @@ __global__ __launch_bounds__(1024) void k_consume_bal(ConsumeArgs a, void* resul
     }
     negative = (threadIdx.x & 63) == 0 ? negative + neg : 0;  // the wavefront's count, once
     if constexpr (KIND == 0) {
-        su = block_sum(su + negative * kMod);
-        if (threadIdx.x == 0) atomicAdd(static_cast<unsigned long long*>(result), su);
+        give(static_cast<unsigned long long*>(result), block_sum(su + negative * kMod), a.set);
     } else {
         negative = block_sum(negative);
         const double s = block_sum((sf[0] + sf[1]) + (sf[2] + sf[3]));
-        if (threadIdx.x == 0)
-            atomicAdd(static_cast<double*>(result),
-                      __builtin_fma((double)negative, kModD, s) * kRecip);
+        give(static_cast<double*>(result), __builtin_fma((double)negative, kModD, s) * kRecip,
+             a.set);
     }
 }
 

@@ -259,10 +259,10 @@ def test_chunks_shared_by_few_and_many_windows(longest, occupancy):
 
 
 def test_chunked_batch_long_windows_back_to_back():
-    """130 windows of 600 chunks each: a workgroup per window in the pre-pass,
-    and over 2^16 chunks in all, so the chunk kernel for long batches; two
+    """130 windows of 1100 chunks each: a workgroup per window in the pre-pass,
+    and over 2^17 chunks in all, so the pre-pass takes the side stream; two
     batches back to back, then a short one; sampled against the oracle."""
-    n, size = 130, 600 * 2048 + 3
+    n, size = 130, 1100 * 2048 + 3
     states = np.array([orc.seed(wl.INDEX_MIN + 97 * i) for i in range(n)], dtype=np.uint64)
     lengths = np.full(n, size, dtype=np.uint64)
     offsets = np.arange(n, dtype=np.uint64) * size

@@ -495,6 +495,36 @@ def test_fused_consumer_state_sum_exact(mulmod):
         assert abs(float(resf.cpu()[0]) - exact) <= bound, (count, float(resf.cpu()[0]), exact)
 
 
+@pytest.mark.parametrize("mulmod", ["fp64", "shoup"])
+@pytest.mark.parametrize("count", [0, 1, 1023, 1025, (1 << 15) - 1, 1 << 15, (1 << 15) + 1, 300_001])
+def test_fused_consumer_sets_a_new_result(mulmod, count):
+    """A result made by the call is set, not added to, whatever its memory
+    held: one workgroup up to 2^15 outputs, a clearing launch and several
+    above, and an explicit grid at either side."""
+    z0 = orc.seed(wl.INDEX_MIN + 5)
+    ref, zr = orc.gen(z0, count, "u64", threads=0)
+    want = int(sum(int(x) for x in ref)) % 2 ** 64
+    for cfg in (None, nn.make_cfg(mulmod=mulmod), nn.make_cfg(mulmod=mulmod, block=64, grid=1),
+                nn.make_cfg(mulmod=mulmod, block=128, grid=3)):
+        for kind in ("u64", "f64"):
+            junk = torch.full((1,), -77, dtype=torch.int64, device="cuda")
+            del junk  # the allocator hands this memory to the result
+            got, zn = nn.consume(z0, count, kind, cfg=cfg)
+            torch.cuda.synchronize()
+            assert zn == zr
+            if kind == "u64":
+                assert int(got.item()) % 2 ** 64 == want
+            else:
+                exact = want_f64(ref)
+                # each of at most 2^19 additions rounds by 2^-53 of the sum
+                assert abs(got.item() - exact) <= 2.0 ** -34 * max(exact, 1.0)
+
+
+def want_f64(states):
+    from fractions import Fraction
+    return float(Fraction(int(sum(int(x) for x in states)), 3 ** 33))
+
+
 @pytest.mark.parametrize("block,grid", [(0, 0), (64, 1), (1024, 3), (192, 700)])
 def test_fused_consumer_balanced_edges(block, grid):
     """The FP64 consumer's balanced states at the edges of its rows: one
