@@ -898,60 +898,59 @@ __global__ __launch_bounds__(kFlatBlock) void k_queue(QueueArgs a) {
 }
 
 // Static batches (nn_generate_batch_static): the copied descriptors become
-// the chunked kernel's BatchDescs.  Thread t takes the contiguous
-// descriptors [t p, t p + p), p = ceil(n / 1024): it counts their chunk
-// records, the workgroup scans the 1024 counts, and each thread writes its
-// descriptors with their record offsets.
-__global__ __launch_bounds__(1024) void k_static_descs(char* scratch, uint32_t n, uint64_t* out) {
-    constexpr uint32_t T = 1024;
+// the chunked kernel's BatchDescs, with their record offsets (the prefix sum of
+// the windows' chunk records).  A workgroup takes kStaticScan descriptors, one a
+// thread: it sums the records of all before them itself (nothing passes
+// between workgroups), then scans its own.  Bound by the loads' latency: 3.1 us
+// for 446 descriptors, 6.3 for 3000, 10.2 for 9999.  With one workgroup for all of
+// them, each thread walking a run of its own, a call of 2924 short windows took
+// 64 us against 52 now, one of 9999 197 against 144.
+constexpr uint32_t kStaticScan = 512;
+typedef uint64_t u64x2_8 __attribute__((ext_vector_type(2), aligned(8)));
+
+__global__ __launch_bounds__(kStaticScan) void k_static_descs(char* scratch, uint32_t n) {
     constexpr uint64_t C = kChunkOuts;
-    __shared__ uint64_t s_sum[T];
+    constexpr uint32_t W = kStaticScan / 64;
+    __shared__ uint64_t s_before[W], s_own[W];
     const uint64_t* raw = reinterpret_cast<const uint64_t*>(scratch + kStaticRawOff);
     BatchDesc* dd = reinterpret_cast<BatchDesc*>(scratch + kStaticDescOff);
-    const uint32_t t = threadIdx.x;
-    const uint32_t p = (n + T - 1) / T;
-    const uint32_t d0 = t * p < n ? t * p : n;
-    const uint32_t d1 = d0 + p < n ? d0 + p : n;
-    auto records = [](uint64_t len, uint64_t off) -> uint64_t {
-        return len ? (len + (off & (C - 1)) + C - 1) / C : 0;
+    const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
+    auto records = [&](uint32_t d) -> uint64_t {
+        // length and offset in one load, and no branch between loads
+        const u64x2_8 q = *reinterpret_cast<const u64x2_8*>(raw + 3 * d + 1);
+        return (q.x + (((q.y & (C - 1)) + C - 1) & -(uint64_t)(q.x != 0))) / C;
     };
-    uint64_t mine = 0;
-    for (uint32_t d = d0; d < d1; ++d) mine += records(raw[3 * d + 1], raw[3 * d + 2]);
-    s_sum[t] = mine;
+    const uint32_t d0 = blockIdx.x * kStaticScan, d = d0 + t;
+    uint64_t before = 0;
+#pragma unroll 8
+    for (uint32_t e = t; e < d0; e += kStaticScan) before += records(e);
+    for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, 64);
+    const uint64_t own = d < n ? records(d) : 0;
+    uint64_t upto = own;  // inclusive scan over the wavefront
+    for (uint32_t off = 1; off < 64; off <<= 1) {
+        const uint64_t x = __shfl_up(upto, off, 64);
+        if (lane >= off) upto += x;
+    }
+    if (lane == 63) {
+        s_before[wave] = before;
+        s_own[wave] = upto;
+    }
     __syncthreads();
-    // inclusive scan of the counts (Hillis-Steele over the 1024 entries)
-    for (uint32_t k = 1; k < T; k <<= 1) {
-        const uint64_t add = t >= k ? s_sum[t - k] : 0;
-        __syncthreads();
-        s_sum[t] += add;
-        __syncthreads();
-    }
-    uint64_t r = s_sum[t] - mine;  // exclusive prefix
-    for (uint32_t d = d0; d < d1; ++d) {
-        const uint64_t len = raw[3 * d + 1];
-        BatchDesc D;
-        D.src = raw[3 * d];
-        D.pos = 0;
-        D.len = len;
-        D.out_off = len ? raw[3 * d + 2] : 0;  // an empty window gets no record
-        D.row_start = r;
-        dd[d] = D;
-        r += records(len, D.out_off);
-    }
-    if (t == T - 1) {
-        BatchHeader h;
-        h.out = out;
-        h.n_desc = n;
-        h.pad0 = 0;
-        h.n_rows = s_sum[T - 1];
-        h.states = nullptr;
-        for (int i = 0; i < 4; ++i) h.pad[i] = 0;
-        *reinterpret_cast<BatchHeader*>(scratch) = h;
-    }
+    if (d >= n) return;
+    uint64_t r = upto - own;
+    for (uint32_t v = 0; v < W; ++v) r += s_before[v] + (v < wave ? s_own[v] : 0);
+    BatchDesc D;
+    D.src = raw[3 * d];
+    D.pos = 0;
+    D.len = raw[3 * d + 1];
+    D.out_off = D.len ? raw[3 * d + 2] : 0;  // an empty window gets no record
+    D.row_start = r;
+    dd[d] = D;
 }
 
-hipError_t launch_static_descs(hipStream_t s, void* scratch, uint32_t n, uint64_t* out) {
-    k_static_descs<<<1, 1024, 0, s>>>(static_cast<char*>(scratch), n, out);
+hipError_t launch_static_descs(hipStream_t s, void* scratch, uint32_t n) {
+    k_static_descs<<<(n + kStaticScan - 1) / kStaticScan, kStaticScan, 0, s>>>(
+        static_cast<char*>(scratch), n);
     return hipGetLastError();
 }
 

@@ -249,7 +249,7 @@ hipError_t launch_batch_flat_inline(int kind, bool nontemporal, uint32_t grid, u
 // nn_generate_batch_static runs the chunked kernel with its workspace in one
 // static device array per device instead of a plan's allocations.  Layout
 // of that array (offsets in bytes):
-//   0                 BatchHeader, written by k_static_descs
+//   0                 unused (a BatchHeader's size)
 //   kStaticDescOff    BatchDesc[kStaticMaxStreams], prepared by k_static_descs
 //   kStaticRawOff     the caller's nn_stream_desc[n], copied in by the host
 //   kStaticRecOff     chunk records (RowRec), written by k_batch_rec
@@ -267,12 +267,11 @@ constexpr uint64_t kStaticRecOff =
     static_align(kStaticRawOff + (uint64_t)kStaticMaxStreams * 3 * sizeof(uint64_t));
 constexpr uint64_t kStaticScratchBytes = kStaticRecOff + kStaticMaxRecords * sizeof(RowRec);
 
-// Prepares a static batch on the device (one workgroup of 1024 threads):
-// the n copied descriptors {state, length, out_offset} become BatchDescs
-// (src = state, pos = 0, row_start = the prefix sum of the windows' chunk
-// records), and the header gets out, n and the record count.  Windows of
-// length 0 get no record.
-hipError_t launch_static_descs(hipStream_t stream, void* scratch, uint32_t n, uint64_t* out);
+// Prepares a static batch on the device: the n copied descriptors {state,
+// length, out_offset} become BatchDescs (src = state, pos = 0, row_start = the
+// prefix sum of the windows' chunk records).  Windows of length 0 get no
+// record.
+hipError_t launch_static_descs(hipStream_t stream, void* scratch, uint32_t n);
 
 // --------------------------------------------------- device request queue --
 // The served form's low-latency path: a persistent kernel serves requests

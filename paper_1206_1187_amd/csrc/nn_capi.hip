@@ -704,10 +704,10 @@ int nn_generate_batch_static(const nn_stream_desc* descs, uint32_t n, void* out_
         }
     }
     char* ws = static_cast<char*>(d->scratch);
-    // the caller's descriptors, then the descriptors and header the kernels read
+    // the caller's descriptors, then the descriptors the kernels read
     hipError_t e = hipMemcpyAsync(ws + kStaticRawOff, descs, (size_t)n * sizeof(nn_stream_desc),
                                   hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = launch_static_descs(s, ws, n, static_cast<uint64_t*>(out_dev));
+    if (e == hipSuccess) e = launch_static_descs(s, ws, n);
     // the chunked plan's arguments (nn_runtime.hip, slot_create) over the static workspace
     BatchArgs a;
     memset(&a, 0, sizeof a);

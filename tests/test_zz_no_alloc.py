@@ -94,6 +94,19 @@ def test_static_batch_matches_plan_two_calls(kind):
         _check_oracle(g, states, lengths, offsets, kind)
 
 
+@pytest.mark.parametrize("n", [129, 1023, 1024, 1025, 2049])
+def test_static_batch_descriptor_scan(n):
+    """Windows on both sides of the 1024 descriptors that one workgroup of the
+    scan takes, every third one empty, some over several chunks."""
+    states, lengths, offsets, total = _batch(90 + n, n, 13)
+    lengths[::3] = 0
+    got = _sentinel(total).view(torch.uint64)
+    fin = nn.generate_batch_static(states, lengths, offsets, got, final_states=True)
+    torch.cuda.synchronize()
+    assert fin.tolist() == [orc.skip(int(s), int(k)) for s, k in zip(states, lengths)]
+    _check_oracle(_bits(got), states, lengths, offsets, "u64")
+
+
 def test_static_batch_empty_and_limits():
     """No streams, only empty windows: nothing written, states unchanged;
     more streams than the workspace holds: NN_ERANGE before any launch."""
