@@ -551,15 +551,16 @@ int nn_e40_skip(uint64_t state, uint64_t k, uint64_t *state_out);
  * uint64 or binary64 and sets *state to z_count; asynchronous on `stream`.
  * cfg (NULL for the defaults) may set block, grid, unroll (1, 2, 4), ilp
  * (1, 2, 4), NN_CFG_TEMPORAL_STORES and mulmod: NN_MULMOD_FP64 (the
- * default: states as two base-3^20 limbs, since 3^40 = (3^20)^2 the step is
- * three exact FP64 products modulo 3^20; defaults 256 threads, one
- * workgroup per CU, ilp 2, unroll 1) or NN_MULMOD_MONTGOMERY (64-bit
+ * default: states as three limbs, 3^40 = (3^14)^2 3^12, whose products are
+ * exact in FP64; row layout defaults 256 threads, one workgroup per CU, ilp 2,
+ * unroll 1) or NN_MULMOD_MONTGOMERY (64-bit
  * states, R = 2^64; defaults 256 threads, three workgroups per CU, ilp 4,
  * unroll 2).  Layouts: the row layout, or (NN_CFG_FLAT, and the default for
  * either kind with the FP64 step) the flat layout: one 256-thread workgroup
- * per chunk of `unroll` rows of 512 outputs (2, 4, 8, 16, 32; default 16, or
- * fewer where the output would not give every compute unit two chunks),
- * residency capped by `occupancy` (default 4); with one workgroup per chunk
+ * per chunk of `unroll` rows of 512 outputs (2, 4, 8, 16, 32; default 8 for
+ * f64 and 16 for u64, or fewer where the output would not give every compute
+ * unit two chunks), residency capped by `occupancy` (default 3 for f64 and 2
+ * for u64; Montgomery's step: 16 rows, 4); with one workgroup per chunk
  * (grid 0) the chunks are taken in XCD runs of 4 MiB per XCD as in the 3^33
  * flat layout; the launch also writes the first element of an output that is
  * only 8-byte aligned (below 2^22 outputs a cfg that sets grid, unroll or
@@ -588,7 +589,7 @@ int nn_debug_mulmod(int mulmod, const uint64_t *a, const uint64_t *b, uint64_t n
 /* nn_e40_debug_mulmod -- the host build of the 3^40 step's Montgomery
  * reduction: out[i] = a[i] * b[i] mod 3^40 for units a[i], b[i]; host
  * pointers.  nn_e40_debug_mulmod_ex selects the reduction: NN_MULMOD_FP64
- * (or NN_MULMOD_DEFAULT; the base-3^20 limb step) or NN_MULMOD_MONTGOMERY;
+ * (or NN_MULMOD_DEFAULT; the three-limb step) or NN_MULMOD_MONTGOMERY;
  * NN_EINVAL for any other, a NULL array or a non-unit operand. */
 int nn_e40_debug_mulmod(const uint64_t *a, const uint64_t *b, uint64_t n, uint64_t *out);
 int nn_e40_debug_mulmod_ex(int mulmod, const uint64_t *a, const uint64_t *b, uint64_t n,

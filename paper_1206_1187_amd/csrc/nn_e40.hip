@@ -85,10 +85,7 @@ constexpr uint32_t kFHi = 2048;
 constexpr uint64_t kFLoOff = (uint64_t)kLo + kHi;
 constexpr uint64_t kFHiOff = kFLoOff + kFLo;
 constexpr uint64_t kFlatMaxRows = (uint64_t)kFLo * kFHi;  // rows of 512 per launch (2^21)
-// The tables' entries as Mult40, then the same entries as base-B limbs
-// (Mult40L, the same size), so the FP64 step starts without Montgomery.
 constexpr uint64_t kTabEntries = kFHiOff + kFHi;
-static_assert(sizeof(Mult40L) == sizeof(Mult40), "limb entries follow at the same stride");
 constexpr uint64_t kMaxThreads = (uint64_t)kLo * kHi / 2;
 constexpr int kMaxDev = 64;
 
@@ -102,7 +99,7 @@ Mult40* g_tab[kMaxDev];  // kLo + kHi + kFLo + kFHi entries per device
 constexpr uint32_t kSymLo = 512;
 constexpr uint32_t kSymHi = kSymLo + kFLo;
 constexpr uint32_t kSymEntries = kSymHi + kFHi;
-__device__ Mult40L e40_sym[kSymEntries];
+__device__ Mult40T e40_sym[kSymEntries];
 
 int device_tables(const Mult40** out) {
     int dev = -1;
@@ -115,7 +112,7 @@ int device_tables(const Mult40** out) {
     std::lock_guard<std::mutex> lock(g_mu);
     if (!g_tab[dev]) {
         static std::vector<Mult40> host = [] {
-            std::vector<Mult40> t(2 * kTabEntries);
+            std::vector<Mult40> t(kTabEntries);
             uint64_t r = 1;
             for (uint32_t l = 0; l < kLo; ++l, r = h_mul(r, kMult)) t[l] = make_mult40(r);
             const uint64_t step = Powers::get().pow(kLo);
@@ -127,8 +124,6 @@ int device_tables(const Mult40** out) {
             const uint64_t big = r;  // (2^53)^(512 kFLo)
             r = 1;
             for (uint32_t i = 0; i < kFHi; ++i, r = h_mul(r, big)) t[kFHiOff + i] = make_mult40(r);
-            Mult40L* limbs = reinterpret_cast<Mult40L*>(t.data() + kTabEntries);
-            for (uint64_t i = 0; i < kTabEntries; ++i) limbs[i] = make_mult40l(t[i].v);
             return t;
         }();
         void* mem = nullptr;
@@ -136,11 +131,11 @@ int device_tables(const Mult40** out) {
         if (e != hipSuccess) return fail(NN_ENOMEM, "hipMalloc e40 tables: %s", hipGetErrorString(e));
         e = hipMemcpy(mem, host.data(), host.size() * sizeof(Mult40), hipMemcpyHostToDevice);
         if (e == hipSuccess) {
-            const Mult40L* limbs = reinterpret_cast<const Mult40L*>(host.data() + kTabEntries);
-            std::vector<Mult40L> sym(limbs, limbs + kSymLo);  // t_lo's first 512
-            sym.insert(sym.end(), limbs + kFLoOff, limbs + kFLoOff + kFLo);
-            sym.insert(sym.end(), limbs + kFHiOff, limbs + kFHiOff + kFHi);
-            e = hipMemcpyToSymbol(HIP_SYMBOL(e40_sym), sym.data(), sizeof(Mult40L) * kSymEntries,
+            std::vector<Mult40T> sym;
+            for (uint32_t k = 0; k < kSymLo; ++k) sym.push_back(make_mult40t(host[k].v));
+            for (uint64_t k = kFLoOff; k < kTabEntries; ++k)  // t_flo, then t_fhi
+                sym.push_back(make_mult40t(host[k].v));
+            e = hipMemcpyToSymbol(HIP_SYMBOL(e40_sym), sym.data(), sizeof(Mult40T) * kSymEntries,
                                   0, hipMemcpyHostToDevice);
         }
         if (e != hipSuccess) {
@@ -163,22 +158,22 @@ struct E40Args {
     Mult40 J;       // (2^53)^(2T)
     Mult40 M1;      // 2^53
     Mult40 JI;      // J^IL
-    Mult40L JL, M1L, JIL;  // the same multipliers as base-B limbs
+    Mult40T JL, JIL;  // the same multipliers as limbs
     const Mult40* t_lo;
     const Mult40* t_hi;
     uint64_t* head;       // 8-byte aligned output's first element, or null
     uint64_t head_state;  // its state
 };
 
-// The two step reductions: MM 0 = Montgomery on 64-bit states, MM 1 = FP64
-// on base-B limbs.
+// The two step reductions: MM 0 = Montgomery on 64-bit states, MM 1 = FP64 on
+// limbs.
 template <int MM>
 struct Step;
 template <>
 struct Step<0> {
     typedef uint64_t S;
     static __device__ __forceinline__ S from(uint64_t z) { return z; }
-    static __device__ __forceinline__ S mul(S z, const Mult40& v, const Mult40L&) {
+    static __device__ __forceinline__ S mul(S z, const Mult40& v, const Mult40T&) {
         return mm40(z, v.mont);
     }
     template <int KIND>
@@ -191,10 +186,10 @@ struct Step<0> {
 };
 template <>
 struct Step<1> {
-    typedef L2 S;
-    static __device__ __forceinline__ S from(uint64_t z) { return limbs(z); }
-    static __device__ __forceinline__ S mul(S z, const Mult40&, const Mult40L& v) {
-        return mul40l(z, v);
+    typedef L3 S;
+    static __device__ __forceinline__ S from(uint64_t z) { return limbs3(z); }
+    static __device__ __forceinline__ S mul(S z, const Mult40&, const Mult40T& v) {
+        return mul40t(z, v);
     }
     template <int KIND>
     static __device__ __forceinline__ uint64_t bits(S z) {
@@ -287,9 +282,9 @@ struct E40FlatArgs {
     uint64_t n_chunks;   // whole chunks, n_chunks * R <= kFlatMaxRows
     uint64_t base;       // state of out[0]
     Mult40 M1, J, JN;
-    Mult40L M1L, JL, JNL;
-    const Mult40* tabs;  // t_lo, t_hi, t_flo, t_fhi, then the same as limbs
-    double base_lo, base_hi;  // base as base-B limbs (limbs())
+    Mult40T JL, JNL;
+    const Mult40* tabs;  // t_lo, t_hi, t_flo, t_fhi (Montgomery)
+    L3 base_l;           // base as limbs
     // k_e40_flat_any only:
     uint32_t runs;       // the first chunks, in XCD runs (e40_run_chunks)
     uint32_t tail;       // outputs of the partial chunk after the whole ones
@@ -305,11 +300,11 @@ __device__ __forceinline__ void e40_start(const E40FlatArgs& a, uint64_t u, uint
         // in limbs throughout: the chunk's two row multipliers, then the
         // lane's two offsets (all four loads independent, from e40_sym), no
         // Montgomery
-        const Mult40L hi = e40_sym[kSymHi + u / kFLo], lo = e40_sym[kSymLo + u % kFLo];
-        const Mult40L la = e40_sym[2u * l], lb = e40_sym[2u * l + 1];
-        const L2 S0 = mul40l(mul40l(L2{a.base_lo, a.base_hi}, hi), lo);
-        za = mul40l(S0, la);
-        zb = mul40l(S0, lb);
+        const Mult40T hi = e40_sym[kSymHi + u / kFLo], lo = e40_sym[kSymLo + u % kFLo];
+        const Mult40T la = e40_sym[2u * l], lb = e40_sym[2u * l + 1];
+        const L3 S0 = mul40t(mul40t(a.base_l, hi), lo);
+        za = mul40t(S0, la);
+        zb = mul40t(S0, lb);
     } else {
         const uint64_t z0 = mm40(mm40(mm40(a.base, a.tabs[kFHiOff + u / kFLo].mont),
                                       a.tabs[kFLoOff + u % kFLo].mont),
@@ -513,25 +508,36 @@ hipError_t launch(int kind, int mm, int ilp, int unroll, bool nt, uint32_t grid,
 
 }  // namespace
 
-// The library's default layout at modulus 3^40 for a 16-byte aligned
-// output with the FP64 step: the flat one, 16 rows of 512 per chunk, in XCD
-// runs, its multipliers at a fixed address (2^30 f64 / 2^28 u64 outputs, one
-// MI355X, medians of four interleaved rounds: f64 6.21-6.30 TB/s at caps 3-5
-// against 5.98-6.11 with 8 rows, 5.81-5.96 with 32 rows and 6.12 for the row
-// layout; u64 6.28-6.36 against 6.10-6.21 with 8 rows and 6.05 for the row
-// layout).  The step is VALU-bound, so the longer chunk pays: a lane's
-// start (four limb products) is spread over 32 outputs.
-// An output too short to give every CU two such chunks takes shorter ones (8,
-// 4, then 2 rows): its time is a workgroup's own chain of rows.  Kernel times
-// with 16 rows and by this rule, f64 (u64): 200,003 outputs 4.16 and 2.74 us
-// (4.34, 2.80), 2^20 5.12 and 4.46 (5.26, 4.38), 3,000,017 7.76 and 7.64
-// (7.88, 7.88); from 2^22 on 16 rows are the faster or tie.
-constexpr uint32_t kE40FlatDefaultRows = 16;
+// The flat layout's default shape, temporal stores (one chunk per workgroup, in
+// XCD runs): rows of 512 per chunk and resident workgroups per CU.  What bounds
+// it is how the stores of a workgroup are spaced, more than the arithmetic: with
+// the 15-instruction step 16 rows at 4 write slower than with 20 instructions,
+// and other shapes faster.  Medians over two boxes, 2^28 and 100,000,007 outputs:
+//   f64 (25.8 VALU instructions an output): 8 rows at 3 311 and 122 us; 16 at 4
+//     355 and 137; 8 at 4 333 and 130; 8 at 2 with non-temporal stores 306 and 118,
+//     but 43.1 against 39.6 at 2^25 (two limbs of 3^20, 30.3 an output, 16 at 4: 335
+//     and 138, 8 at 3 326);
+//   u64 (30.8): 16 rows at 2 339 and 125; 16 at 4 336 and 135; 8 at 3 341 and 129; 8
+//     at 3 non-temporal 330 and 124, but 43.3 against 40.5 at 2^25 (two limbs, 16 at
+//     4: 350 and 132).
+// Montgomery's step keeps 16 rows at 4.
+struct E40Shape {
+    uint32_t rows, occupancy;
+};
+inline E40Shape e40_shape(int kind, int mm) {
+    if (mm == 0) return {16, kFlatDefaultOccupancy};
+    return kind == NN_OUT_F64 ? E40Shape{8, 3} : E40Shape{16, 2};
+}
+
+// An output too short to give every CU two such chunks takes shorter ones
+// (halved down to 2 rows): its time is a workgroup's own chain of rows.  Kernel
+// times with 16 rows and by this rule, two limbs, f64 (u64): 200,003 outputs 4.16
+// and 2.74 us (4.34, 2.80), 2^20 5.12 and 4.46 (5.26, 4.38).
 
 // nn_e40_generate_ex's flat layout (arguments already validated: a valid
 // state, count > 0, an in-range pointer).  cfg: unroll = rows of 512
 // outputs per chunk (2, 4, 8, 16, 32; default by size), grid = workgroups per launch
-// (0: one per chunk), occupancy = residency cap (0: 4), store policy
+// (0: one per chunk), occupancy = residency cap (0: e40_shape), store policy
 // (default temporal).
 int generate_flat(uint64_t* state, uint64_t count, void* out_dev, int kind, void* stream,
                   const nn_launch_cfg& c, int mm) {
@@ -547,14 +553,15 @@ int generate_flat(uint64_t* state, uint64_t count, void* out_dev, int kind, void
     DeviceTables* d = nullptr;
     st = current_device(&d);
     if (st) return st;
-    const uint32_t occ = c.occupancy ? c.occupancy : kFlatDefaultOccupancy;
+    const E40Shape shape = e40_shape(kind, mm);
+    const uint32_t occ = c.occupancy ? c.occupancy : shape.occupancy;
     if (occ < 2 || occ > 16) return fail(NN_EINVAL, "occupancy %u: must be 0 or in [2, 16]", occ);
     const uint32_t lds = (d->lds_per_cu / (occ + 1) / 512 + 1) * 512;
     if (lds > d->lds_per_block || (uint64_t)lds * occ > d->lds_per_cu)
         return fail(NN_EINVAL, "occupancy %u not expressible on this device", occ);
     const bool nt = (c.flags & NN_CFG_NONTEMPORAL_STORES) != 0;
     const uint64_t s = *state;
-    uint32_t rows = c.unroll ? c.unroll : kE40FlatDefaultRows;
+    uint32_t rows = c.unroll ? c.unroll : shape.rows;
     if (!c.unroll && !c.grid)
         while (rows > 2 && count / (512ull * rows) < 2ull * (d->cus > 0 ? d->cus : 1)) rows /= 2;
     const uint64_t per = 512ull * rows;
@@ -562,8 +569,7 @@ int generate_flat(uint64_t* state, uint64_t count, void* out_dev, int kind, void
     E40FlatArgs a = {};
     a.M1 = make_mult40(kMult);
     a.J = make_mult40(Powers::get().pow(512));
-    a.M1L = make_mult40l(a.M1.v);
-    a.JL = make_mult40l(a.J.v);
+    a.JL = make_mult40t(a.J.v);
     a.tabs = tab;
     // an output that is only 8-byte aligned: its first element beside the
     // 16-byte aligned rest
@@ -575,8 +581,7 @@ int generate_flat(uint64_t* state, uint64_t count, void* out_dev, int kind, void
         const uint64_t n = count - off < max_launch ? count - off : max_launch;
         a.out = (uint64_t*)out_dev + off;
         a.base = h_mul(s, Powers::get().pow(off + 1));  // the state of this slice's first output
-        a.base_lo = limbs(a.base).lo;
-        a.base_hi = limbs(a.base).hi;
+        a.base_l = limbs3(a.base);
         a.n_chunks = n / per;
         a.tail = (uint32_t)(n % per);
         a.runs = mm == 1 ? (uint32_t)e40_run_chunks((int)rows, a.n_chunks) : 0u;
@@ -585,12 +590,11 @@ int generate_flat(uint64_t* state, uint64_t count, void* out_dev, int kind, void
         if (c.grid && c.grid < a.n_chunks) {
             grid = c.grid;
             a.JN = make_mult40(Powers::get().pow(per * grid - 512ull * (rows - 1)));
-            a.JNL = make_mult40l(a.JN.v);
+            a.JNL = make_mult40t(a.JN.v);
             rest.n_chunks = rest.runs = 0;
             rest.out = a.out + a.n_chunks * per;
             rest.base = h_mul(a.base, Powers::get().pow(a.n_chunks * per));
-            rest.base_lo = limbs(rest.base).lo;
-            rest.base_hi = limbs(rest.base).hi;
+            rest.base_l = limbs3(rest.base);
         }
         const hipError_t e =
             launch_flat(kind, mm, (int)rows, nt, grid, lds, (hipStream_t)stream, a, rest);
@@ -712,9 +716,8 @@ int nn_e40_generate_ex(uint64_t* state, uint64_t count, void* out_dev, int kind,
     a.J = e40::make_mult40(e40::Powers::get().pow(row));
     a.M1 = e40::make_mult40(e40::kMult);
     a.JI = e40::make_mult40(e40::Powers::get().pow(row * ilp));
-    a.JL = e40::make_mult40l(a.J.v);
-    a.M1L = e40::make_mult40l(a.M1.v);
-    a.JIL = e40::make_mult40l(a.JI.v);
+    a.JL = e40::make_mult40t(a.J.v);
+    a.JIL = e40::make_mult40t(a.JI.v);
     a.t_lo = tab;
     a.t_hi = tab + e40::kLo;
     hipError_t e = e40::launch(kind, mm, (int)ilp, (int)unroll, !(c.flags & NN_CFG_TEMPORAL_STORES),
@@ -742,7 +745,14 @@ int nn_e40_debug_mulmod_ex(int mulmod, const uint64_t* a, const uint64_t* b, uin
         for (uint64_t i = 0; i < n; ++i) out[i] = e40::mm40(a[i], e40::make_mult40(b[i]).mont);
     else
         for (uint64_t i = 0; i < n; ++i)
-            out[i] = e40::to_u64(e40::mul40l(e40::limbs(a[i]), e40::make_mult40l(b[i])));
+        {
+            // the kernels' step and the form on two limbs; 0, which no product
+            // of units is, where they differ
+            const uint64_t two = e40::to_u64(e40::mul40l(e40::limbs(a[i]), e40::make_mult40l(b[i])));
+            const uint64_t three =
+                e40::to_u64(e40::mul40t(e40::limbs3(a[i]), e40::make_mult40t(b[i])));
+            out[i] = two == three ? two : 0;
+        }
     return ok();
 }
 

@@ -3,8 +3,9 @@
 // multiplier 2^53 (still 53 bits of alpha_{2,3} per step), Eq. 2 with 3^40
 // in place of 3^33.  m > 2^63, so states need all 64 bits and the product
 // of two of them 128: the FP64 reduction of the 3^33 path does not apply.
-// The step uses Montgomery's reduction with R = 2^64 and multipliers kept in
-// Montgomery form (v R mod m), so states stay in standard form.
+// The default step runs on FP64 limbs; the other is Montgomery's reduction with
+// R = 2^64 and multipliers kept in Montgomery form (v R mod m), so its states stay
+// in standard form.
 #pragma once
 
 #include <stdint.h>
@@ -51,7 +52,8 @@ NN_HD uint64_t mm40(uint64_t z, uint64_t vmont) {
 
 NN_HD double to_f64(uint64_t z) { return (double)z * kRecip; }
 
-// The FP64 step: base-B limbs, B = 3^20 < 2^32, m = B^2.  For a state
+// The step on two limbs, an exact form of its own against which the host build
+// checks the kernels' (below): base-B limbs, B = 3^20 < 2^32, m = B^2.  For a state
 // z = x1 B + x0 and a multiplier v = j1 B + j0 the term x1 j1 B^2 is a
 // multiple of m, so
 //     v z = (x1 j0 + x0 j1 + c) B + r   (mod m),   x0 j0 = c B + r,
@@ -127,6 +129,96 @@ NN_HD uint64_t to_u64(L2 z) {
 NN_HD double to_f64(L2 z) { return __builtin_fma(top(z), kB, z.lo) * kRecip; }
 
 inline Mult40L make_mult40l(uint64_t v) { return Mult40L{(double)(v % kLimb), (double)(v / kLimb)}; }
+
+// The kernels' FP64 step: three balanced limbs.  With B = 3^14 and D = 3^12, m = B^2 D, and
+// a state z stands as z = (x2 B + x1) B + x0 (mod m) with |x0|, |x1| < B/2 and
+// |x2| < D/2, the balanced residue of z in its balanced digits.  The product
+// with a multiplier's limbs j needs only what stays below B^2 D:
+//     t0 = x0 j0,                        x0' = t0 mod B, carry q0;
+//     t1 = x0 j1 + x1 j0 + q0,           x1' = t1 mod B, carry q1;
+//     t2 = x0 j2 + x1 j1 + x2 j0 + q1,   x2' = t2 mod D,
+// six products as FMAs and three reductions of three instructions each, 15 where
+// two limbs of 3^20 take 20 (their products have 64 bits and need the two-product
+// and a quotient each).  Every t is an integer below 2^43.4, so all of this is
+// exact, and a quotient's fused multiply-add onto 1.5 * 2^52 rounds t/B to the
+// nearest integer: t/B is at least 1/(2B) = 2^-23 away from a half (B is odd),
+// its error below 2^-30.  So limbs are unique, whatever led to them.
+constexpr uint64_t kLimb3 = 4782969ULL;    // 3^14
+constexpr uint64_t kTopLimb = 531441ULL;  // 3^12
+constexpr double kB3 = 4782969.0;
+constexpr double kRB3 = 1.0 / 4782969.0;  // RN(1/B)
+constexpr double kD = 531441.0;
+constexpr double kRD = 1.0 / 531441.0;  // RN(1/D)
+constexpr double kBD = 2541865828329.0;  // B D = 3^26
+constexpr double kRBD = 1.0 / 2541865828329.0;
+constexpr double kHalfRBD = 0.5 / 2541865828329.0;
+static_assert(kLimb3 * kLimb3 * kTopLimb == kMod, "3^40 = (3^14)^2 3^12");
+
+struct L3 {
+    double x0, x1, x2;
+};
+
+struct Mult40T {
+    double j0, j1, j2;  // a multiplier's balanced limbs
+};
+
+// The integer nearest to t/base for the base's reciprocal rb (kBalRound in
+// nn_arith.hpp: 1.5 * 2^52).
+NN_HD double near_quot(double t, double rb) {
+    return __builtin_fma(t, rb, kBalRound) - kBalRound;
+}
+
+NN_HD L3 mul40t(L3 z, Mult40T v) {
+    const double t0 = z.x0 * v.j0;
+    const double q0 = near_quot(t0, kRB3);
+    const double t1 = __builtin_fma(z.x0, v.j1, __builtin_fma(z.x1, v.j0, q0));
+    const double q1 = near_quot(t1, kRB3);
+    const double t2 = __builtin_fma(
+        z.x0, v.j2, __builtin_fma(z.x1, v.j1, __builtin_fma(z.x2, v.j0, q1)));
+    const double q2 = near_quot(t2, kRD);
+    return L3{__builtin_fma(-q0, kB3, t0), __builtin_fma(-q1, kB3, t1), __builtin_fma(-q2, kD, t2)};
+}
+
+// A state's limbs: its balanced residue, digit by digit.
+NN_HD L3 limbs3(uint64_t z) {
+    const int64_t b = (int64_t)(z > kMod / 2 ? z - kMod : z);  // |b| < 2^63
+    const int64_t n = (int64_t)kLimb3, h = n / 2;
+    int64_t x0 = b % n;
+    x0 += x0 < -h ? n : x0 > h ? -n : 0;
+    const int64_t r = (b - x0) / n;
+    int64_t x1 = r % n;
+    x1 += x1 < -h ? n : x1 > h ? -n : 0;
+    return L3{(double)x0, (double)x1, (double)((r - x1) / n)};
+}
+
+// The output's z in [0, m) is T B + x0 for T = x2 B + x1, or with T + B D where
+// that is negative: for T < 0, or T = 0 and x0 < 0 (x0 is never 0, a state being
+// a unit).  (T + 1/2) / (B D), the half taking x0's sign, lies in (-1, 1) and
+// at least 1/(2 B D) from 0 and 1, far beyond the one rounding that forms it, so its
+// floor, 0 or -1, tells.  Returns that T, in [0, B D).
+NN_HD double top(L3 z) {
+    const double t = __builtin_fma(z.x2, kB3, z.x1);
+    const double f =
+        __builtin_floor(__builtin_fma(t, kRBD, __builtin_copysign(kHalfRBD, z.x0)));
+    return __builtin_fma(-f, kBD, t);
+}
+
+NN_HD uint64_t to_u64(L3 z) {
+    // top < 2^41.3 lies in the low bits of top + 2^52, x0 (below 2^22 in
+    // magnitude) in the low word of x0 + 1.5 * 2^52
+    const uint64_t t = __builtin_bit_cast(uint64_t, top(z) + 4503599627370496.0);
+    const int32_t x0 = (int32_t)(uint32_t)__builtin_bit_cast(uint64_t, z.x0 + kBalRound);
+    const uint64_t lo = (uint64_t)(uint32_t)t * (uint32_t)kLimb3 + (uint64_t)(int64_t)x0;
+    return lo + ((uint64_t)(((uint32_t)(t >> 32) & 0x3ffu) * (uint32_t)kLimb3) << 32);
+}
+
+// RN(z) is one FMA: top B + x0 formed exactly and rounded once.
+NN_HD double to_f64(L3 z) { return __builtin_fma(top(z), kB3, z.x0) * kRecip; }
+
+inline Mult40T make_mult40t(uint64_t v) {
+    const L3 x = limbs3(v);
+    return Mult40T{x.x0, x.x1, x.x2};
+}
 
 }  // namespace e40
 }  // namespace nn

@@ -89,6 +89,23 @@ def test_e40_host_build_of_limb_step_at_limb_edges():
     assert np.array_equal(nn.e40_debug_mulmod(a, b, "fp64"), want)
 
 
+@pytest.mark.parametrize("half", [0, 1])
+def test_e40_host_build_of_limb_step_at_balanced_edges(half):
+    """The FP64 step keeps balanced digits x0, x1 (base 3^14) and x2 (base
+    3^12): states and multipliers whose digits sit at 0, +-1 and the ends of
+    their ranges, so sums and carries take their largest values and the output
+    both signs, T = 0 among them."""
+    B, D = 3 ** 14, 3 ** 12
+    ends = [0, 1, -1, B // 2, -(B // 2)]
+    tops = [0, 1, -1, D // 2, -(D // 2)]
+    vals = sorted({((x2 * B + x1) * B + x0) % M for x2 in tops for x1 in ends for x0 in ends})
+    vals = [v for v in vals if v % 3][half::2]
+    a = [x for x in vals for _ in vals]
+    b = [y for _ in vals for y in vals]
+    want = np.array([x * y % M for x, y in zip(a, b)], dtype=np.uint64)
+    assert np.array_equal(nn.e40_debug_mulmod(a, b, "fp64"), want)
+
+
 def test_e40_generate_validation_before_device():
     lib = _native.lib()
     buf = (ctypes.c_uint64 * 64)()
