@@ -79,11 +79,11 @@ typedef enum nn_mulmod {
  *    rows of 512 consecutive outputs (one contiguous chunk), two per lane in
  *    one 16-byte store per row, and exits; the same launch writes a partial
  *    last chunk and, for an output that is only 8-byte aligned, its first
- *    element, the rest being 16-byte aligned.  With 4 rows the chunks are
- *    taken in XCD runs: of every 2048 consecutive chunks, each of the 8
- *    XCDs (which take consecutive workgroups in turn) writes 256
- *    consecutive ones (4 MiB); chunks after the last full run, and every
- *    chunk with other row counts, in address order;
+ *    element, the rest being 16-byte aligned.  With 2 or 4 rows the
+ *    chunks are taken in XCD runs: of every 32 MiB of consecutive chunks, each
+ *    of the 8 XCDs (which take consecutive workgroups in turn) writes 4 MiB of
+ *    consecutive ones; chunks after the last full run, and every chunk with
+ *    other row counts, in address order;
  *  - rows (NN_CFG_ROWS; the default otherwise): grid*block threads loop
  *    over rows of width*grid*block outputs, stepping by a jump multiplier;
  *  - consecutive (NN_CFG_CONSECUTIVE): the paper's per-thread loop (Section
@@ -102,7 +102,9 @@ typedef enum nn_mulmod {
  * unroll: 1, 2, 4 or 8 iterations of the step loop per trip (rows); outputs
  * per thread and tile, 2, 4, 8, 16 or 32 (consecutive, default 4 with 512
  * threads per workgroup); rows per workgroup, 1, 2, 4, 8 or 16 (flat,
- * default 4).
+ * default 4; a cfg that sets neither unroll nor occupancy, NN_MULMOD_FP64 at
+ * most, temporal stores and no address order takes 2 from 2^24 outputs on, for
+ * f64 up to 2^29).
  * flags: NN_CFG_TEMPORAL_STORES keeps stores cacheable and
  * NN_CFG_NONTEMPORAL_STORES makes them non-temporal streaming stores (at
  * most one of the two; default: non-temporal, except temporal for the flat
@@ -111,7 +113,7 @@ typedef enum nn_mulmod {
  * width: outputs per lane and store, 1 (8-byte stores) or 2 (16-byte
  * stores, needs a 16-byte aligned output) (rows; flat is always 2).
  * occupancy: 0, or a cap in [2,16] on resident workgroups per compute unit
- * (flat; 0 there means 4), enforced through unused dynamic LDS.
+ * (flat; 0 there means 4, with the 2 rows above 5 for f64 and 6 for u64), enforced through unused dynamic LDS.
  * Consecutive: width 2 (16-byte stores) on a 16-byte aligned output, else 1. 
  * ilp: rows each thread keeps in flight, 1, 2 or 4 (rows with width 2):
  * 2*ilp independent multiplication chains per lane. */

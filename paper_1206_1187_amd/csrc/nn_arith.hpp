@@ -70,7 +70,8 @@ struct Mult {
 // this form because their stores, spaced by the longer instruction stream,
 // write faster on MI355X (same GPU, same shapes: plain u64 6.8-6.9 against
 // 5.8 TB/s, interleaved batch 6.1 against 5.8 TB/s).  The fused consumer,
-// bound by its arithmetic, uses mm_bal below.  Translation units are built
+// bound by its arithmetic, uses mm_bal below, and so do the plain generator's
+// chunks of two rows, whose shape suits the shorter stream.  Translation units are built
 // with FP contraction off so no product is fused into a neighbouring add.
 NN_HD double mm_fp64(double z, double v, double qh, double ql) {
     const double mod = (double)kMod;
@@ -84,8 +85,7 @@ NN_HD double mm_fp64(double z, double v, double qh, double ql) {
 }
 
 // ------------------------------------------------------- balanced FP64 --
-// The step on balanced representatives, for a consumer that needs the sum of
-// the states and not each of them reduced to [1, m): a state is an integer r
+// The step on balanced representatives: a state is an integer r
 // congruent to z with |r| < 0.6 m, the multiplier v' one of v, v - m with
 // |v'| < m/2, and q' = RN(v'/m).  Six instructions against nn_dev_mulmod's
 // eleven: no conditional add, and one product of the quotient instead of two.
@@ -165,16 +165,28 @@ NN_HD uint64_t mm_modbarrett_step(uint64_t z) {
 }
 
 // ----------------------------------------------------- variant policies --
-// State type, conversion and one multiplication per reduction.
+// State type, multiplier type, conversion and one multiplication per reduction.
 struct VarFP64 {
     typedef double S;
+    typedef Mult M;
     static NN_HD S load(uint64_t x) { return (double)x; }
     static NN_HD S mul(S z, const Mult& f) { return mm_fp64(z, f.v, f.qh, f.ql); }
     static NN_HD uint64_t to_u64(S z) { return (uint64_t)z; }
     static NN_HD double to_f64(S z) { return z * kRecip; }
 };
+// FP64 on balanced states: the step is six instructions, the output's z four more.
+struct VarBal {
+    typedef double S;
+    typedef BalMult M;
+    static NN_HD S load(uint64_t x) { return balanced((double)x); }
+    static NN_HD S mul(S r, const M& f) { return mm_bal(r, f); }
+    static NN_HD double state(S r) { return r < 0.0 ? r + kModD : r; }
+    static NN_HD uint64_t to_u64(S r) { return (uint64_t)state(r); }
+    static NN_HD double to_f64(S r) { return state(r) * kRecip; }
+};
 struct VarBarrett {
     typedef uint64_t S;
+    typedef Mult M;
     static NN_HD S load(uint64_t x) { return x; }
     static NN_HD S mul(S z, const Mult& f) { return mm_barrett(z, f.vi); }
     static NN_HD uint64_t to_u64(S z) { return z; }
@@ -182,6 +194,7 @@ struct VarBarrett {
 };
 struct VarShoup {
     typedef uint64_t S;
+    typedef Mult M;
     static NN_HD S load(uint64_t x) { return x; }
     static NN_HD S mul(S z, const Mult& f) { return mm_shoup(z, f.vi, f.shoup); }
     static NN_HD uint64_t to_u64(S z) { return z; }
@@ -189,6 +202,7 @@ struct VarShoup {
 };
 struct VarMontgomery {
     typedef uint64_t S;
+    typedef Mult M;
     static NN_HD S load(uint64_t x) { return x; }
     static NN_HD S mul(S z, const Mult& f) { return mm_montgomery(z, f.mont); }
     static NN_HD uint64_t to_u64(S z) { return z; }

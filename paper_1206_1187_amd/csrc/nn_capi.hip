@@ -155,7 +155,15 @@ int resolve_cfg(const nn_launch_cfg* cfg, int kind, uint64_t count, const Device
                                  : c.width == 0 && count >= kFlatUnalignedMin));
     if ((c.flags & NN_CFG_ADDRESS_ORDER) && !r->flat)
         return fail(NN_EINVAL, "NN_CFG_ADDRESS_ORDER applies to the flat layout only");
-    r->occupancy = c.occupancy ? c.occupancy : (r->flat ? kFlatDefaultOccupancy : 0u);
+    // Neither rows nor residency asked for, nor address order, non-temporal
+    // stores or another reduction: the fast shape.
+    const bool fast = r->flat && !c.unroll && !c.occupancy && r->mulmod == NN_MULMOD_FP64 &&
+                      count >= kFlatFastMin &&
+                      (kind == NN_OUT_U64 || count < kFlatFastMaxF64) &&
+                      !(c.flags & (NN_CFG_ADDRESS_ORDER | NN_CFG_NONTEMPORAL_STORES));
+    r->occupancy = c.occupancy ? c.occupancy
+                   : fast      ? flat_fast_occupancy(kind)
+                               : (r->flat ? kFlatDefaultOccupancy : 0u);
     r->lds = 0;
     if (r->occupancy) {
         if (r->occupancy < 2 || r->occupancy > 16)
@@ -174,12 +182,11 @@ int resolve_cfg(const nn_launch_cfg* cfg, int kind, uint64_t count, const Device
         r->ilp = 1;
         // rows per workgroup; temporal stores unless asked otherwise (the
         // measured best, see kFlatDefaultRows)
-        r->unroll = c.unroll ? c.unroll : kFlatDefaultRows;
+        r->unroll = c.unroll ? c.unroll : fast ? kFlatFastRows : kFlatDefaultRows;
         if (r->unroll == 0 || r->unroll > kFlatMaxRows || (r->unroll & (r->unroll - 1)))
             return fail(NN_EINVAL, "unroll %u: the flat layout writes 1, 2, 4, 8 or 16 rows "
                                    "per workgroup", r->unroll);
         if (!store_flags) r->nontemporal = false;
-        if (r->unroll != 4) r->xcd_runs = false;
         const uint64_t chunk = count < kFlatMaxCount ? count : kFlatMaxCount;
         const uint64_t per = (uint64_t)kFlatPerBlock * r->unroll;
         r->grid = (uint32_t)((chunk + per - 1) / per);
@@ -360,8 +367,11 @@ int nn_generate_ex(uint64_t* state, uint64_t count, void* out_dev, int kind, voi
         static const Mult M1 = make_mult(kMult);
         static const Mult J = make_mult(MultPowers::get().pow(kFlatPerBlock));
         FlatArgs f;
+        static const BalMult bal_M1 = make_bal(M1.vi), bal_J = make_bal(J.vi);
         f.M1 = M1;
         f.J = J;
+        f.bal_M1 = bal_M1;
+        f.bal_J = bal_J;
         f.head_state = h_skip(s, 1);
         hipError_t e = hipSuccess;
         for (uint64_t off = 0; off < count && e == hipSuccess;) {
@@ -778,7 +788,13 @@ int nn_debug_mulmod(int mulmod, const uint64_t* a, const uint64_t* b, uint64_t n
         const Mult f = make_mult(b[i]);
         switch (mulmod) {
             case NN_MULMOD_DEFAULT:
-            case NN_MULMOD_FP64: out[i] = VarFP64::to_u64(VarFP64::mul(VarFP64::load(a[i]), f)); break;
+            case NN_MULMOD_FP64: {
+                // both forms; 0, which no product of units is, where they differ
+                const uint64_t r = VarFP64::to_u64(VarFP64::mul(VarFP64::load(a[i]), f));
+                const uint64_t bal = VarBal::to_u64(VarBal::mul(VarBal::load(a[i]), make_bal(b[i])));
+                out[i] = r == bal ? r : 0;
+                break;
+            }
             case NN_DEBUG_DEVICE_MULMOD:
                 out[i] = (uint64_t)nn_dev_mulmod((double)a[i], nn_dev_mult{f.v, f.qh, f.ql});
                 break;

@@ -41,13 +41,14 @@ __device__ __forceinline__ void flat_start(uint64_t b, uint32_t l, int R, uint64
 }
 
 // XCD runs (see kFlatXcdRun): the chunk (or record) that workgroup w takes
-// when runs of kFlatXcds*kFlatXcdRun workgroups give XCD x = w mod kFlatXcds
-// the kFlatXcdRun consecutive ones [x kFlatXcdRun, (x + 1) kFlatXcdRun) of
-// its run.  A permutation of every whole run.
+// when runs of kFlatXcds*G workgroups give XCD x = w mod kFlatXcds the G
+// consecutive ones [x G, (x + 1) G) of its run.  A permutation of every whole
+// run.
+template <uint32_t G = kFlatXcdRun>
 __device__ __forceinline__ uint64_t xcd_run_index(uint64_t w) {
-    constexpr uint64_t run = (uint64_t)kFlatXcds * kFlatXcdRun;
+    constexpr uint64_t run = (uint64_t)kFlatXcds * G;
     const uint64_t r = w % run;
-    return w - r + (r % kFlatXcds) * kFlatXcdRun + r / kFlatXcds;
+    return w - r + (r % kFlatXcds) * G + r / kFlatXcds;
 }
 
 // The 64-bit pattern stored for a state: the state itself or its variate.

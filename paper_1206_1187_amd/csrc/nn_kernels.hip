@@ -12,7 +12,10 @@
 // Section 3.2.
 #include <hip/hip_runtime.h>
 
+#include <vector>
+
 #include "nn_device.hpp"
+#include "nn_host.hpp"
 
 namespace nn {
 
@@ -366,37 +369,59 @@ __global__ __launch_bounds__(1024) void k_fill(uint64_t* __restrict__ out, uint6
 // Its address is a link-time constant of the code, so a workgroup issues
 // its table loads at once instead of after the load of a table pointer
 // from its arguments.  Filled per device at set-up (upload_flat_symbol).
+// flat_bal: the same multipliers balanced.
 __device__ Mult flat_sym[kFlatSymEntries];
+__device__ BalMult flat_bal[kFlatSymEntries];
 
-// flat_start over flat_sym: the states of lane l's pair (outputs 2l and
+template <class V>
+__device__ __forceinline__ const typename V::M* flat_tab() {
+    if constexpr (std::is_same<typename V::M, BalMult>::value)
+        return flat_bal;
+    else
+        return flat_sym;
+}
+
+// flat_start over flat_tab: the states of lane l's pair (outputs 2l and
 // 2l + 1) of the chunk that begins u = b*R rows after the output whose state
 // is `base`.  b*R < kFlatMaxRowsPerLaunch.
 template <class V>
 __device__ __forceinline__ void flat_start_sym(uint64_t b, uint32_t l, int R, uint64_t base,
-                                               const Mult& M1, typename V::S& za,
+                                               const typename V::M& M1, typename V::S& za,
                                                typename V::S& zb) {
     const uint64_t u = b * (uint64_t)R;
-    const Mult hi = flat_sym[kFlatSymHi + u / kFlatLoSize];
-    const Mult lo = flat_sym[kFlatSymLo + u % kFlatLoSize];
-    const Mult lane = flat_sym[kFlatSymLane + l];
+    const typename V::M hi = flat_tab<V>()[kFlatSymHi + u / kFlatLoSize];
+    const typename V::M lo = flat_tab<V>()[kFlatSymLo + u % kFlatLoSize];
+    const typename V::M lane = flat_tab<V>()[kFlatSymLane + l];
     za = V::mul(V::mul(V::mul(V::load(base), hi), lo), lane);
     zb = V::mul(za, M1);
 }
 
 hipError_t upload_flat_symbol(const Mult* entries) {
+    std::vector<BalMult> bal;
+    for (uint32_t k = 0; k < kFlatSymEntries; ++k) bal.push_back(make_bal(entries[k].vi));
+    const hipError_t e =
+        hipMemcpyToSymbol(HIP_SYMBOL(flat_bal), bal.data(), sizeof(BalMult) * kFlatSymEntries, 0,
+                          hipMemcpyHostToDevice);
+    if (e != hipSuccess) return e;
     return hipMemcpyToSymbol(HIP_SYMBOL(flat_sym), entries, sizeof(Mult) * kFlatSymEntries, 0,
                              hipMemcpyHostToDevice);
 }
 
-// The chunk that workgroup w writes: w itself (G = 0), or its XCD-run
-// chunk (G = kFlatXcdRun, in launches of whole runs).
+// The chunk that workgroup w writes: w itself (G = 0), or its XCD-run chunk (runs
+// of G chunks per XCD, in launches of whole runs).
 template <int G>
 __device__ __forceinline__ uint64_t flat_chunk(uint64_t w) {
-    static_assert(G == 0 || G == (int)kFlatXcdRun, "XCD runs of kFlatXcdRun chunks");
     if constexpr (G == 0)
         return w;
     else
-        return xcd_run_index(w);
+        return xcd_run_index<G>(w);
+}
+// In a launch whose first `runs` chunks are in XCD runs.
+template <int R>
+__device__ __forceinline__ uint32_t flat_chunk_any(uint32_t w, uint32_t runs) {
+    if constexpr (flat_xcd_run(R) != 0)
+        if (w < runs) return (uint32_t)xcd_run_index<flat_xcd_run(R)>(w);
+    return w;
 }
 
 // Flat layout (see launch_generate_flat).  Workgroup w writes the R rows of
@@ -415,7 +440,8 @@ __device__ __forceinline__ uint64_t flat_chunk(uint64_t w) {
 template <class V, int KIND, bool NT, int R, int G>
 __global__ __launch_bounds__(kFlatBlock) void k_generate_flat(uint64_t base,
                                                               uint64_t* __restrict__ out,
-                                                              Mult M1, Mult J) {
+                                                              typename V::M M1,
+                                                              typename V::M J) {
     extern __shared__ char occupancy_cap[];  // dynamic LDS only limits residency
     (void)occupancy_cap;
     const uint64_t b = flat_chunk<G>(blockIdx.x);
@@ -448,15 +474,31 @@ __global__ __launch_bounds__(kFlatBlock) void k_generate_flat(uint64_t base,
 // until its arguments are there, which the whole-chunk kernel avoids: on whole
 // runs that one stays ahead (2^23 variates 11.7 against 12.1 us, 2^30 1187
 // against 1193).
+template <class V>
+__host__ __device__ __forceinline__ typename V::M flat_m1(const FlatArgs& a) {
+    if constexpr (std::is_same<typename V::M, BalMult>::value)
+        return a.bal_M1;
+    else
+        return a.M1;
+}
+template <class V>
+__host__ __device__ __forceinline__ typename V::M flat_j(const FlatArgs& a) {
+    if constexpr (std::is_same<typename V::M, BalMult>::value)
+        return a.bal_J;
+    else
+        return a.J;
+}
+
 template <class V, int KIND, bool NT, int R>
 __global__ __launch_bounds__(kFlatBlock) void k_generate_flat_any(FlatArgs a) {
     extern __shared__ char occupancy_cap[];
     (void)occupancy_cap;
     const uint32_t w = blockIdx.x;
-    const uint32_t b = R == 4 && w < a.runs ? (uint32_t)xcd_run_index(w) : w;
+    const uint32_t b = flat_chunk_any<R>(w, a.runs);
     const uint32_t l = threadIdx.x;
+    const typename V::M M1 = flat_m1<V>(a), J = flat_j<V>(a);
     typename V::S za, zb;
-    flat_start_sym<V>(b, l, R, a.base, a.M1, za, zb);
+    flat_start_sym<V>(b, l, R, a.base, M1, za, zb);
     const global_ptr<uint64_t> p = as_global(a.out) + ((uint64_t)kFlatPerBlock * R * b + 2u * l);
     if (b < a.full) {
 #pragma unroll
@@ -466,8 +508,8 @@ __global__ __launch_bounds__(kFlatBlock) void k_generate_flat_any(FlatArgs a) {
             v.y = out_bits<V, KIND>(zb);
             put<NT>(reinterpret_cast<global_ptr<u64x2>>(p + r * kFlatPerBlock), v);
             if (r + 1 < R) {
-                za = V::mul(za, a.J);
-                zb = V::mul(zb, a.J);
+                za = V::mul(za, J);
+                zb = V::mul(zb, J);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -482,8 +524,8 @@ __global__ __launch_bounds__(kFlatBlock) void k_generate_flat_any(FlatArgs a) {
             } else {
                 put<NT>(p + r * kFlatPerBlock, out_bits<V, KIND>(za));
             }
-            za = V::mul(za, a.J);
-            zb = V::mul(zb, a.J);
+            za = V::mul(za, J);
+            zb = V::mul(zb, J);
         }
     }
     if (w == 0 && a.head && l == 0)
@@ -536,7 +578,7 @@ __global__ __launch_bounds__(kFlatBlock) void k_fill_flat_any(FlatArgs a, uint64
     extern __shared__ char occupancy_cap[];
     (void)occupancy_cap;
     const uint32_t w = blockIdx.x;
-    const uint32_t b = R == 4 && w < a.runs ? (uint32_t)xcd_run_index(w) : w;
+    const uint32_t b = flat_chunk_any<R>(w, a.runs);
     const uint32_t l = threadIdx.x;
     const u64x2 v = fill_pair<R, START>(b, value);
     const global_ptr<uint64_t> p = as_global(a.out) + ((uint64_t)kFlatPerBlock * R * b + 2u * l);
@@ -571,15 +613,16 @@ static uint32_t flat_grid(const FlatArgs& a) {
 template <class V, int KIND, bool NT, int R>
 static hipError_t flat_one(uint32_t lds, hipStream_t s, const FlatArgs& a) {
     if (flat_whole(a)) {
-        if constexpr (R == 4) {
+        if constexpr (flat_xcd_run(R) != 0) {
             if (a.runs) {
-                hipLaunchKernelGGL((k_generate_flat<V, KIND, NT, R, kFlatXcdRun>), dim3(a.full),
-                                   dim3(kFlatBlock), lds, s, a.base, a.out, a.M1, a.J);
+                hipLaunchKernelGGL((k_generate_flat<V, KIND, NT, R, flat_xcd_run(R)>),
+                                   dim3(a.full), dim3(kFlatBlock), lds, s, a.base, a.out,
+                                   flat_m1<V>(a), flat_j<V>(a));
                 return hipGetLastError();
             }
         }
         hipLaunchKernelGGL((k_generate_flat<V, KIND, NT, R, 0>), dim3(a.full), dim3(kFlatBlock),
-                           lds, s, a.base, a.out, a.M1, a.J);
+                           lds, s, a.base, a.out, flat_m1<V>(a), flat_j<V>(a));
         return hipGetLastError();
     }
     hipLaunchKernelGGL((k_generate_flat_any<V, KIND, NT, R>), dim3(flat_grid(a)), dim3(kFlatBlock),
@@ -587,11 +630,21 @@ static hipError_t flat_one(uint32_t lds, hipStream_t s, const FlatArgs& a) {
     return hipGetLastError();
 }
 
+// Chunks of two rows take the FP64 reduction's balanced form (kFlatFastRows).
+template <class V>
+struct TwoRows {
+    typedef V T;
+};
+template <>
+struct TwoRows<VarFP64> {
+    typedef VarBal T;
+};
+
 template <class V, int KIND, bool NT>
 static hipError_t flat_r(int rows, uint32_t lds, hipStream_t s, const FlatArgs& a) {
     switch (rows) {
         case 1: return flat_one<V, KIND, NT, 1>(lds, s, a);
-        case 2: return flat_one<V, KIND, NT, 2>(lds, s, a);
+        case 2: return flat_one<typename TwoRows<V>::T, KIND, NT, 2>(lds, s, a);
         case 4: return flat_one<V, KIND, NT, 4>(lds, s, a);
         case 8: return flat_one<V, KIND, NT, 8>(lds, s, a);
         case 16: return flat_one<V, KIND, NT, 16>(lds, s, a);
@@ -621,9 +674,9 @@ hipError_t launch_generate_flat(int mulmod, int kind, bool nt, int rows, uint32_
 template <bool NT, int R, bool START>
 static hipError_t fill_flat_one(uint32_t lds, hipStream_t s, const FlatArgs& a, uint64_t value) {
     if (flat_whole(a)) {
-        if constexpr (R == 4) {
+        if constexpr (flat_xcd_run(R) != 0) {
             if (a.runs) {
-                hipLaunchKernelGGL((k_fill_flat<NT, R, START, kFlatXcdRun>), dim3(a.full),
+                hipLaunchKernelGGL((k_fill_flat<NT, R, START, flat_xcd_run(R)>), dim3(a.full),
                                    dim3(kFlatBlock), lds, s, a.out, value);
                 return hipGetLastError();
             }

@@ -111,6 +111,22 @@ constexpr uint32_t kFlatMaxRows = 16;
 // cfg field without NN_CFG_FLAT (below, a cfg that sets one means the rows).
 constexpr uint64_t kFlatUnalignedMin = 1ull << 22;
 constexpr uint32_t kFlatDefaultRows = 4;
+// The shape without a cfg (FP64 reduction, temporal stores, XCD runs): two rows of
+// balanced states at 5 (f64) or 6 (u64) workgroups per CU.  As at modulus 3^40,
+// what bounds these kernels is how their stores are spaced: the shorter step needs
+// shorter chunks.  Against four rows at 4 with the longer step, f64: 67,108,869
+// outputs 79.2 against 81.6 us, 100,000,007 115.9 against 119.5, 2^29 - 1 593 against
+// 605; u64: 159,912,993 181 against 188, 2^28 302 against 310, 2^30 1177 against 1229
+// (7.30 TB/s).  Other mixes write slower (2^30, f64, the shorter step with four
+// rows at 4 and 3: 1228 and 1187; the longer one with two rows at 6: 1392; two rows
+// at 6 without runs 1215).  Below 2^24 outputs, which the last-level cache takes,
+// four rows tie or are ahead (3,000,017 f64 6.0 against 6.2).  From 2^29 f64 outputs
+// on the four rows that nn_default_cfg documents for them stay (2^30: 1193; two
+// rows at 5, as a cfg, 1173).
+constexpr uint32_t kFlatFastRows = 2;
+inline uint32_t flat_fast_occupancy(int kind) { return kind == 1 ? 5u : 6u; }
+constexpr uint64_t kFlatFastMin = 1ull << 24;
+constexpr uint64_t kFlatFastMaxF64 = 1ull << 29;
 constexpr uint32_t kFlatDefaultOccupancy = 4;
 
 // The flat kernels' own copy of their multipliers (a static device array):
@@ -130,11 +146,16 @@ hipError_t upload_flat_symbol(const Mult* entries);
 // chunks beyond the last full run keep workgroup order.
 constexpr uint32_t kFlatXcds = 8;
 constexpr uint32_t kFlatXcdRun = 256;
-// Whole chunks of a flat launch that go to the XCD-run kernel (runs: the
-// launch takes XCD runs at all).
+// Chunks of two rows take runs of as many bytes.  The chunks per XCD of a run, 0
+// for row counts without runs:
+constexpr uint32_t flat_xcd_run(int rows) {
+    return rows == 2 || rows == 4 ? kFlatXcdRun * 4 / rows : 0;
+}
+// Whole chunks of a flat launch that are taken in XCD runs (runs: the launch takes
+// any).
 inline uint64_t flat_run_chunks(int rows, bool runs, uint64_t whole_chunks) {
-    const uint64_t run = (uint64_t)kFlatXcds * kFlatXcdRun;
-    return rows == 4 && runs ? whole_chunks / run * run : 0;
+    const uint64_t run = (uint64_t)kFlatXcds * flat_xcd_run(rows);
+    return run && runs ? whole_chunks / run * run : 0;
 }
 
 // One launch writes all of it: the whole chunks, the partial last one and,
@@ -149,6 +170,7 @@ struct FlatArgs {
     uint64_t head_state;
     Mult M1;         // 2^53
     Mult J;          // (2^53)^kFlatPerBlock: the next row of a lane
+    BalMult bal_M1, bal_J;  // both balanced
 };
 
 // rows: rows per workgroup (1, 2, 4, 8, 16); lds_bytes > 0 caps the

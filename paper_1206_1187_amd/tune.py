@@ -63,11 +63,11 @@ def _lookup(form, kind, size, path=CACHE):
 #: output kind (make_cfg keyword arguments).  The full-size GPU parity tests
 #: run exactly these, so the timed kernels are the compared ones.
 BENCH_PLAIN = {
-    "f64": dict(layout="flat", mulmod="fp64", unroll=4, occupancy=4, temporal=True),
-    # raw states: the FP64 reduction too (the library default and the
-    # autotuner's pick with the chunks in XCD runs; Shoup's, which keeps the
-    # state an integer, ties or trails by 1-2 % there)
-    "u64": dict(layout="flat", mulmod="fp64", unroll=4, occupancy=4, temporal=True),
+    "f64": dict(layout="flat", mulmod="fp64", unroll=2, occupancy=5, temporal=True),
+    # raw states: the FP64 reduction too (the autotuner's pick at 2^28 outputs;
+    # Shoup's, which keeps the state an integer, ties with four rows and trails
+    # the balanced states of two)
+    "u64": dict(layout="flat", mulmod="fp64", unroll=2, occupancy=5, temporal=True),
 }
 
 

@@ -159,12 +159,12 @@ def test_output_alignment():
 @pytest.mark.parametrize("head", [0, 1])
 def test_flat_remainders_in_one_launch(rows, head):
     """Partial chunks at their edges (one output, a row, one short of a
-    chunk), alone, after a few chunks and, with four rows, after a whole XCD
-    run, with and without the head element of an output that is only 8-byte
+    chunk), alone, after a few chunks and, with two and four rows, after a whole
+    XCD run, with and without the head element of an output that is only 8-byte
     aligned; the fill, with and without the generator's start, likewise."""
     z0 = orc.seed(wl.INDEX_MIN + 7)
     per = 512 * rows
-    wholes = [0, 3] + ([2048, 2049] if rows == 4 else [])
+    wholes = [0, 3] + {2: [4096, 4097], 4: [2048, 2049]}.get(rows, [])
     top = wholes[-1] * per + max(per, 514) + 1  # the largest count below
     ref, _ = orc.gen(z0, top, "u64", threads=0)
     for whole in wholes:
@@ -185,6 +185,20 @@ def test_flat_remainders_in_one_launch(rows, head):
                 h = _bits(buf)
                 assert (h[:at] == SENTINEL).all() and (h[at + count:] == SENTINEL).all()
                 assert (h[at:at + count] == 0x3FF0000000000001).all(), (rows, whole, rest, head)
+
+
+@pytest.mark.parametrize("kind", ["f64", "u64"])
+@pytest.mark.parametrize("count", [(1 << 24) - 1, 1 << 24, (1 << 24) + 1025])
+def test_default_shape_on_both_sides_of_its_sizes(kind, count):
+    """Without a cfg: four rows below 2^24 outputs, two rows of balanced states
+    from there on (whole XCD runs, and runs with chunks and a tail after them),
+    on 16- and 8-byte aligned outputs."""
+    z0 = orc.seed(wl.INDEX_MIN + 31)
+    ref, zr = orc.gen(z0, count, kind, threads=0)
+    for guard in (512, 513):
+        got, zn = _gen_guarded(z0, count, kind, guard=guard)
+        assert np.array_equal(got, ref.view(np.uint64)), guard
+        assert zn == zr
 
 
 @pytest.mark.parametrize("variant", VARIANTS)
