@@ -295,8 +295,8 @@ def main():
     out_f = torch.empty(case.count_f64, dtype=torch.float64, device="cuda")
     out_u = torch.empty(case.count_u64, dtype=torch.uint64, device="cuda")
     # Both kinds in the launch configuration tune.BENCH_PLAIN names (the
-    # flat layout: chunks of four 512-output rows per workgroup, temporal
-    # stores, residency cap 4), the one the full-size parity tests compare.
+    # flat layout: chunks of two 512-output rows per workgroup, temporal
+    # stores, residency cap 5), the one the full-size parity tests compare.
     from paper_1206_1187_amd import tune
     cfg_f = tune.bench_plain_cfg("f64")
     cfg_u = tune.bench_plain_cfg("u64")
@@ -365,8 +365,8 @@ def main():
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBPS,
             "traffic": traffic_from_profile(),
-            "kernel": "k_generate_flat<VarFP64, 1, false, 4, 256> (f64, flat: 4 rows of 512 per "
-                      "workgroup in XCD runs of 256 chunks, temporal stores, residency cap 4)",
+            "kernel": "k_generate_flat<VarBal, 1, false, 2, 512> (f64, flat: 2 rows of 512 per "
+                      "workgroup in XCD runs of 512 chunks, temporal stores, residency cap 5)",
             "algorithmic_bytes_per_launch": 8 * case.count_f64,
         },
     }
