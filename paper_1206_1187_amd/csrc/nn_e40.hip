@@ -512,7 +512,7 @@ hipError_t launch(int kind, int mm, int ilp, int unroll, bool nt, uint32_t grid,
 // XCD runs): rows of 512 per chunk and resident workgroups per CU.  What bounds
 // it is how the stores of a workgroup are spaced, more than the arithmetic: with
 // the 15-instruction step 16 rows at 4 write slower than with 20 instructions,
-// and other shapes faster.  Medians over two boxes, 2^28 and 100,000,007 outputs:
+// and other shapes faster.  Medians over two machines, 2^28 and 100,000,007 outputs:
 //   f64 (25.8 VALU instructions an output): 8 rows at 3 311 and 122 us; 16 at 4
 //     355 and 137; 8 at 4 333 and 130; 8 at 2 with non-temporal stores 306 and 118,
 //     but 43.1 against 39.6 at 2^25 (two limbs of 3^20, 30.3 an output, 16 at 4: 335
