@@ -200,7 +200,9 @@ int nn_default_cfg(int kind, uint64_t count, nn_launch_cfg *cfg_out);
  * z_1..z_count modulo 2^64 (exact, independent of the launch shape); for
  * NN_OUT_F64 the binary64 sum of the variates (summation order depends on
  * the launch shape).  Sets *state to z_count.  cfg: block, grid and mulmod
- * only (NULL for the defaults).  Asynchronous on `stream`. */
+ * only (NULL for the defaults); a grid without a block runs 1024 threads per
+ * workgroup, above 16384 workgroups 256; grid * block is at most 2^24.
+ * Asynchronous on `stream`. */
 int nn_consume(uint64_t *state, uint64_t count, int kind, void *result_dev, void *stream,
                const nn_launch_cfg *cfg);
 /* nn_consume_set -- nn_consume into a value the caller need not initialise:

@@ -438,7 +438,11 @@ int consume(uint64_t* state, uint64_t count, int kind, void* result_dev, void* s
     if (c.flags || c.occupancy || (c.width && c.width != 2) || (c.ilp && c.ilp != 2) || c.unroll)
         return fail(NN_EINVAL, "nn_consume takes block, grid and mulmod only");
     const KindDefaults& kd = kind_defaults(NN_OUT_F64);
-    const uint32_t block = c.block ? c.block : kConsumeBlock;
+    // A grid without a block keeps the blocks within kMaxThreads: grids of up to
+    // 65536 workgroups take 256 threads, as they did before the larger default.
+    const uint32_t block = c.block                                          ? c.block
+                           : (uint64_t)c.grid * kConsumeBlock > kMaxThreads ? kDefaultBlock
+                                                                            : kConsumeBlock;
     if (block < 64 || block > 1024 || block % 64)
         return fail(NN_EINVAL, "block %u: must be a multiple of 64 in [64, 1024]", block);
     const uint32_t mulmod = c.mulmod ? c.mulmod : kd.mulmod;

@@ -563,6 +563,29 @@ def test_fused_consumer_balanced_edges(block, grid):
             assert abs(float(resf.cpu()[0]) - exact) <= (count + 1) * 2.0 ** -53 * exact, count
 
 
+@pytest.mark.parametrize("mulmod", ["fp64", "shoup"])
+@pytest.mark.parametrize("grid", [16384, 16385, 65536, 65537])
+def test_fused_consumer_grids_without_a_block(grid, mulmod):
+    """A grid alone is taken up to 65536 workgroups (2^24 threads of the smaller
+    blocks), on both sides of 16384 (2^24 threads of the larger ones), and
+    refused above."""
+    z0 = orc.seed(wl.INDEX_MIN + 21)
+    count = 40_001
+    cfg = nn.make_cfg(grid=grid, mulmod=mulmod)
+    if grid > 65536:
+        with pytest.raises(nn.NNError):
+            nn.consume(z0, count, "u64", cfg=cfg)
+        return
+    ref, zr = orc.gen(z0, count, "u64", threads=0)
+    res, zn = nn.consume(z0, count, "u64", cfg=cfg)
+    resf, _ = nn.consume(z0, count, "f64", cfg=cfg)
+    assert zn == zr
+    got = int(res.view(torch.int64).cpu().numpy().view(np.uint64)[0])
+    assert got == int(ref.sum(dtype=np.uint64))
+    exact = want_f64(ref)
+    assert abs(resf.item() - exact) <= (count + 1) * 2.0 ** -53 * exact
+
+
 def test_consecutive_layout_bit_exact():
     """The consecutive layout (the paper's per-thread loop with the Modified
     Barrett step, serial order restored through LDS): tile sizes from 2 to
