@@ -454,8 +454,7 @@ int consume(uint64_t* state, uint64_t count, int kind, void* result_dev, void* s
         grid = 1;
     } else if (!grid) {
         const uint64_t need = (count - 1) / (kConsumeMinRows * block) + 1;
-        const uint64_t cap = (uint64_t)(d->cus > 0 ? d->cus : 1) * kConsumeBlock / block *
-                             (count >= kConsumeTwoPerCu ? 2 : 1);
+        const uint64_t cap = (uint64_t)(d->cus > 0 ? d->cus : 1) * consume_per_cu(block, count);
         grid = (uint32_t)(need < cap ? need : cap);
     }
     if ((uint64_t)grid * block > kMaxThreads)

@@ -65,10 +65,20 @@ struct ConsumeArgs {
 // compute unit, and a thread has at least kConsumeMinRows outputs.  From
 // kConsumeTwoPerCu outputs on two per compute unit hide more latency than
 // their atomics cost (2^28 variates: 66.4 against 69.2 us; 10,000,019: 11.2
-// against 9.2).
+// against 9.2).  A caller's smaller blocks fill a compute unit likewise, but
+// below kConsumeTwoPerCu outputs with kConsumeMaxPerCu at most: more of them
+// wait for their atomics (64 threads, 10,000,019 variates: 19.2 us with 4, 29.8
+// with 8, 53.3 with 16; 2^26: 43.4, 44.1 and 62.5).  From kConsumeTwoPerCu on
+// the unit is filled twice, as with the default's (2^30: 255 against 410 us).
 constexpr uint32_t kConsumeBlock = 1024;
 constexpr uint64_t kConsumeMinRows = 8;
 constexpr uint64_t kConsumeTwoPerCu = 1ull << 27;
+constexpr uint32_t kConsumeMaxPerCu = 4;
+inline uint32_t consume_per_cu(uint32_t block, uint64_t count) {
+    const uint32_t fill = kConsumeBlock / block;  // block <= kConsumeBlock
+    if (count >= kConsumeTwoPerCu) return 2 * fill;
+    return fill < kConsumeMaxPerCu ? fill : kConsumeMaxPerCu;
+}
 
 // Outputs up to which a call that sets the result takes one workgroup, which
 // stores its sum: at most 32 rows a thread, where the kernel takes 5.1 us
