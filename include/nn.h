@@ -283,9 +283,11 @@ typedef struct nn_stream_desc {
  * copy and a kernel launch instead of replaying the plan's graph),
  * NN_BATCH_INTERLEAVED, NN_BATCH_CHUNKS.  A cfg that names no kernel (neither
  * of those two, block, grid and cluster 0, mulmod 0 or NN_MULMOD_FP64) gets
- * the chunked one, with non-temporal stores at an occupancy of 3; occupancy: NN_BATCH_CHUNKS only, 0 (4) or a cap in
- * [2,16] on the chunk kernel's resident workgroups per compute unit (as
- * nn_launch_cfg's occupancy caps the plain flat layout's). */
+ * the chunked one, with non-temporal stores at an occupancy of 3, if
+ * max_outputs / 2048 + 2 per descriptor of the plan (see below) stays under
+ * 2^24, and the blocked one on larger plans; occupancy: NN_BATCH_CHUNKS only,
+ * 0 (4) or a cap in [2,16] on the chunk kernel's resident workgroups per
+ * compute unit (as nn_launch_cfg's occupancy caps the plain flat layout's). */
 typedef struct nn_batch_cfg {
     uint32_t block;
     uint32_t grid;

@@ -178,6 +178,25 @@ inline bool chunks_dense(uint64_t chunks, uint64_t windows) {
 // Residency of a plan that names no kernel (non-temporal stores): 3 workgroups
 // per CU write the 10,000-window batch at 6.72 TB/s, 4 at 6.62.
 constexpr uint32_t kChunkImpliedOccupancy = 3;
+// Workgroups that a launch of 256 threads may have: the runtime counts the
+// threads of a launch in 32 bits (2^24 workgroups are refused; of 2^24 + 5 five
+// would run).  Longer batches take the records round-robin.
+constexpr uint64_t kMaxChunkGrid = (1ull << 24) - 1;
+inline uint32_t chunk_grid(uint64_t records) {
+    return (uint32_t)(records < kMaxChunkGrid ? records : kMaxChunkGrid);
+}
+// A plan that names no kernel takes the chunked one only while its records (16
+// bytes each in two slots) are few enough for a launch of a workgroup each:
+// 512 MiB at most, for nearly 2^35 outputs, what the card's memory can hold, or
+// nearly 2^23 streams.  A larger capacity ("no limit") keeps the blocked kernel,
+// which holds nothing for the outputs: 2^45 outputs as chunks would be 550 GB of
+// records.
+inline uint64_t chunk_records(uint64_t max_outputs, uint64_t cap_desc) {
+    return max_outputs / kChunkOuts + 2 * cap_desc;
+}
+inline bool chunks_implied(uint64_t max_outputs, uint64_t cap_desc) {
+    return chunk_records(max_outputs, cap_desc) <= kMaxChunkGrid;
+}
 // Chunks from which a batch's pre-pass goes to the plan's side stream, beside
 // the previous batch's chunk kernel: back to back 10,000 windows of 1,320,000
 // chunks take 3035 against 3043 us, 9999 of 364,000 870 against 878-903.  A batch

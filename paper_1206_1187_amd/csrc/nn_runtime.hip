@@ -345,9 +345,12 @@ int plan_create(int kind, uint32_t max_streams, uint64_t max_outputs, const nn_b
     if (c.flags &
         ~(NN_CFG_TEMPORAL_STORES | NN_BATCH_NO_GRAPH | NN_BATCH_INTERLEAVED | NN_BATCH_CHUNKS))
         return fail(NN_EINVAL, "unknown batch flags 0x%x", c.flags);
-    // A cfg that asks for no kernel gets the chunked one (see below).
+    // Direct batches split streams into pieces of at most kBatchMaxLen.
+    const uint64_t cap_desc = (uint64_t)max_streams + (indexed ? 0 : max_outputs / kBatchMaxLen + 1);
+    // A cfg that asks for no kernel gets the chunked one.
     const bool implied = !(c.flags & (NN_BATCH_CHUNKS | NN_BATCH_INTERLEAVED)) && !c.block &&
-                         !c.grid && !c.cluster && (!c.mulmod || c.mulmod == NN_MULMOD_FP64);
+                         !c.grid && !c.cluster && (!c.mulmod || c.mulmod == NN_MULMOD_FP64) &&
+                         chunks_implied(max_outputs, cap_desc);
     const bool chunks = (c.flags & NN_BATCH_CHUNKS) != 0 || implied;
     if (chunks && (c.flags & NN_BATCH_INTERLEAVED))
         return fail(NN_EINVAL, "NN_BATCH_CHUNKS and NN_BATCH_INTERLEAVED are exclusive");
@@ -384,8 +387,6 @@ int plan_create(int kind, uint32_t max_streams, uint64_t max_outputs, const nn_b
     if (interleaved && !c.cluster) cluster = grid;  // one range: all workgroups interleave
     if (grid > (1u << 20)) return fail(NN_EINVAL, "grid %u too large", grid);
     if (grid % cluster) return fail(NN_EINVAL, "grid %u is not a multiple of cluster %u", grid, cluster);
-    // Direct batches split streams into pieces of at most kBatchMaxLen.
-    const uint64_t cap_desc = (uint64_t)max_streams + (indexed ? 0 : max_outputs / kBatchMaxLen + 1);
     if (cap_desc > 0xffffffffull) return fail(NN_ERANGE, "batch capacity too large");
 
     nn_batch_plan* p = new (std::nothrow) nn_batch_plan();
@@ -407,7 +408,8 @@ int plan_create(int kind, uint32_t max_streams, uint64_t max_outputs, const nn_b
                     "block 64, 128 or 256");
     }
     p->cluster = cluster;
-    p->cap_rows = max_outputs / (chunks ? (uint64_t)kChunkOuts : 2ull * block) + 2 * cap_desc;
+    p->cap_rows = chunks ? chunk_records(max_outputs, cap_desc)
+                         : max_outputs / (2ull * block) + 2 * cap_desc;
     p->map_grid = (uint32_t)(d->cus > 0 ? d->cus * 4 : 64);
     p->max_streams = max_streams;
     p->max_outputs = max_outputs;
@@ -647,15 +649,16 @@ int plan_launch_staged(nn_batch_plan* p, uint32_t nd, void* out, hipStream_t str
         const bool side = p->side && rows >= kOverlapChunks;
         q.args.JR = wide ? p->JR256 : p->JR64;
         e = hipLaunchKernel(batch_rec_kernel(p->indexed, !wide),
-                            dim3(wide ? rec_grid : (nd + 3) / 4), dim3(256), params, 0,
+                            dim3(wide ? rec_grid : chunk_grid(((uint64_t)nd + 3) / 4)), dim3(256),
+                            params, 0,
                             side ? p->side : stream);
         if (e == hipSuccess && side) e = hipEventRecord(q.ready, p->side);
         if (e == hipSuccess && side) e = hipStreamWaitEvent(stream, q.ready, 0);
-        // one workgroup per record unless the plan fixed a grid
+        // one workgroup per record unless the plan fixed a grid (or they are too many)
         if (e == hipSuccess)
             e = hipLaunchKernel(batch_chunks_kernel(p->kind, p->nontemporal,
                                                     owned && chunks_dense(rows, nd)),
-                                dim3(p->grid ? p->grid : (uint32_t)rows), dim3(kFlatBlock), params,
+                                dim3(p->grid ? p->grid : chunk_grid(rows)), dim3(kFlatBlock), params,
                                 p->flat_lds, stream);
         return batch_launched(p, e, stream);
     }

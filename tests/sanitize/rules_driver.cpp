@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <stdio.h>
 
+#include "nn_batch.hpp"
 #include "nn_kernels.hpp"
 
 static int fails = 0;
@@ -34,8 +35,32 @@ static void consume_workgroups() {
     CHECK(nn::consume_per_cu(1024, 1) == 1 && nn::consume_per_cu(1024, 1ull << 27) == 2);
 }
 
+// Plans that name no kernel: a workgroup per record fits one launch, whose
+// threads are counted in 32 bits, and the records of both slots stay within 512
+// MiB; every launch of the chunked kernels fits as well.
+static void batch_capacity() {
+    const uint64_t outs[] = {0, 2047, 2048, 1ull << 32, (1ull << 35) - (1 << 16), 1ull << 35,
+                             1ull << 40, 1ull << 45};
+    const uint64_t descs[] = {1, 10000, 1ull << 22, (1ull << 23) - 1, 1ull << 23, 0xffffffffull};
+    for (uint64_t o : outs)
+        for (uint64_t d : descs)
+            if (nn::chunks_implied(o, d)) {
+                CHECK(nn::chunk_records(o, d) * 256 < 1ull << 32);
+                CHECK(nn::chunk_records(o, d) * 2 * sizeof(nn::RowRec) < 1ull << 29);
+            }
+    CHECK(nn::chunks_implied(1ull << 32, 10000 + 257));
+    CHECK(!nn::chunks_implied(1ull << 40, 1) && !nn::chunks_implied(1ull << 45, 1));
+    CHECK(!nn::chunks_implied(1, 1ull << 23));
+    for (uint64_t r : {1ull, 2ull, (1ull << 24) - 1, 1ull << 24, (1ull << 24) + 5, 1ull << 33}) {
+        CHECK(nn::chunk_grid(r) >= 1 && nn::chunk_grid(r) <= r);
+        CHECK((uint64_t)nn::chunk_grid(r) * 256 < 1ull << 32);
+        CHECK(r >= 1ull << 24 || nn::chunk_grid(r) == r);
+    }
+}
+
 int main() {
     consume_workgroups();
+    batch_capacity();
     if (fails) {
         fprintf(stderr, "%d check(s) failed\n", fails);
         return 1;

@@ -281,6 +281,31 @@ def test_chunked_batch_long_windows_back_to_back():
                 assert np.array_equal(flat[o:o + 700].cpu().numpy().view(np.uint64), ref), (i, at)
 
 
+def test_plan_capacities_without_a_limit():
+    """A plan and a server whose capacity is "no limit": no chunk records are
+    set aside for it (2^45 outputs would need 550 GB, a server's 2^40 17 GB a
+    lane), and batches come out as on any plan."""
+    from paper_1206_1187_amd import serve
+    n = 40
+    states, lengths, offsets, total = _mixed_batch(71, [1 + 997 * i for i in range(n)])
+    with nn.BatchPlan("u64", n, 1 << 45) as plan:
+        for m in (n, 3):
+            buf = _sentinel(total)
+            plan.generate(states[:m], lengths[:m], offsets[:m], buf.view(torch.uint64))
+            torch.cuda.synchronize()
+            _check_batch(_bits(buf), states[:m], lengths[:m], offsets[:m], "u64")
+    free = torch.cuda.mem_get_info()[0]
+    with serve.Server(states.tolist(), 1 << 20, kind="u64", max_batch_outputs=1 << 40) as srv:
+        assert free - torch.cuda.mem_get_info()[0] < 1 << 30
+        t = srv.submit(3, 5000)
+        done = []
+        while not done:
+            done = srv.poll()
+        assert done[0].ticket == t
+        got = srv.data(done[0]).view(torch.int64).cpu().numpy().view(np.uint64)
+        assert np.array_equal(got, orc.gen(int(states[3]), 5000, "u64")[0])
+
+
 def test_chunked_batch_validation():
     for bad in (dict(block=128), dict(cluster=4), dict(mulmod="shoup"), dict(interleaved=True)):
         with pytest.raises(nn.NNError):
