@@ -346,7 +346,9 @@ typedef struct nn_batch_plan nn_batch_plan;
  * Errors: NN_EINVAL (kind, cfg), NN_ERANGE (capacity), NN_ENOMEM, NN_EHIP. */
 int nn_batch_plan_create(int kind, uint32_t max_streams, uint64_t max_outputs,
                          const nn_batch_cfg *cfg, nn_batch_plan **plan_out);
-/* Waits for the plan's last batch, then frees it (NULL is a no-op). */
+/* Waits for the plan's batches (and whatever else its device is running), then
+ * frees it (NULL is a no-op).  Any device may be current.  NN_EHIP if the wait
+ * failed. */
 int nn_batch_plan_destroy(nn_batch_plan *plan);
 /* The plan's resolved configuration. */
 int nn_batch_plan_cfg(const nn_batch_plan *plan, nn_batch_cfg *cfg_out);

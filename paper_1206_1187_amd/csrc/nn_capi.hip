@@ -545,8 +545,9 @@ int nn_batch_plan_create(int kind, uint32_t max_streams, uint64_t max_outputs,
 }
 
 int nn_batch_plan_destroy(nn_batch_plan* plan) {
-    if (plan) plan_release(plan);
-    return ok();
+    const hipError_t e = plan ? plan_release(plan) : hipSuccess;
+    return e == hipSuccess ? ok()
+                           : fail(NN_EHIP, "waiting for the plan's batches: %s", hipGetErrorString(e));
 }
 
 int nn_batch_plan_cfg(const nn_batch_plan* plan, nn_batch_cfg* cfg_out) {
@@ -617,7 +618,6 @@ int nn_generate_batch(nn_batch_plan* plan, const nn_stream_desc* descs, uint32_t
                 launch_flat_inline(plan->kind, plan->nontemporal, plan->flat_lds, plan->tabs,
                                    nullptr, few, nd, out_dev, (hipStream_t)stream);
             if (e != hipSuccess) return fail(NN_EHIP, "batch launch: %s", hipGetErrorString(e));
-            plan->unslotted = true;
             if (final_states)
                 for (uint32_t i = 0; i < n; ++i)
                     final_states[i] = h_skip(descs[i].state, descs[i].length);

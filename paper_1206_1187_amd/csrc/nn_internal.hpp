@@ -93,7 +93,6 @@ struct nn_batch_plan {
     char* pinned = nullptr;           // both slots' staging
     nn_batch_slot slot[2];
     int next = 0;  // the slot of the next batch
-    bool unslotted = false;  // a batch ran without a slot (and its event)
 };
 
 namespace nn {
@@ -105,7 +104,9 @@ namespace nn {
 int plan_create(int kind, uint32_t max_streams, uint64_t max_outputs, const nn_batch_cfg* cfg,
                 bool indexed, const uint64_t* states, const uint64_t* host_states,
                 nn_batch_plan** out);
-void plan_release(nn_batch_plan* p);
+// Waits for the plan's device, whichever is current, and frees the plan; returns
+// the wait's status.
+hipError_t plan_release(nn_batch_plan* p);
 
 // Waits until the next batch's slot is free (the batch before the previous
 // one has finished).

@@ -220,14 +220,15 @@ int current_device(DeviceTables** out) {
 
 // ---------------------------------------------------------------- plans --
 
-void plan_release(nn_batch_plan* p) {
-    if (p->unslotted) (void)hipDeviceSynchronize();
-    if (p->side) (void)hipStreamSynchronize(p->side);
+hipError_t plan_release(nn_batch_plan* p) {
+    int prev = p->device;
+    (void)hipGetDevice(&prev);
+    if (prev != p->device) (void)hipSetDevice(p->device);
+    // Waits for the whole device, which freeing its memory below does in any
+    // case (hipFree): that covers a batch without a slot, which has no event.
+    const hipError_t waited = hipDeviceSynchronize();
     for (nn_batch_slot& q : p->slot) {
-        if (q.done) {
-            (void)hipEventSynchronize(q.done);
-            (void)hipEventDestroy(q.done);
-        }
+        if (q.done) (void)hipEventDestroy(q.done);
         if (q.ready) (void)hipEventDestroy(q.ready);
         if (q.exec) (void)hipGraphExecDestroy(q.exec);
         if (q.graph) (void)hipGraphDestroy(q.graph);
@@ -237,7 +238,9 @@ void plan_release(nn_batch_plan* p) {
     if (p->side) (void)hipStreamDestroy(p->side);
     if (p->chunk_mem) (void)hipFree(p->chunk_mem);
     if (p->pinned) (void)hipHostFree(p->pinned);
+    if (prev != p->device) (void)hipSetDevice(prev);
     delete p;
+    return waited;
 }
 
 namespace {
@@ -403,7 +406,7 @@ int plan_create(int kind, uint32_t max_streams, uint64_t max_outputs, const nn_b
     p->chunks = chunks;
     if (p->interleaved &&
         (mulmod != NN_MULMOD_FP64 || (block & (block - 1)) || block > 256)) {
-        plan_release(p);
+        (void)plan_release(p);
         return fail(NN_EINVAL, "the interleaved batch kernel needs the FP64 reduction and "
                     "block 64, 128 or 256");
     }
@@ -426,7 +429,7 @@ int plan_create(int kind, uint32_t max_streams, uint64_t max_outputs, const nn_b
         // default priority; non-blocking, so it does not wait for the null stream
         hipError_t e = hipStreamCreateWithFlags(&p->side, hipStreamNonBlocking);
         if (e != hipSuccess) {
-            plan_release(p);
+            (void)plan_release(p);
             return fail(NN_EHIP, "batch side stream: %s", hipGetErrorString(e));
         }
     }
@@ -435,7 +438,7 @@ int plan_create(int kind, uint32_t max_streams, uint64_t max_outputs, const nn_b
     for (nn_batch_slot& q : p->slot) {
         st = slot_create(p, q, *d, states);
         if (st) {
-            plan_release(p);
+            (void)plan_release(p);
             return st;
         }
     }

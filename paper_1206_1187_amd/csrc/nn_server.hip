@@ -165,7 +165,7 @@ constexpr uint32_t kDefaultLanes = 2;
 void server_free(nn_server* s) {
     if (s->dq) queue_destroy(s->dq);  // before the pool and the state table
     for (Lane& l : s->lanes) {
-        if (l.plan) plan_release(l.plan);
+        if (l.plan) (void)plan_release(l.plan);
         if (l.stream) (void)hipStreamDestroy(l.stream);
     }
     if (s->fake) {

@@ -306,6 +306,33 @@ def test_plan_capacities_without_a_limit():
         assert np.array_equal(got, orc.gen(int(states[3]), 5000, "u64")[0])
 
 
+@pytest.mark.parametrize("device", [0, 1])
+def test_destroy_waits_for_every_batch(device):
+    """Batches of few windows (without a slot) and of many, on two streams
+    behind long work: both are finished when the plan is destroyed, also with
+    another device current."""
+    if device >= torch.cuda.device_count():
+        pytest.skip("one device")
+    long = torch.empty(1 << 28, dtype=torch.float64, device="cuda:0")
+    states, lengths, offsets, total = _mixed_batch(72, [700] * 200)
+    outs = [_sentinel(total) for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    events = [torch.cuda.Event() for _ in range(2)]
+    torch.cuda.synchronize()
+    plan = nn.BatchPlan("u64", 200, total)
+    for stream, event, out, m in zip(streams, events, outs, (20, 200)):
+        for _ in range(20):  # about 6 ms
+            nn.generate_into(int(states[0]), long, stream=stream)
+        plan.generate(states[:m], lengths[:m], offsets[:m], out.view(torch.uint64), stream=stream)
+        event.record(stream)
+    with torch.cuda.device(device):
+        plan.close()
+        assert torch.cuda.current_device() == device
+    assert all(e.query() for e in events)
+    for out, m in zip(outs, (20, 200)):
+        _check_batch(_bits(out), states[:m], lengths[:m], offsets[:m], "u64")
+
+
 def test_chunked_batch_validation():
     for bad in (dict(block=128), dict(cluster=4), dict(mulmod="shoup"), dict(interleaved=True)):
         with pytest.raises(nn.NNError):
