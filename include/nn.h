@@ -313,10 +313,10 @@ typedef struct nn_batch_cfg {
  * writes the chunks' records (the state of the chunk's first element as if
  * the window covered it, and the window's part of the chunk), and
  * 256-thread workgroups write the records' chunks as four rows of 512
- * outputs with one 16-byte store per lane and row.  The plan sorts the
- * windows by output offset (they are independent) and gives each chunk one
- * record and one workgroup, which writes every window's part of it; windows
- * that overlap each other get a record per chunk and window instead.
+ * outputs with one 16-byte store per lane and row.  Windows in output order
+ * give each chunk one record and one workgroup, which writes every window's
+ * part of it; others (out of order, or overlapping each other) get a record per
+ * chunk and window, or are put in order first where that is quicker.
  * grid 0 (the default): one workgroup per record, the records taken in
  * the plain flat layout's XCD runs; a nonzero grid: that many
  * persistent workgroups taking the records round-robin in the same order.  Needs

@@ -586,15 +586,14 @@ int plan_launch_staged(nn_batch_plan* p, uint32_t nd, void* out, hipStream_t str
         return fail(NN_ERANGE, "batch of %llu rows, plan holds %llu", (unsigned long long)rows,
                     (unsigned long long)p->cap_rows);
     // The chunked kernel's owned mode (one record, and one workgroup, per
-    // chunk) needs the non-empty windows sorted by output offset and
-    // disjoint.  Windows are independent, so they are sorted here if they
-    // are not (a server's batches come in admission order); overlapping
-    // windows take a record per chunk and window.
+    // chunk) needs the non-empty windows in output order and disjoint.  Others
+    // take a record per chunk and window, unless they are worth sorting first
+    // (windows are independent).
     bool owned = p->chunks;
     if (owned) {
         bool sorted = true;
         for (uint32_t k = 1; k < nd && sorted; ++k) sorted = dd[k - 1].out_off <= dd[k].out_off;
-        if (!sorted)
+        if (!sorted && batch_sorts(p->nontemporal, rows, nd))
             std::sort(dd, dd + nd,
                       [](const BatchDesc& x, const BatchDesc& y) { return x.out_off < y.out_off; });
     }

@@ -58,7 +58,18 @@ static void batch_capacity() {
     }
 }
 
+// Windows out of order are sorted on the host only where the kernel's time is
+// long beside it: never with non-temporal stores, nor for short windows.
+static void batch_order() {
+    for (uint64_t n : {129ull, 9999ull, 1ull << 20}) {
+        CHECK(!nn::batch_sorts(true, n * 1000, n));
+        CHECK(!nn::batch_sorts(false, n * 4, n));
+        CHECK(!nn::batch_sorts(false, n * 32 - 1, n) && nn::batch_sorts(false, n * 32, n));
+    }
+}
+
 int main() {
+    batch_order();
     consume_workgroups();
     batch_capacity();
     if (fails) {

@@ -201,6 +201,29 @@ def test_chunked_batch_unsorted_windows(temporal):
         assert f == orc.skip(s, n)
 
 
+@pytest.mark.parametrize("temporal", [False, True])
+@pytest.mark.parametrize("longest", [3, 900, 200_000])
+def test_many_windows_out_of_order(longest, temporal):
+    """More windows than travel in the kernel arguments, shuffled: dozens to a
+    chunk, several to a chunk, and many chunks each (put in order first with
+    temporal stores), some empty; on a plan without a kernel, on a chunked one
+    and on a chunked one with few workgroups."""
+    rng = np.random.default_rng(longest)
+    lengths = [int(x) for x in rng.integers(longest // 2 + 1, longest + 1, 140)]
+    lengths[5] = lengths[77] = 0
+    states, lengths, offsets, total = _mixed_batch(73 + longest, lengths)
+    perm = rng.permutation(len(lengths))
+    st, ln, of = states[perm], lengths[perm], offsets[perm]
+    for kind, dt in (("u64", torch.uint64), ("f64", torch.float64)):
+        for kw in (dict(), dict(chunks=True), dict(chunks=True, grid=5)):
+            buf = _sentinel(total)
+            with nn.BatchPlan(kind, len(lengths), total, temporal=temporal, **kw) as plan:
+                fin = plan.generate(st, ln, of, buf.view(dt), final_states=True)
+                torch.cuda.synchronize()
+            _check_batch(_bits(buf), st, ln, of, kind)
+            assert fin.tolist() == [orc.skip(int(s), int(k)) for s, k in zip(st, ln)]
+
+
 @pytest.mark.parametrize("kind", ["u64", "f64"])
 @pytest.mark.parametrize("n", [1, 16, 17, 63, 64, 65, 127, 128, 129])
 def test_few_windows_default_chunked_and_static(kind, n):
