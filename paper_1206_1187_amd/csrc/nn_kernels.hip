@@ -630,13 +630,16 @@ static hipError_t flat_one(uint32_t lds, hipStream_t s, const FlatArgs& a) {
     return hipGetLastError();
 }
 
-// Chunks of two rows take the FP64 reduction's balanced form (kFlatFastRows).
-template <class V>
+// Chunks of two rows with temporal stores take the FP64 reduction's balanced
+// form (kFlatFastRows).  Non-temporal ones are spaced better by the longer step:
+// two rows at cap 4, u64 2^26 + 5 outputs 81.0 against 83.7 us, 2^28 295 against
+// 317, 2^30 1207 against 1251; f64 2^28 314 against 318, 2^30 1242 against 1248.
+template <class V, bool NT>
 struct TwoRows {
     typedef V T;
 };
 template <>
-struct TwoRows<VarFP64> {
+struct TwoRows<VarFP64, false> {
     typedef VarBal T;
 };
 
@@ -644,7 +647,7 @@ template <class V, int KIND, bool NT>
 static hipError_t flat_r(int rows, uint32_t lds, hipStream_t s, const FlatArgs& a) {
     switch (rows) {
         case 1: return flat_one<V, KIND, NT, 1>(lds, s, a);
-        case 2: return flat_one<typename TwoRows<V>::T, KIND, NT, 2>(lds, s, a);
+        case 2: return flat_one<typename TwoRows<V, NT>::T, KIND, NT, 2>(lds, s, a);
         case 4: return flat_one<V, KIND, NT, 4>(lds, s, a);
         case 8: return flat_one<V, KIND, NT, 8>(lds, s, a);
         case 16: return flat_one<V, KIND, NT, 16>(lds, s, a);

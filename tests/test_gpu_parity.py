@@ -188,6 +188,27 @@ def test_flat_remainders_in_one_launch(rows, head):
 
 
 @pytest.mark.parametrize("kind", ["f64", "u64"])
+@pytest.mark.parametrize("temporal", [False, True])
+def test_two_rows_by_store_policy(kind, temporal):
+    """Two rows per workgroup take one form of the FP64 step with temporal
+    stores and another with non-temporal ones: partial chunks alone and after a
+    whole XCD run (4096 chunks), on 16- and 8-byte aligned outputs."""
+    z0 = orc.seed(wl.INDEX_MIN + 13)
+    per = 1024
+    ref, _ = orc.gen(z0, 4097 * per + 514, kind, threads=0)
+    for whole in (0, 3, 4096, 4097):
+        for rest in (0, 1, 513):
+            count = whole * per + rest
+            if not count:
+                continue
+            for guard in (512, 513):
+                got, zn = _gen_guarded(z0, count, kind, guard=guard,
+                                       cfg=nn.make_cfg(layout="flat", unroll=2, temporal=temporal))
+                assert np.array_equal(got, ref.view(np.uint64)[:count]), (whole, rest, guard)
+                assert zn == orc.skip(z0, count)
+
+
+@pytest.mark.parametrize("kind", ["f64", "u64"])
 @pytest.mark.parametrize("count", [(1 << 24) - 1, 1 << 24, (1 << 24) + 1025])
 def test_default_shape_on_both_sides_of_its_sizes(kind, count):
     """Without a cfg: four rows below 2^24 outputs, two rows of balanced states
