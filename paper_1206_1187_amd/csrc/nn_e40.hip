@@ -508,36 +508,10 @@ hipError_t launch(int kind, int mm, int ilp, int unroll, bool nt, uint32_t grid,
 
 }  // namespace
 
-// The flat layout's default shape, temporal stores (one chunk per workgroup, in
-// XCD runs): rows of 512 per chunk and resident workgroups per CU.  What bounds
-// it is how the stores of a workgroup are spaced, more than the arithmetic: with
-// the 15-instruction step 16 rows at 4 write slower than with 20 instructions,
-// and other shapes faster.  Medians over two machines, 2^28 and 100,000,007 outputs:
-//   f64 (25.8 VALU instructions an output): 8 rows at 3 311 and 122 us; 16 at 4
-//     355 and 137; 8 at 4 333 and 130; 8 at 2 with non-temporal stores 306 and 118,
-//     but 43.1 against 39.6 at 2^25 (two limbs of 3^20, 30.3 an output, 16 at 4: 335
-//     and 138, 8 at 3 326);
-//   u64 (30.8): 16 rows at 2 339 and 125; 16 at 4 336 and 135; 8 at 3 341 and 129; 8
-//     at 3 non-temporal 330 and 124, but 43.3 against 40.5 at 2^25 (two limbs, 16 at
-//     4: 350 and 132).
-// Montgomery's step keeps 16 rows at 4.
-struct E40Shape {
-    uint32_t rows, occupancy;
-};
-inline E40Shape e40_shape(int kind, int mm) {
-    if (mm == 0) return {16, kFlatDefaultOccupancy};
-    return kind == NN_OUT_F64 ? E40Shape{8, 3} : E40Shape{16, 2};
-}
-
-// An output too short to give every CU two such chunks takes shorter ones
-// (halved down to 2 rows): its time is a workgroup's own chain of rows.  Kernel
-// times with 16 rows and by this rule, two limbs, f64 (u64): 200,003 outputs 4.16
-// and 2.74 us (4.34, 2.80), 2^20 5.12 and 4.46 (5.26, 4.38).
-
 // nn_e40_generate_ex's flat layout (arguments already validated: a valid
 // state, count > 0, an in-range pointer).  cfg: unroll = rows of 512
 // outputs per chunk (2, 4, 8, 16, 32; default by size), grid = workgroups per launch
-// (0: one per chunk), occupancy = residency cap (0: e40_shape), store policy
+// (0: one per chunk), occupancy = residency cap (0: flat_occupancy), store policy
 // (default temporal).
 int generate_flat(uint64_t* state, uint64_t count, void* out_dev, int kind, void* stream,
                   const nn_launch_cfg& c, int mm) {
@@ -553,17 +527,16 @@ int generate_flat(uint64_t* state, uint64_t count, void* out_dev, int kind, void
     DeviceTables* d = nullptr;
     st = current_device(&d);
     if (st) return st;
-    const E40Shape shape = e40_shape(kind, mm);
-    const uint32_t occ = c.occupancy ? c.occupancy : shape.occupancy;
+    uint32_t rows = c.unroll ? c.unroll : flat_rows(kind, mm);
+    if (!c.unroll && !c.grid)
+        rows = flat_rows_for(rows, count, d->cus > 0 ? (uint32_t)d->cus : 1u);
+    const uint32_t occ = c.occupancy ? c.occupancy : flat_occupancy(mm, rows);
     if (occ < 2 || occ > 16) return fail(NN_EINVAL, "occupancy %u: must be 0 or in [2, 16]", occ);
     const uint32_t lds = (d->lds_per_cu / (occ + 1) / 512 + 1) * 512;
     if (lds > d->lds_per_block || (uint64_t)lds * occ > d->lds_per_cu)
         return fail(NN_EINVAL, "occupancy %u not expressible on this device", occ);
     const bool nt = (c.flags & NN_CFG_NONTEMPORAL_STORES) != 0;
     const uint64_t s = *state;
-    uint32_t rows = c.unroll ? c.unroll : shape.rows;
-    if (!c.unroll && !c.grid)
-        while (rows > 2 && count / (512ull * rows) < 2ull * (d->cus > 0 ? d->cus : 1)) rows /= 2;
     const uint64_t per = 512ull * rows;
     const uint64_t max_launch = kFlatMaxRows * 512;
     E40FlatArgs a = {};

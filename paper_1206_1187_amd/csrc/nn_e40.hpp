@@ -220,5 +220,42 @@ inline Mult40T make_mult40t(uint64_t v) {
     return Mult40T{x.x0, x.x1, x.x2};
 }
 
+// ------------------------------------------------ the flat layout's shape --
+// Rows of 512 outputs per chunk and resident workgroups per CU, one chunk per
+// workgroup in XCD runs.  What bounds the FP64 step's kernels is how the stores of
+// a compute unit's workgroups are spaced, more than the arithmetic, and that is a
+// matter of rows times residency: the best residency falls as the rows grow, for
+// both kinds and store policies.  Medians, 2^28 and 100,000,007 outputs, us:
+//   rows           cap 2       3           4           6           8
+//    2  f64        478 183     386 147     368 134     345 134     336 132
+//    4             384 153     332 127     316 122     313 127     315 131
+//    8             330 125     311 124     332 129     341 132     345 133
+//   16             327 129     349 136     351 140     353 140     355 141
+//    2  u64        475 190     407 154     405 142     377 147     368 145
+//    4             393 154     355 131     335 124     346 129     343 131
+//    8             346 133     312 122     319 128     327 130     325 131
+//   16             328 122     326 136     353 138     365 142     364 143
+// 32 rows: 357 140 (f64) and 357 136 (u64) at 2, 364 144 and 373 143 at 4.  One cap
+// for every row count would cost up to a third: u64, 2^24 outputs, two rows 32.8
+// us at 2 and 23.9 at 6.  Montgomery's step, bound by its arithmetic, keeps 4.
+inline uint32_t flat_occupancy(int mm, uint32_t rows) {
+    if (mm == 0) return 4;
+    return rows <= 2 ? 6 : rows == 4 ? 4 : rows == 8 ? 3 : 2;
+}
+
+// The default rows (kind 0 u64, 1 f64).  f64 (25.8 VALU instructions an output)
+// is fastest with 8; u64 (30.8) with 8 or 16 alike within the spread of machines
+// (2^26 + 5 outputs 83.8 and 84.2 us, 2^28 312-331 and 325-330).
+inline uint32_t flat_rows(int kind, int mm) { return mm == 1 && kind == 1 ? 8 : 16; }
+
+// An output too short to give every CU two such chunks takes shorter ones
+// (halved down to 2 rows): its time is a workgroup's own chain of rows.  Kernel
+// times, f64 (u64): 200,003 outputs with 16 rows 3.84 (4.34) us, by this rule 2.70
+// (2.74); 2^20 4.66 (5.16) and 4.08 (4.28).
+inline uint32_t flat_rows_for(uint32_t rows, uint64_t count, uint32_t cus) {
+    while (rows > 2 && count / (512ull * rows) < 2ull * cus) rows /= 2;
+    return rows;
+}
+
 }  // namespace e40
 }  // namespace nn

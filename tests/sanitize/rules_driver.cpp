@@ -6,6 +6,7 @@
 #include <stdio.h>
 
 #include "nn_batch.hpp"
+#include "nn_e40.hpp"
 #include "nn_kernels.hpp"
 
 static int fails = 0;
@@ -68,7 +69,28 @@ static void batch_order() {
     }
 }
 
+// Modulus 3^40, flat layout: the residency cap goes with the rows actually taken
+// (a caller's or the size rule's), fewer workgroups the longer their chunks.
+static void e40_shapes() {
+    namespace e = nn::e40;
+    for (uint32_t rows = 2; rows <= 32; rows *= 2) {
+        CHECK(e::flat_occupancy(0, rows) == 4);
+        const uint32_t cap = e::flat_occupancy(1, rows);
+        CHECK(cap >= 2 && cap <= 16 && cap * rows >= 12 && cap * rows <= 64);
+        CHECK(rows == 2 || cap <= e::flat_occupancy(1, rows / 2));
+    }
+    for (int kind = 0; kind < 2; ++kind)
+        for (uint64_t count : {1ull, 200003ull, 3000017ull, (1ull << 22) - 1, 1ull << 22,
+                               1ull << 23, 1ull << 30}) {
+            const uint32_t most = e::flat_rows(kind, 1), rows = e::flat_rows_for(most, count, 256);
+            CHECK(rows >= 2 && rows <= most);
+            CHECK(rows == 2 || count / (512 * rows) >= 512);
+            CHECK(rows == most || count / (1024 * rows) < 512);
+        }
+}
+
 int main() {
+    e40_shapes();
     batch_order();
     consume_workgroups();
     batch_capacity();
