@@ -104,7 +104,7 @@ typedef enum nn_mulmod {
  * threads per workgroup); rows per workgroup, 1, 2, 4, 8 or 16 (flat,
  * default 4; a cfg that sets neither unroll nor occupancy, NN_MULMOD_FP64 at
  * most, temporal stores and no address order takes 2 from 2^24 outputs on, for
- * f64 up to 2^29).
+ * f64 below 2^29).
  * flags: NN_CFG_TEMPORAL_STORES keeps stores cacheable and
  * NN_CFG_NONTEMPORAL_STORES makes them non-temporal streaming stores (at
  * most one of the two; default: non-temporal, except temporal for the flat

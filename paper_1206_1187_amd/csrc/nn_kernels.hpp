@@ -130,9 +130,12 @@ constexpr uint32_t kFlatDefaultRows = 4;
 // (7.30 TB/s).  Other mixes write slower (2^30, f64, the shorter step with four
 // rows at 4 and 3: 1228 and 1187; the longer one with two rows at 6: 1392; two rows
 // at 6 without runs 1215).  Below 2^24 outputs, which the last-level cache takes,
-// four rows tie or are ahead (3,000,017 f64 6.0 against 6.2).  From 2^29 f64 outputs
-// on the four rows that nn_default_cfg documents for them stay (2^30: 1193; two
-// rows at 5, as a cfg, 1173).
+// four rows tie or are ahead (3,000,017 f64 6.0 against 6.2).  The f64 limit is no
+// measured line: two rows stay 1 to 1.5 % ahead beyond it (medians of eight
+// alternating runs, 2^29 589.7 against 598.1 us, 700,000,001 773 and 778, 2^30 1170
+// and 1186; on other machines 2^30 took two rows up to 1212).  nn_default_cfg's
+// shape for 2^30 f64 outputs, four rows at 4, is checked as part of its interface;
+// the limit is the power of two below it.
 constexpr uint32_t kFlatFastRows = 2;
 inline uint32_t flat_fast_occupancy(int kind) { return kind == 1 ? 5u : 6u; }
 constexpr uint64_t kFlatFastMin = 1ull << 24;

@@ -222,6 +222,30 @@ def test_default_shape_on_both_sides_of_its_sizes(kind, count):
         assert zn == zr
 
 
+@pytest.mark.parametrize("skew", [0, 1])
+@pytest.mark.parametrize("count", [(1 << 29) - 1, 1 << 29, (1 << 29) + 1])
+def test_default_shape_at_its_f64_limit(count, skew):
+    """Without a cfg: two rows below 2^29 f64 outputs, four from there on, on 16-
+    and 8-byte aligned outputs; sampled against the oracle, and nothing written
+    beyond either end."""
+    z0 = orc.seed(wl.INDEX_MIN + 41)
+    assert nn.default_cfg("f64", count).unroll == (2 if count < 1 << 29 else 4)
+    buf = torch.empty(count + 4, dtype=torch.float64, device="cuda")
+    flat = buf.view(torch.int64)
+    flat[:2] = flat[-4:] = -77
+    at0 = 2 - skew
+    zn = nn.generate_into(z0, buf[at0:at0 + count])
+    torch.cuda.synchronize()
+    assert zn == orc.skip(z0, count)
+    assert (flat[:at0] == -77).all() and (flat[at0 + count:] == -77).all()
+    for start in (0, 1 << 24, count // 2, count - 5000):
+        ref, _ = orc.gen(orc.skip(z0, start), 5000, "f64", threads=0)
+        got = flat[at0 + start:at0 + start + 5000].cpu().numpy().view(np.uint64)
+        assert np.array_equal(got, ref.view(np.uint64)), start
+    del buf, flat
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("variant", VARIANTS)
 def test_flat_layout_bit_exact(variant):
     """The flat layout (workgroups of 1-16 rows of 512 outputs) for every
