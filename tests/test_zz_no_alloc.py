@@ -107,6 +107,21 @@ def test_static_batch_descriptor_scan(n):
     _check_oracle(_bits(got), states, lengths, offsets, "u64")
 
 
+@pytest.mark.parametrize("n", [511, 512, 513, 1024, 1536, 1537])
+def test_static_batch_scan_workgroups(n):
+    """Windows on both sides of the 512 descriptors that one workgroup of the
+    scan takes: a lone descriptor in a second and a fourth workgroup, whole
+    workgroups, every third window empty, some over several chunks."""
+    states, lengths, offsets, total = _batch(190 + n, n, 13)
+    lengths[::3] = 0
+    for kind, dt in (("u64", torch.uint64), ("f64", torch.float64)):
+        got = _sentinel(total).view(dt)
+        fin = nn.generate_batch_static(states, lengths, offsets, got, final_states=True)
+        torch.cuda.synchronize()
+        assert fin.tolist() == [orc.skip(int(s), int(k)) for s, k in zip(states, lengths)]
+        _check_oracle(_bits(got), states, lengths, offsets, kind)
+
+
 def test_static_batch_empty_and_limits():
     """No streams, only empty windows: nothing written, states unchanged;
     more streams than the workspace holds: NN_ERANGE before any launch."""
