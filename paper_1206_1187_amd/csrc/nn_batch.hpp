@@ -266,6 +266,14 @@ struct BatchFlatInline {
     FlatWin w[N];
 };
 constexpr uint32_t kFlatInlineDescs = 128;
+// Outputs up to which a server's lane that runs beside others sends 17 to
+// kFlatInlineDescs windows this way.  Two such kernels at a time hold each other
+// up, which the shorter start of the record kernel's workgroups does not; a
+// shorter batch is bound by its launches instead.  The served trace 64 times
+// faster on two lanes, in 10^9 outputs a second by the longest batch: 2^25 778
+// against 697 with records, 2^26 810 and 788, 2^27 796 and 821.  (One lane, 2^27:
+// 771 and 719.)
+constexpr uint64_t kInlineBesideMax = 1ull << 26;
 
 // grid = the windows' chunks in total; lds caps residency as for the
 // plain flat layout.  N is kInlineDescs or kFlatInlineDescs.

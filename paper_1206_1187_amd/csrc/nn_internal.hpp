@@ -93,6 +93,7 @@ struct nn_batch_plan {
     char* pinned = nullptr;           // both slots' staging
     nn_batch_slot slot[2];
     int next = 0;  // the slot of the next batch
+    bool beside = false;  // a server's lane that runs beside others (kInlineBesideMax)
 };
 
 namespace nn {

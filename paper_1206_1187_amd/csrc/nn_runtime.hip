@@ -493,12 +493,14 @@ bool flat_inline(const nn_batch_plan* p, const BatchDesc* dd, uint32_t nd) {
     if (p->mulmod != NN_MULMOD_FP64 || (p->indexed && !p->host_states)) return false;
     const bool few = nd <= kInlineDescs;
     if (!few && (nd > kFlatInlineDescs || !p->chunks || p->grid)) return false;
+    uint64_t outputs = 0;
     for (uint32_t k = 0; k < nd; ++k) {
         // a window's chunks are counted in the flat layout's row tables
         if (dd[k].len > kFlatMaxCount - kInlineAlign) return false;
         if (!few && dd[k].out_off + dd[k].len > (1ull << 51)) return false;  // refused below
+        outputs += dd[k].len;
     }
-    return true;
+    return few || !p->beside || outputs <= kInlineBesideMax;
 }
 
 namespace {

@@ -480,6 +480,7 @@ int nn_server_create(const nn_server_cfg* cfg, const uint64_t* stream_states, ui
             server_free(s);
             return st;
         }
+        l.plan->beside = c.lanes > 1;
     }
     if (c.flags & NN_SERVER_DEVICE_QUEUE) {
         int st = queue_create((int)c.kind, c.queue_workgroups, c.queue_capacity, c.queue_idle_s,

@@ -41,6 +41,63 @@ LANE_SHAPES = {"blocked": {}, "interleaved": dict(interleaved=True, block=128),
                "chunked": dict(chunks=True, temporal=True)}
 
 
+@pytest.mark.parametrize("lanes", [1, 2])
+@pytest.mark.parametrize("size", [(1 << 26) // 40, (1 << 26) // 40 + 1, 1 << 21])
+def test_served_bursts_of_few_long_requests(lanes, size):
+    """Forty requests of one burst, 2^26 outputs together and more: up to there a
+    lane beside others sends them in the kernel arguments, above through the
+    record pre-pass; on a lane alone always the former.  Sampled against the
+    oracle."""
+    states = _states(5, 31)
+    with serve.Server(states, 1 << 30, kind="u64", lanes=lanes) as srv:
+        for burst in range(2):
+            tickets = [srv.submit(i % 5, size) for i in range(40)]
+            done = {}
+            while len(done) < 40:
+                for c in srv.poll():
+                    done[c.ticket] = c
+            for i, t in enumerate(tickets):
+                c = done[t]
+                assert c.status == 0 and c.count == size
+                pos = (8 * burst + i // 5) * size
+                got = srv.data(c).view(torch.int64)
+                for at in (0, size // 2, size - 300):
+                    ref, _ = orc.gen(orc.skip(int(states[i % 5]), pos + at), 300, "u64")
+                    assert np.array_equal(_bits(got[at:at + 300]), ref), (burst, i, at)
+            for t in tickets:
+                srv.release(t)
+
+
+@pytest.mark.parametrize("kind", ["f64", "u64"])
+@pytest.mark.parametrize("shape", [dict(), dict(block=256), dict(chunks=True, temporal=True),
+                                   dict(chunks=True, grid=7)])
+def test_served_batches_of_many_requests(kind, shape):
+    """Batches of more requests than travel in the kernel arguments, on every
+    lane kernel, with released regions reused so that pool offsets come out of
+    order."""
+    states = _states(6, 33)
+    rng = np.random.default_rng(34)
+    sizes = [int(x) for x in np.exp(rng.uniform(0, np.log(30_000.0), 600))]
+    pos = [0] * 6
+    with serve.Server(states, 12 << 20, kind=kind, lanes=2, **shape) as srv:
+        for burst in range(3):
+            want = []
+            for i in range(200):
+                n = sizes[200 * burst + i]
+                want.append((srv.submit(i % 6, n), i % 6, pos[i % 6], n))
+                pos[i % 6] += n
+            done = {}
+            while len(done) < 200:
+                for c in srv.poll():
+                    done[c.ticket] = c
+            order = rng.permutation(200)
+            for t, stream, at, n in want:
+                ref, _ = orc.gen(orc.skip(int(states[stream]), at), n, kind)
+                assert np.array_equal(_bits(srv.data(done[t])), ref.view(np.uint64)), (burst, t)
+            for k in order:
+                srv.release(want[k][0])
+
+
 @pytest.mark.parametrize("kind,shape", [("f64", "blocked"), ("u64", "blocked"),
                                         ("f64", "interleaved"), ("u64", "interleaved"),
                                         ("f64", "chunked"), ("u64", "chunked")])
