@@ -246,6 +246,40 @@ def test_default_shape_at_its_f64_limit(count, skew):
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("what", ["f64", "u64", "e40_u64", "fill"])
+def test_beyond_one_launch_unaligned(what):
+    """More than 2^30 outputs into an output that is only 8-byte aligned: the
+    first launch takes the head element beside its 2^30, the second starts one
+    later; sampled against the oracle around both, nothing written beyond."""
+    count = (1 << 30) + 1 + 2051
+    buf = torch.empty(count + 4, dtype=torch.int64, device="cuda")
+    buf[:2] = buf[-4:] = -77
+    at0 = 1
+    out = buf[at0:at0 + count].view(torch.uint64 if "u64" in what else torch.float64)
+    z0 = (orc.e40_seed if "e40" in what else orc.seed)(orc.E40_INDEX_MIN + 3 if "e40" in what
+                                                      else wl.INDEX_MIN + 3)
+    if what == "fill":
+        nn.fill(out, 0x3FF0000000000001)
+        assert (buf[at0:at0 + count] == 0x3FF0000000000001).all()
+    elif "e40" in what:
+        assert nn.e40_generate_into(z0, out) == orc.e40_skip(z0, count)
+    else:
+        assert nn.generate_into(z0, out) == orc.skip(z0, count)
+    torch.cuda.synchronize()
+    assert buf[0] == -77 and (buf[at0 + count:] == -77).all()
+    for start, n in ((0, 3000), (123_456_789, 3000), ((1 << 30) - 1500, 1501 + 2051)):
+        if what == "fill":
+            break
+        if "e40" in what:
+            ref, _ = orc.e40_gen(orc.e40_skip(z0, start), n, "u64")
+        else:
+            ref, _ = orc.gen(orc.skip(z0, start), n, what, threads=0)
+        got = buf[at0 + start:at0 + start + n].cpu().numpy().view(np.uint64)
+        assert np.array_equal(got, ref.view(np.uint64)), start
+    del buf, out
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("variant", VARIANTS)
 def test_flat_layout_bit_exact(variant):
     """The flat layout (workgroups of 1-16 rows of 512 outputs) for every
