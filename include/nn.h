@@ -140,7 +140,7 @@ typedef struct nn_launch_cfg {
  * NN_MULMOD_MODBARRETT; grid, width, ilp and occupancy must be 0. */
 #define NN_CFG_PAPER_STRIDED 16u
 #define NN_CFG_NONTEMPORAL_STORES 32u
-/* Flat layout with 4 rows: the whole chunks in address order (workgroup w
+/* Flat layout with 2 or 4 rows: the whole chunks in address order (workgroup w
  * writes chunk w) instead of the default XCD runs; for comparison. */
 #define NN_CFG_ADDRESS_ORDER 128u
 
@@ -280,7 +280,8 @@ typedef struct nn_stream_desc {
  * workgroups (a multiple of cluster); cluster: 1..64 (interleaved: up to
  * grid; 0 = grid); mulmod: an
  * nn_mulmod; flags: NN_CFG_TEMPORAL_STORES, NN_BATCH_NO_GRAPH (enqueue a
- * copy and a kernel launch instead of replaying the plan's graph),
+ * copy and a kernel launch instead of replaying the plan's graph; the chunked
+ * kernel has no graph and takes the flag without effect),
  * NN_BATCH_INTERLEAVED, NN_BATCH_CHUNKS.  A cfg that names no kernel (neither
  * of those two, block, grid and cluster 0, mulmod 0 or NN_MULMOD_FP64) gets
  * the chunked one, with non-temporal stores at an occupancy of 3, if

@@ -299,8 +299,13 @@ def generate_batch_static(states, lengths, out_offsets, out, stream=None, final_
 
 
 class BatchPlan:
-    """A batch plan (include/nn.h, nn_batch_plan): many streams generated by
-    one persistent kernel replayed from a hipGraph.
+    """A batch plan (include/nn.h, nn_batch_plan): many streams generated in one
+    call.  Without a kernel named (``block``, ``grid``, ``cluster``,
+    ``interleaved``, another ``mulmod``) it is the chunked one: up to 128 windows
+    in the arguments of one launch, more in a record pre-pass and a launch with a
+    workgroup per 16 KiB chunk.  The others are persistent kernels replayed from a
+    hipGraph, or with ``graph=False`` launched directly; a chunked plan has no
+    graph either way.
 
         plan = BatchPlan("f64", max_streams=10000, max_outputs=1 << 32)
         final = plan.generate(states, lengths, offsets, out)   # out: cuda tensor

@@ -31,8 +31,9 @@ struct BatchDesc {
 
 constexpr uint64_t kBatchMaxLen = 1ull << 24;
 
-// Device workspace image, uploaded per batch as one contiguous block:
-// the header, then n_desc descriptors.
+// A batch's staging area, the header and then n_desc descriptors: uploaded as one
+// block for the blocked and interleaved kernels; the chunked kernel's pre-pass
+// reads the descriptors where they are, in pinned host memory.
 struct BatchHeader {
     uint64_t* out;
     uint32_t n_desc;
@@ -91,9 +92,9 @@ constexpr uint32_t kRecChunk = 4096;
 // Kernel arguments (fixed for the life of a plan but for the batch's own:
 // n_rec, out, n_desc and mode).
 struct BatchArgs {
-    // Chunked kernel: its record array and, set for each batch (the plan
-    // updates its graph node's arguments with the grid), the record count and
-    // the output; record and count lead, so one scalar load fetches both.
+    // Chunked kernel: its record array and, set for each batch, the record
+    // count and the output; record and count lead, so one scalar load fetches
+    // both.
     RowRec* rec;            // row records (device workspace; interleaved kernels too)
     uint64_t n_rec;
     uint64_t* out;

@@ -29,7 +29,7 @@ struct Resolved {
     uint32_t block, grid, mulmod, unroll, width, occupancy, ilp;
     bool nontemporal, flat, consec, strided;
     bool small_unaligned;  // flat by the rule for small outputs that are only 8-byte aligned
-    bool xcd_runs;  // flat, 4 rows: whole chunks in XCD runs (NN_CFG_ADDRESS_ORDER clears it)
+    bool xcd_runs;  // flat, 2 or 4 rows: whole chunks in XCD runs (NN_CFG_ADDRESS_ORDER clears it)
     uint32_t lds;  // dynamic LDS bytes per workgroup that cap residency
 };
 

@@ -121,8 +121,9 @@ inline BatchDesc* plan_staged_descs(nn_batch_plan* p) {
                                         1);
 }
 // Fills in the row prefix of the `nd` staged descriptors (their src, pos,
-// len and out_off set by the caller), uploads them and launches on
-// `stream`, and records the plan's completion event.  The caller checked
+// len and out_off set by the caller), uploads them where the plan's kernel reads
+// them from the device, launches on `stream`, and records the slot's completion
+// event.  The caller checked
 // nd <= p->cap_desc and holds p->mu.
 int plan_launch_staged(nn_batch_plan* p, uint32_t nd, void* out, hipStream_t stream);
 

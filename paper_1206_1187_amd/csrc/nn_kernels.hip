@@ -231,10 +231,12 @@ __global__ __launch_bounds__(1024) void k_consume(ConsumeArgs a, void* result) {
 //    three that split it into multiples of 2^26 (added to hi, which starts at
 //    1.5 * 2^78 where the unit is 2^26) and the rest (below 2^26, added to
 //    lo): exact for 2^24 pairs, so hi and lo are emptied every 2^20 trips.
-// Four rows in flight per thread: four independent chains.  2^30 variates: 258
-// us, 4.16e12 a second (85 % of the VALU's rate for eight instructions an
-// output at 2.4 GHz), against 421 us with nn_dev_mulmod's step and a
-// conversion per variate; 2^30 raw states 304 us against 600.
+// Four rows in flight per thread: four independent chains.  2^30 variates back to
+// back: 246-258 us, 4.2-4.4e12 a second (85-89 % of the VALU's rate for eight
+// instructions an output at 2.4 GHz), against 402-421 us with nn_dev_mulmod's step
+// and a conversion per variate; 2^30 raw states 300-304 us against 532-600.  After
+// a minute of launches bound by HBM, at the clock these leave, 278-283 and
+// 350-360 us (before: 427 and 604).
 template <int KIND>
 __global__ __launch_bounds__(1024) void k_consume_bal(ConsumeArgs a, void* result) {
     constexpr double kSplit = 453347182355485940514816.0;  // 1.5 * 2^78

@@ -152,9 +152,9 @@ constexpr uint32_t kFlatSymEntries = kFlatSymHi + kFlatHiSize;
 hipError_t upload_flat_symbol(const Mult* entries);
 
 // XCD runs: the 8 XCDs take consecutive workgroups in turn, so with chunks in
-// workgroup order each XCD writes every eighth 16 KiB chunk.  With four rows
-// per workgroup the whole chunks are taken in runs of 8*kFlatXcdRun
-// workgroups instead, in which XCD x writes the kFlatXcdRun consecutive
+// workgroup order each XCD writes every eighth chunk.  With two or four rows per
+// workgroup the whole chunks are taken in runs instead, with four rows of
+// 8*kFlatXcdRun workgroups, in which XCD x writes the kFlatXcdRun consecutive
 // chunks [x kFlatXcdRun, (x + 1) kFlatXcdRun) of the run (4 MiB).  Whole
 // chunks beyond the last full run keep workgroup order.
 constexpr uint32_t kFlatXcds = 8;

@@ -151,10 +151,10 @@ def pick_plain_grid(cfg, out, state, deltas, rounds=3, reps=5):
 
 def pick_plain_layout(cfg, out, state, rounds=3, reps=5):
     """`cfg` (a row-layout nn_launch_cfg, NN_CFG_ROWS set) or the flat layout
-    at its library defaults (fields 0: four 512-output rows per workgroup,
-    temporal stores, residency cap 4), whichever runs faster on the current
-    device (on an output that is only 8-byte aligned the flat layout writes
-    its first element alone).  Returns (cfg, {"rows": ms, "flat": ms})."""
+    at its library defaults (fields 0: two or four 512-output rows per
+    workgroup by kind and size, temporal stores), whichever runs faster on the
+    current device (on an output that is only 8-byte aligned the flat layout
+    writes its first element alone).  Returns (cfg, {"rows": ms, "flat": ms})."""
     import paper_1206_1187_amd as nn
     flat = nn.make_cfg(layout="flat", mulmod=int(cfg.mulmod))
     cands = {"rows": cfg, "flat": flat}
