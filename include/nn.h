@@ -569,8 +569,8 @@ int nn_e40_skip(uint64_t state, uint64_t k, uint64_t *state_out);
  * per chunk of `unroll` rows of 512 outputs (2, 4, 8, 16, 32; default 8 for
  * f64 and 16 for u64, or fewer where the output would not give every compute
  * unit two chunks), residency capped by `occupancy` (default by the rows: 6 with
- * 2, 4 with 4, 3 with 8, 2 with more; Montgomery's step: 16 rows, 4); with one
- * workgroup per chunk
+ * 2, 4 with 4, 3 with 8 (2 for f64 with non-temporal stores), 2 with more;
+ * Montgomery's step: 16 rows, 4); with one workgroup per chunk
  * (grid 0) the chunks are taken in XCD runs of 4 MiB per XCD as in the 3^33
  * flat layout; the launch also writes the first element of an output that is
  * only 8-byte aligned (below 2^22 outputs a cfg that sets grid, unroll or

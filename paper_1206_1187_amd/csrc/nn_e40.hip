@@ -530,12 +530,12 @@ int generate_flat(uint64_t* state, uint64_t count, void* out_dev, int kind, void
     uint32_t rows = c.unroll ? c.unroll : flat_rows(kind, mm);
     if (!c.unroll && !c.grid)
         rows = flat_rows_for(rows, count, d->cus > 0 ? (uint32_t)d->cus : 1u);
-    const uint32_t occ = c.occupancy ? c.occupancy : flat_occupancy(mm, rows);
+    const bool nt = (c.flags & NN_CFG_NONTEMPORAL_STORES) != 0;
+    const uint32_t occ = c.occupancy ? c.occupancy : flat_occupancy(mm, kind, nt, rows);
     if (occ < 2 || occ > 16) return fail(NN_EINVAL, "occupancy %u: must be 0 or in [2, 16]", occ);
     const uint32_t lds = (d->lds_per_cu / (occ + 1) / 512 + 1) * 512;
     if (lds > d->lds_per_block || (uint64_t)lds * occ > d->lds_per_cu)
         return fail(NN_EINVAL, "occupancy %u not expressible on this device", occ);
-    const bool nt = (c.flags & NN_CFG_NONTEMPORAL_STORES) != 0;
     const uint64_t s = *state;
     const uint64_t per = 512ull * rows;
     const uint64_t max_launch = kFlatMaxRows * 512;

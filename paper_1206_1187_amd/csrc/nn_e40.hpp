@@ -235,12 +235,16 @@ inline Mult40T make_mult40t(uint64_t v) {
 //    4             393 154     355 131     335 124     346 129     343 131
 //    8             346 133     312 122     319 128     327 130     325 131
 //   16             328 122     326 136     353 138     365 142     364 143
-// 32 rows: 357 140 (f64) and 357 136 (u64) at 2, 364 144 and 373 143 at 4.  One cap
+// 32 rows: 357 140 (f64) and 357 136 (u64) at 2, 364 144 and 373 143 at 4.
+// Non-temporal stores follow the same line but for f64 with 8 rows, whose outputs
+// take the fewest instructions: 305 120 at 2, 326 130 at 3, 339 131 at 4 (u64 331 126,
+// 322 119 and 326 124).  One cap
 // for every row count would cost up to a third: u64, 2^24 outputs, two rows 32.8
 // us at 2 and 23.9 at 6.  Montgomery's step, bound by its arithmetic, keeps 4.
-inline uint32_t flat_occupancy(int mm, uint32_t rows) {
+inline uint32_t flat_occupancy(int mm, int kind, bool nontemporal, uint32_t rows) {
     if (mm == 0) return 4;
-    return rows <= 2 ? 6 : rows == 4 ? 4 : rows == 8 ? 3 : 2;
+    if (rows == 8) return kind == 1 && nontemporal ? 2 : 3;
+    return rows <= 2 ? 6 : rows == 4 ? 4 : 2;
 }
 
 // The default rows (kind 0 u64, 1 f64).  f64 (25.8 VALU instructions an output)

@@ -73,12 +73,14 @@ static void batch_order() {
 // (a caller's or the size rule's), fewer workgroups the longer their chunks.
 static void e40_shapes() {
     namespace e = nn::e40;
-    for (uint32_t rows = 2; rows <= 32; rows *= 2) {
-        CHECK(e::flat_occupancy(0, rows) == 4);
-        const uint32_t cap = e::flat_occupancy(1, rows);
-        CHECK(cap >= 2 && cap <= 16 && cap * rows >= 12 && cap * rows <= 64);
-        CHECK(rows == 2 || cap <= e::flat_occupancy(1, rows / 2));
-    }
+    for (int kind = 0; kind < 2; ++kind)
+        for (bool nt : {false, true})
+            for (uint32_t rows = 2; rows <= 32; rows *= 2) {
+                CHECK(e::flat_occupancy(0, kind, nt, rows) == 4);
+                const uint32_t cap = e::flat_occupancy(1, kind, nt, rows);
+                CHECK(cap >= 2 && cap <= 16 && cap * rows >= 12 && cap * rows <= 64);
+                CHECK(rows == 2 || cap <= e::flat_occupancy(1, kind, nt, rows / 2));
+            }
     for (int kind = 0; kind < 2; ++kind)
         for (uint64_t count : {1ull, 200003ull, 3000017ull, (1ull << 22) - 1, 1ull << 22,
                                1ull << 23, 1ull << 30}) {
